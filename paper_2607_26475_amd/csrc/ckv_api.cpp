@@ -369,6 +369,7 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
   a.chunk = 1;
   a.hist_part = nullptr;
   a.score_nwg = 0;
+  a.min_range = 1;
   a.units = d.U;
   a.mpart = nullptr;
   a.mout = nullptr;
@@ -404,6 +405,8 @@ ScoreArgs score_args(const Dims& d, const Layout& L, const uint16_t* q,
   a.units = d.U;
   a.chunk = 1;
   a.hist_part = nullptr;
+  a.min_range = 1;
+  a.tails = 0;
   return a;
 }
 
@@ -449,6 +452,8 @@ bool use_partials(const Dims& d, const Layout& L, int nwg) {
 }
 
 void set_partials(void* ws, const Layout& L, int nwg, ScoreArgs* sc, SelectArgs* sa) {
+  const int64_t gu = (sc->max_ctx + kStageRows - 1) / kStageRows;
+  sc->min_range = sa->min_range = min_range_groups(gu, kMaxPartials);
   sc->hist_part = at<uint32_t>(ws, L.hist_part);
   sa->hist_part = sc->hist_part;
   sa->score_nwg = nwg;
@@ -808,6 +813,7 @@ int ckv_score_keys(const ckv_shape* shape, const uint16_t* q, const uint16_t* k_
   Layout L = make_layout(d, 1, 0);
   if ((rc = check_grid(d, L))) return rc;
   ScoreArgs a = score_args(d, L, q, k_score, ctx_lens, scale, scores, nullptr);
+  a.tails = 1;
   CKV_TRY_HIP(launch_score(a, d.G, false, score_blocks(a, d.G, ScoreKind::kPlain),
                            (hipStream_t)stream),
               "score launch");

@@ -42,11 +42,10 @@ constexpr int kFusedSelectMaxCtx = 65536;
 // Scoring grids are capped at kMaxScoreWgs workgroups.  With per-workgroup
 // histograms (ScoreArgs::hist_part) the histogram of unit u is the sum of the
 // slots u + wg over the workgroups wg whose range meets the unit's groups
-// (all of them, below n_b or not: a range past n_b stores zeros, so the
-// slots to read follow from the shape alone); slot u + wg is unique because
-// ranges and units are both in group order.  The selection
-// reads at most kMaxPartials slots per unit, else the histograms are added
-// with atomics.
+// below n_b (both sides derive the ranges from ctx_lens); slot u + wg is
+// unique because ranges and units are both in group order.  The selection
+// reads at most kMaxPartials slots per unit (min_range keeps it so), else the
+// histograms are added with atomics.
 constexpr int kMaxScoreWgs = 1024;
 constexpr int kMaxPartials = 8;
 
@@ -88,6 +87,8 @@ struct ScoreArgs {
   float scale;
   int Hq, Hkv, max_ctx, units;
   int chunk;                // rows per scored entry: n_b rows give ceil(n_b/chunk) entries
+  int min_range;            // fewest groups of a workgroup's range (range_groups)
+  int tails;                // write -inf to every score at or past n_b (score_keys)
 };
 
 struct SelectArgs {
@@ -98,6 +99,7 @@ struct SelectArgs {
   uint32_t* ctrl;           // [U][kCtrlWords]
   const uint32_t* hist_part;  // non-null: the scoring pass wrote per-workgroup
   int score_nwg;            //   histograms with a grid of score_nwg workgroups
+  int min_range;            //   and ranges of at least min_range groups
   int units;
   int32_t* sel;             // [U][k]   positions above the digit-1 bin, then
                             //          the chosen candidates
@@ -115,7 +117,7 @@ struct SelectArgs {
   float* mout;              // [B][mHq][d]
   int mchunks, mG, mHq;
   // Non-zero: the slots come from the XCD-affine ranges of the one-launch
-  // same-step kernel (xcd_slot0), not from ranges in plain unit order.
+  // same-step kernel (hist_slots), not from ranges in plain unit order.
   int affine;
 };
 
@@ -228,38 +230,12 @@ struct MissArgs {
 // ceil(n_b / chunk), clamped to [0, hi].
 __device__ __forceinline__ int unit_len(int n_rows, int hi, int chunk) {
   const int n = max(n_rows, 0);
+  if (chunk == 1) return min(n, hi);  // uniform: no division for positions
   return min(n / chunk + (n % chunk != 0 ? 1 : 0), hi);
 }
 
 __device__ __forceinline__ int clamp_len(int n, int hi) {
   return n < 0 ? 0 : (n > hi ? hi : n);
-}
-
-// Workgroup of the balanced split of T groups over nwg workgroups (range
-// [wg*T/nwg, (wg+1)*T/nwg)) that holds group g.
-__host__ __device__ __forceinline__ int64_t range_owner(int64_t g, int64_t T, int64_t nwg) {
-  return ((g + 1) * nwg - 1) / T;
-}
-
-// The one-launch same-step kernel's scoring ranges: its scoring workgroups
-// are spread over the 8 XCDs round-robin by index, and the workgroups
-// x, x + 8, x + 16, ... (XCD x) score the units x, x + 8, x + 16, ... in
-// balanced contiguous ranges of those units' groups.  A unit's scores are
-// then written on the XCD where its selection and attention run (the same
-// index map, split_block), and the units of an XCD are complete as soon as
-// that XCD's ranges are.  Needs U and nwg multiples of 8.  The slot of (unit,
-// workgroup) is unique within XCD x's block of U/8 + nwg/8 slots, as in plain
-// unit order.  xcd_slot0 returns the first slot of `unit` and the number of
-// consecutive slots that hold its histogram.
-__host__ __device__ __forceinline__ int64_t xcd_slot0(int unit, int units, int nwg,
-                                                      int64_t gu, int* nslots) {
-  const int x = unit & 7, v = unit >> 3;
-  const int ux = units >> 3, nx = nwg >> 3;
-  const int64_t T = (int64_t)ux * gu;
-  const int64_t lo = range_owner((int64_t)v * gu, T, nx);
-  const int64_t hi = range_owner((int64_t)v * gu + gu - 1, T, nx);
-  *nslots = (int)(hi - lo + 1);
-  return (int64_t)x * (ux + nx) + v + lo;
 }
 
 // Monotone map from fp32 to uint32: a < b as floats <=> key(a) < key(b);
@@ -403,6 +379,130 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
 // Sum over the 64 lanes of a wave, the same in every lane.
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
   return __builtin_amdgcn_readlane(wave_incl_scan(x), 63);
+}
+
+// ---- the scoring pass's ranges ------------------------------------------------
+// The groups of kStageRows positions below n_b of all units, numbered
+// unit-major, are cut into equal ranges, one per scoring workgroup: work past
+// a request's length is not counted, so a ragged batch keeps every workgroup
+// busy (split by stored positions, a batch whose lengths average 77 % of
+// max_ctx took as long as a full one: 153 us per layer of 4 requests of up to
+// 131072 positions, 5.4 TB/s).  The numbering follows from ctx_lens alone, so
+// the selection finds a unit's slots without a hand-over.  Items are
+// requests (mult units each), or, for the XCD-affine ranges of the one-launch
+// kernel, units x, x + 8, ... of XCD x.  Valid groups fit in 32 bits: a group is
+// 8 KiB of keys.  All functions are wave-uniform and need all 64 lanes.
+__device__ __forceinline__ uint32_t groups_of(int n) {
+  return (uint32_t)(n + kStageRows - 1) / kStageRows;
+}
+
+struct GroupScan {
+  int n;       // entries per unit of this lane's item of the current 64
+  uint32_t s;  // inclusive sum of its groups
+};
+
+// Sum of the groups of the ni items (one unit each); *first: the scan of
+// items 0..63.  len(i): item i's entries per unit.
+template <class LEN>
+__device__ __forceinline__ uint32_t sum_groups(int ni, LEN len, GroupScan* first) {
+  const int lane = threadIdx.x & 63;
+  first->n = lane < ni ? len(lane) : 0;
+  first->s = wave_incl_scan(groups_of(first->n));
+  uint32_t t = __builtin_amdgcn_readlane(first->s, 63);
+  for (int i0 = 64; i0 < ni; i0 += 64)
+    t += wave_sum_u32(i0 + lane < ni ? groups_of(len(i0 + lane)) : 0u);
+  return t;
+}
+
+// Groups before item `item` (of one unit per item), and its entries in *n.
+template <class LEN>
+__device__ __forceinline__ uint32_t groups_before(int item, LEN len, GroupScan first, int* n) {
+  const int lane = threadIdx.x & 63;
+  uint32_t base = 0u;
+  int i0 = 0;
+  for (; item >= i0 + 64;) {
+    base += __builtin_amdgcn_readlane(first.s, 63);
+    i0 += 64;
+    first.n = i0 + lane <= item ? len(i0 + lane) : 0;  // items past `item` are not needed
+    first.s = wave_incl_scan(groups_of(first.n));
+  }
+  const int l = __builtin_amdgcn_readfirstlane(item - i0);
+  *n = __builtin_amdgcn_readlane(first.n, l);
+  return base + __builtin_amdgcn_readlane(first.s, l) - groups_of(*n);
+}
+
+// The item that holds group g (g below mult * the sum): its number, the
+// entries and groups of one of its units, and its first group.
+struct GroupItem {
+  int item, n;
+  uint32_t vg, base;
+};
+template <class LEN>
+__device__ __forceinline__ GroupItem find_item(int ni, LEN len, GroupScan first, uint32_t mult,
+                                               uint32_t g) {
+  const int lane = threadIdx.x & 63;
+  uint32_t base = 0u;
+  int i0 = 0;
+  while (i0 + 64 < ni && g >= base + mult * __builtin_amdgcn_readlane(first.s, 63)) {
+    base += mult * __builtin_amdgcn_readlane(first.s, 63);
+    i0 += 64;
+    first.n = i0 + lane < ni ? len(i0 + lane) : 0;
+    first.s = wave_incl_scan(groups_of(first.n));
+  }
+  const uint64_t past = __ballot(base + mult * first.s > g);
+  const int l = past ? __ffsll((unsigned long long)past) - 1 : 63;
+  GroupItem r;
+  r.item = i0 + l;
+  r.n = __builtin_amdgcn_readlane(first.n, l);
+  r.vg = groups_of(r.n);
+  r.base = base + mult * (__builtin_amdgcn_readlane(first.s, l) - r.vg);
+  return r;
+}
+
+// Groups per range: an equal share of the total, at least min_range (the host
+// sets it so that no unit meets more than kMaxPartials ranges when the
+// histograms go to slots, else 1).
+__device__ __forceinline__ uint32_t range_groups(uint32_t total, int nwg, int min_range) {
+  return max((total + (uint32_t)nwg - 1u) / (uint32_t)nwg, (uint32_t)min_range);
+}
+// A unit's vg <= gu groups meet at most floor((gu - 1) / R) + 2 ranges of R.
+__host__ __device__ __forceinline__ int min_range_groups(int64_t gu, int max_slots) {
+  return (int)((gu - 1) / (max_slots - 1)) + 1;
+}
+
+// The one-launch same-step kernel's scoring ranges are XCD-affine: its
+// scoring workgroups are spread over the 8 XCDs round-robin by index, and the
+// workgroups x, x + 8, x + 16, ... (XCD x) score the units x, x + 8, x + 16,
+// ... in ranges of those units' groups.  A unit's scores are then written on
+// the XCD where its selection and attention run (the same index map,
+// split_block), and the units of an XCD are complete as soon as that XCD's
+// ranges are.  Needs U and nwg multiples of 8.  The slot of (unit, workgroup)
+// is unique within XCD x's block of U/8 + nwg/8 slots, as in plain unit order.
+//
+// hist_slots: the first slot of `unit` and the number of consecutive slots
+// that hold its histogram (0 for a unit without positions).
+struct SlotRange {
+  int64_t first;
+  int count;
+};
+__device__ __forceinline__ SlotRange hist_slots(const SelectArgs& a, int unit) {
+  const int x = a.affine ? (unit & 7) : 0;
+  const int ni = a.affine ? (a.units >> 3) : a.units / a.Hkv;
+  const int nwg = a.affine ? (a.score_nwg >> 3) : a.score_nwg;
+  const uint32_t mult = a.affine ? 1u : (uint32_t)a.Hkv;
+  const int item = a.affine ? (unit >> 3) : unit / a.Hkv;
+  const uint32_t h = a.affine ? 0u : (uint32_t)(unit - item * a.Hkv);
+  auto len = [&](int i) {
+    return unit_len(a.ctx_lens[a.affine ? (8 * i + x) / a.Hkv : i], a.max_ctx, a.chunk);
+  };
+  GroupScan first;
+  const uint32_t R = range_groups(mult * sum_groups(ni, len, &first), nwg, a.min_range);
+  int n;
+  const uint32_t before = groups_before(item, len, first, &n);
+  const uint32_t mine = groups_of(n), g0 = mult * before + h * mine;
+  const uint32_t lo = g0 / R, hi = (g0 + mine - 1u) / R;
+  return SlotRange{a.affine ? (int64_t)x * (ni + nwg) + item + lo : (int64_t)unit + lo,
+                   mine ? (int)(hi - lo + 1u) : 0};
 }
 
 // Inclusive prefix sum over a workgroup of NW waves.  `tmp` is LDS scratch of

@@ -39,6 +39,7 @@ __global__ __launch_bounds__(HIST ? 64 * kHistScoreWaves : kScoreThreads) void k
   __shared__ __attribute__((aligned(16)))
   uint32_t lds_stage[kWaves * (kStageDwords + kFlushGroups * kStageRows)];
   score_range<G, HIST, kWaves>(a, blockIdx.x, gridDim.x, lds_hist, lds_stage);
+  if (!HIST && a.tails) fill_tails(a, blockIdx.x, gridDim.x);
 }
 
 
@@ -510,7 +511,8 @@ struct SelLds {
 template <int NT = kFinishThreads, int CAP = kCandLds, bool COH = false>
 __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const SelLds& L,
                                            bool write, int32_t* share, uint32_t lo,
-                                           uint32_t hi, bool clear) {
+                                           uint32_t hi, bool clear,
+                                           const SlotRange* known = nullptr) {
   static_assert(NT >= 128 && kHistBins % NT == 0 && kFusedSelectMaxCtx % (kSelPer * NT) == 0,
                 "workgroup shape");
   constexpr int kBatch = kSelPer * NT;
@@ -524,22 +526,14 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   // the histogram, and the first batch of scores (clamped to the row, not
   // to n_b, which is not known yet; positions at or past n_b are masked).
   // The histogram is the sum of the slots unit + wg of the workgroups that
-  // scored the unit's groups (every such workgroup stores one, zeros where
-  // its groups lie past n_b), or one slot already summed.
+  // scored the unit's groups (hist_slots; a unit without positions reads one
+  // it does not use), or one slot already summed.
   const uint32_t* slots = a.hist + (int64_t)unit * kHistBins;
   int nslots = 1;
   if (a.hist_part) {
-    const int64_t gu = (a.max_ctx + kStageRows - 1) / kStageRows;
-    if (a.affine) {
-      slots = a.hist_part + xcd_slot0(unit, a.units, a.score_nwg, gu, &nslots) * kHistBins;
-      nslots = min(nslots, kMaxPartials);  // the host keeps it below
-    } else {
-      const int64_t T = gu * a.units, g0 = (int64_t)unit * gu;
-      const int64_t lo_wg = range_owner(g0, T, a.score_nwg);
-      const int64_t hi_wg = range_owner(g0 + gu - 1, T, a.score_nwg);
-      slots = a.hist_part + (unit + lo_wg) * kHistBins;
-      nslots = (int)min<int64_t>(hi_wg - lo_wg + 1, kMaxPartials);  // the host keeps it below
-    }
+    const SlotRange r = known ? *known : hist_slots(a, unit);
+    slots = a.hist_part + r.first * kHistBins;
+    nslots = max(1, min(r.count, kMaxPartials));  // at most kMaxPartials by min_range
   }
   const int len_b = a.ctx_lens[unit / a.Hkv];
   uint2 hv[kMaxPartials][kHistBins / NT / 2];
@@ -679,7 +673,8 @@ __device__ __forceinline__ void select_attn_part(const SelectArgs& sa, const Att
                                                  int unit, int split, int nsplit,
                                                  uint32_t* lds, uint32_t* tmp,
                                                  uint32_t* misc,
-                                                 const FusedSync* fs = nullptr) {
+                                                 const FusedSync* fs = nullptr,
+                                                 const SlotRange* slots = nullptr) {
   static_assert(!MERGE2 || HEADS == 1, "the merge joins row shares");
   static_assert(G % HEADS == 0, "whole heads per workgroup");
   constexpr int GA = G / HEADS;  // heads each workgroup attends with
@@ -694,7 +689,7 @@ __device__ __forceinline__ void select_attn_part(const SelectArgs& sa, const Att
   if (HEADS == 1) share_range(hi, split, nsplit, &lo, &hi);
   // the workgroups of a unit all read its histogram: none clears it
   select_unit<kFinishThreads, kCandLds, COH>(sa, unit, L, split == 0, share, (uint32_t)lo,
-                                             (uint32_t)hi, false);
+                                             (uint32_t)hi, false, slots);
   __syncthreads();
   const int qh0 = (unit % sa.Hkv) * G + (HEADS > 1 ? split * GA : 0);
   if constexpr (MERGE2)
@@ -723,7 +718,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_attn(SelectArgs sa, A
 // Scoring, selection and attention of a same-step call in one launch, for
 // the head-halves form at U and grid multiples of 8.  The first nS
 // workgroups (one per CU, dispatched first) score with XCD-affine ranges
-// (xcd_slot0): the units of XCD x are complete as soon as its ranges are.
+// (hist_slots): the units of XCD x are complete as soon as its ranges are.
 // The XCDs stream at different rates, so the units of the faster ones select
 // and attend while the slower ones still score, and no unit waits for a
 // launch boundary.  The 2U workgroups after them are k_select_attn's head
@@ -752,11 +747,9 @@ __global__ __launch_bounds__(kFinishThreads) void k_critical(ScoreArgs sc, Selec
   int unit, half;
   split_block(blockIdx.x - nS, 2, &unit, &half);
   if (unit >= sa.units) return;  // uniform over the workgroup
-  int nslots;
-  const int64_t s0 = xcd_slot0(unit, sa.units, sa.score_nwg,
-                               (sa.max_ctx + kStageRows - 1) / kStageRows, &nslots);
-  if ((int)threadIdx.x < nslots) {
-    uint64_t* f = fs.flags + 2 * (s0 + threadIdx.x) + half;
+  const SlotRange slots = hist_slots(sa, unit);
+  if ((int)threadIdx.x < slots.count) {
+    uint64_t* f = fs.flags + 2 * (slots.first + threadIdx.x) + half;
     for (uint32_t spin = 0;
          __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != fs.tag &&
          spin < kFusedSpinLimit;
@@ -766,9 +759,9 @@ __global__ __launch_bounds__(kFinishThreads) void k_critical(ScoreArgs sc, Selec
   }
   __syncthreads();
   if constexpr (ROWS)
-    select_attn_part<G, 1, true, true>(sa, at, unit, half, 2, lds, tmp, misc, &fs);
+    select_attn_part<G, 1, true, true>(sa, at, unit, half, 2, lds, tmp, misc, &fs, &slots);
   else
-    select_attn_part<G, 2, true>(sa, at, unit, half, 1, lds, tmp, misc);
+    select_attn_part<G, 2, true>(sa, at, unit, half, 1, lds, tmp, misc, nullptr, &slots);
 }
 
 // Same-step over chunks (Sec. 2.2): sa is the chunk problem (one landmark

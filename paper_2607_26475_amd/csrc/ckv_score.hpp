@@ -52,15 +52,7 @@ __device__ __forceinline__ void store_hist(const uint32_t* lds_hist, uint32_t* s
         *reinterpret_cast<const uint4*>(lds_hist + kPer * t + i);
 }
 
-// An empty slot, for a workgroup whose groups of the unit all lie past n_b.
-template <int NT = kScoreThreads>
-__device__ __forceinline__ void store_zero_hist(uint32_t* slot) {
-  for (int i = 4 * (int)threadIdx.x; i < kHistBins; i += 4 * NT)
-    *reinterpret_cast<uint4*>(slot + i) = make_uint4(0u, 0u, 0u, 0u);
-}
-
-// The workgroup's LDS histogram (or zeros, lds_hist null) as its slot,
-// device-coherent, 8 bytes per lane with consecutive lanes on consecutive
+// The workgroup's LDS histogram as its slot, device-coherent, 8 bytes per lane with consecutive lanes on consecutive
 // words (NT threads).
 template <int NT>
 __device__ __forceinline__ void store_hist_coherent(const uint32_t* lds_hist, uint32_t* slot) {
@@ -69,22 +61,10 @@ __device__ __forceinline__ void store_hist_coherent(const uint32_t* lds_hist, ui
 #pragma unroll
   for (int q = 0; q < kPairs; ++q) {
     const int i = 2 * (t + NT * q);
-    const uint64_t w = lds_hist ? ((uint64_t)lds_hist[i] | ((uint64_t)lds_hist[i + 1] << 32))
-                                : 0ull;
+    const uint64_t w = (uint64_t)lds_hist[i] | ((uint64_t)lds_hist[i + 1] << 32);
     __hip_atomic_store(reinterpret_cast<uint64_t*>(slot + i), w, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   }
-}
-
-// After a fused scoring workgroup's stores of the consecutive slots [slot0,
-// slot0 + count): every thread waits for its own stores, the barrier then
-// covers the workgroup's, and each slot's two flags take the launch's tag.
-__device__ __forceinline__ void hand_over(const FusedSync& fs, int64_t slot0, int count) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  for (int t = threadIdx.x; t < 2 * count; t += blockDim.x)
-    __hip_atomic_store(fs.flags + 2 * slot0 + t, fs.tag, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Scores of one staged group (kStageRows keys of one unit starting at row
@@ -140,15 +120,35 @@ __device__ __forceinline__ void load_query(const ScoreArgs& a, int unit, bf16x8*
   }
 }
 
-// Scores a balanced share of the whole batch: the positions of every unit are
-// cut into groups of kStageRows keys, the groups of all units are numbered
-// unit-major, and workgroup `wg` of `nwg` takes the contiguous range
-// [wg*T/nwg, (wg+1)*T/nwg) of the T groups.  A range spans few units; for each
+// Scores of positions [32 * first, max_ctx) rows past the units' last valid
+// groups: -inf, in equal shares of the stored groups (all threads of the
+// workgroup; only score_keys, whose output has those rows, needs them).
+__device__ __forceinline__ void fill_tails(const ScoreArgs& a, int wg, int nwg) {
+  const int64_t gu = (a.max_ctx + kStageRows - 1) / kStageRows;
+  const int64_t total = (int64_t)a.units * gu;
+  const int64_t t0 = total * wg / nwg, t1 = total * (wg + 1) / nwg;
+  for (int64_t t = t0; t < t1;) {
+    const int unit = (int)(t / gu);
+    const int64_t ubase = (int64_t)unit * gu, end = min(t1, ubase + gu);
+    const int64_t vg = groups_of(unit_len(a.ctx_lens[unit / a.Hkv], a.max_ctx, a.chunk));
+    float* srow = a.scores + (int64_t)unit * a.max_ctx;
+    const int64_t j1 = min((end - ubase) * kStageRows, (int64_t)a.max_ctx);
+    for (int64_t j = max(t - ubase, vg) * kStageRows + threadIdx.x; j < j1; j += blockDim.x)
+      srow[j] = -INFINITY;
+    t = end;
+  }
+}
+
+// Scores a balanced share of the whole batch: the positions below n_b of
+// every unit are cut into groups of kStageRows keys, the groups of all units
+// are numbered unit-major, and workgroup `wg` of `nwg` takes a contiguous range
+// of R groups (range_groups).  A range spans few units; for each
 // unit it touches the workgroup loads that unit's G query rows once and, if
 // HIST, counts the first radix digit of its scores in LDS and, when it leaves
 // the unit, adds the counts to the unit's histogram or stores them as its own
-// slot (hist_part; an all-zero slot when its groups of the unit all lie at or
-// past n_b).  Groups at or beyond n_b only write -inf.  Must be called by all
+// slot (hist_part).  Rows of a unit's last group at or past n_b get -inf; later
+// groups are not written (the selections read only below n_b; fill_tails
+// writes them for score_keys).  Must be called by all
 // 64 * NW threads of the workgroup; lds_stage holds NW * (kStageDwords +
 // kFlushGroups * kStageRows) dwords.
 //
@@ -179,7 +179,7 @@ __device__ __forceinline__ void load_query(const ScoreArgs& a, int unit, bf16x8*
 // 158-165 us), as it is with 16-row groups.
 //
 // FUSED (the scoring role of the one-launch same-step kernel, HIST with
-// per-workgroup slots): the ranges are XCD-affine (xcd_slot0); the workgroup
+// per-workgroup slots): the ranges are XCD-affine (hist_slots); the workgroup
 // may have more than NW waves, the others only join its barriers; scores and
 // slots are stored device-coherent, 8 bytes per lane over whole lines, and
 // each finished (unit, slot) is handed over through fs (FusedSync).
@@ -194,32 +194,42 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
   const int lrow = lane >> 4, lchunk = lane & 15;
   const bool active = !FUSED || wave < NW;  // uniform over the wave
   constexpr int kLoads = kStageRows / 4;  // 4 rows per load instruction
-  const int64_t gpu_groups = (a.max_ctx + kStageRows - 1) / kStageRows;  // per unit
   // FUSED: XCD x = wg % 8 scores units x, x + 8, ... with its nwg / 8 workgroups
   const int xcd = FUSED ? (wg & 7) : 0;
   const int wr = FUSED ? (wg >> 3) : wg, nwr = FUSED ? (nwg >> 3) : nwg;
-  const int64_t units_r = FUSED ? (a.units >> 3) : a.units;
-  const int64_t total = units_r * gpu_groups;
-  const int64_t g0 = total * wr / nwr, g1 = total * (wr + 1) / nwr;
+  const int items = FUSED ? (a.units >> 3) : a.units / a.Hkv;
+  const uint32_t mult = FUSED ? 1u : (uint32_t)a.Hkv;
+  auto len = [&](int i) {
+    return unit_len(a.ctx_lens[FUSED ? (8 * i + xcd) / a.Hkv : i], a.max_ctx, a.chunk);
+  };
+  GroupScan first_items;
+  const uint32_t total = mult * sum_groups(items, len, &first_items);
+  const uint32_t R = range_groups(total, nwr, a.min_range);
+  const uint32_t g0 = (uint32_t)min((uint64_t)wr * R, (uint64_t)total);
+  const uint32_t g1 = (uint32_t)min((uint64_t)g0 + R, (uint64_t)total);
+  if (g0 >= g1) return;  // uniform over the workgroup
+  GroupItem it = find_item(items, len, first_items, mult, g0);
   uint32_t* stage = lds_stage + (active ? wave : 0) * kStageDwords;
   float* sbuf = reinterpret_cast<float*>(lds_stage + NW * kStageDwords) +
                 (active ? wave : 0) * kFlushGroups * kStageRows;
+  const int item0 = it.item;
 
-  for (int64_t seg = g0; seg < g1;) {
-    const int vunit = (int)(seg / gpu_groups);
-    const int unit = FUSED ? 8 * vunit + xcd : vunit;
-    const int64_t slot = FUSED ? xcd * (units_r + nwr) + vunit + wr : (int64_t)unit + wg;
-    const int64_t ubase = (int64_t)vunit * gpu_groups;
-    const int64_t seg_end = min(g1, ubase + gpu_groups);
-    const int n = unit_len(a.ctx_lens[unit / a.Hkv], a.max_ctx, a.chunk);
-    float* srow = a.scores + (int64_t)unit * a.max_ctx;
-    // groups [ubase + first_empty, ...) hold no position below n_b
-    const int64_t valid_end = min(seg_end, ubase + (n + kStageRows - 1) / kStageRows);
-    for (int64_t gg = max(seg, valid_end); gg < seg_end; ++gg) {
-      const int j = (int)(gg - ubase) * kStageRows + (tid & (kStageRows - 1));
-      if (tid < kStageRows && j < a.max_ctx) srow[j] = -INFINITY;
+  for (uint32_t seg = g0; seg < g1;) {
+    while (seg >= it.base + mult * it.vg) {  // the next item that has groups
+      it.base += mult * it.vg;
+      ++it.item;
+      it.n = len(it.item);
+      it.vg = groups_of(it.n);
     }
-    if (seg < valid_end) {  // uniform over the workgroup
+    const uint32_t h = FUSED ? 0u : (seg - it.base) / it.vg;
+    const int unit = FUSED ? 8 * it.item + xcd : it.item * a.Hkv + (int)h;
+    const int64_t slot =
+        FUSED ? (int64_t)xcd * (items + nwr) + it.item + wr : (int64_t)unit + wg;
+    const uint32_t ubase = it.base + h * it.vg;
+    const uint32_t seg_end = min(g1, ubase + it.vg);
+    const int n = it.n;
+    float* srow = a.scores + (int64_t)unit * a.max_ctx;
+    {
       if (HIST) {
         if (!FUSED || tid < NT)
           for (int i = tid; i < kHistBins; i += NT) lds_hist[i] = 0u;
@@ -232,7 +242,7 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
       // replaced by -inf): lane-conditional loads would make the compiler
       // wait for every outstanding load at each use.
       // loads [i0, i1) of a group's kLoads
-      auto load_part = [&](int64_t gg, uint4* v, int i0, int i1) {
+      auto load_part = [&](uint32_t gg, uint4* v, int i0, int i1) {
         const int jb = (int)(gg - ubase) * kStageRows;
 #pragma unroll
         for (int i = i0; i < i1; ++i) {
@@ -240,10 +250,10 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
           v[i] = ld16_nt(kunit + (int64_t)j * a.key_stride + 8 * lchunk);
         }
       };
-      auto load_group = [&](int64_t gg, uint4* v) { load_part(gg, v, 0, kLoads); };
+      auto load_group = [&](uint32_t gg, uint4* v) { load_part(gg, v, 0, kLoads); };
       // writes the scores of the nb buffered groups [first, first + nb): one
       // contiguous run, 16 bytes per lane when rows are 16-byte aligned
-      auto flush = [&](int64_t first, int nb) {
+      auto flush = [&](uint32_t first, int nb) {
         __builtin_amdgcn_wave_barrier();
         const int jb = (int)(first - ubase) * kStageRows;
         const int count = nb * kStageRows;
@@ -286,12 +296,12 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
         }
         __builtin_amdgcn_wave_barrier();
       };
-      // this wave's groups of the segment below n_b: every NW-th one (none
-      // for the waves past NW of the fused role)
-      const int64_t w1 = valid_end, w0 = active ? seg + wave : w1;
+      // this wave's groups of the segment: every NW-th one (none for the waves
+      // past NW of the fused role)
+      const uint32_t w1 = seg_end, w0 = active ? seg + wave : w1;
       uint4 cur[kLoads], nxt[kLoads];
-      int64_t gg = w0;
-      int64_t first = gg;
+      uint32_t gg = w0;
+      uint32_t first = gg;
       int nb = 0;
       if (gg < w1) load_group(gg, cur);
 #pragma unroll 1
@@ -331,21 +341,23 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
         }
         __syncthreads();
       }
-    } else if (HIST && a.hist_part) {  // the unit's histogram sums this slot too
-      if constexpr (FUSED) {
-        if (tid < NT) store_hist_coherent<NT>(nullptr, a.hist_part + slot * kHistBins);
-      } else {
-        store_zero_hist<NT>(a.hist_part + slot * kHistBins);
-      }
     }
     seg = seg_end;
   }
   if constexpr (FUSED) {
     // every slot of the range handed over at its end, after one wait for all
-    // its stores (a wait between units would stall the key stream)
-    if (g0 < g1) {
-      const int v0 = (int)(g0 / gpu_groups), v1 = (int)((g1 - 1) / gpu_groups);
-      hand_over(fs, xcd * (units_r + nwr) + v0 + wr, v1 - v0 + 1);
+    // its stores (a wait between units would stall the key stream): each
+    // thread waits for its own, the barrier then covers the workgroup's, and
+    // each slot's two flags take the launch's tag.  Units without positions
+    // have no slot, and nobody would clear its flags.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const int64_t slot0 = (int64_t)xcd * (items + nwr) + wr;
+    for (int t = tid; t < 2 * (it.item - item0 + 1); t += blockDim.x) {
+      const int i = item0 + (t >> 1);
+      if (len(i))
+        __hip_atomic_store(fs.flags + 2 * (slot0 + i) + (t & 1), fs.tag, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
