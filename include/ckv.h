@@ -237,9 +237,9 @@ int ckv_critical_kv_attn_noalloc(const ckv_shape* shape, const uint16_t* q_att,
  *      every row of idx_true.  hits[b][h] = |idx_true ∩ idx_pred|;
  *   3. computes out = attention of q_att over exactly the rows of idx_true,
  *      the same-step result of ckv_critical_kv_attn with q_sel = q_att;
- *   4. in the same launch as that attention, selects idx_next/n_next from
- *      q_sel (the speculative query; NULL means q_att): the prediction for
- *      the next step.
+ *   4. selects idx_next/n_next from q_sel (the speculative query; NULL means
+ *      q_att), scored in the same pass over the keys as 1.: the prediction
+ *      for the next step.
  * idx_pred must be ascending in [0, max_ctx) and -1 padded, as
  * ckv_select_topk writes it; n_pred is clamped to [0, k].  k_buf/v_buf are
  * modified: slots of mispredicted rows are overwritten.  All streams run at

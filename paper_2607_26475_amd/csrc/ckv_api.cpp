@@ -182,7 +182,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // start of every selecting call.
 struct Layout {
   size_t hist = 0, coarse = 0, ctrl = 0, hist2 = 0, coarse2 = 0, ctrl2 = 0, zero_end = 0;
-  size_t sel = 0, cand = 0, bitmap = 0, scores = 0, part = 0, hist_part = 0, hist_part_bytes = 0;
+  size_t sel = 0, cand = 0, scores2 = 0, bitmap = 0, scores = 0, part = 0, hist_part = 0, hist_part_bytes = 0;
   size_t slot_of = 0, miss_pos = 0, miss_slot = 0, n_miss = 0, free_slot = 0, total = 0;
   size_t chunk_idx = 0, n_chunks = 0;  // decode step: selected chunks of a chunked layer
   size_t scores_b = 0, hist_part_b = 0;  // decode step: the second scores and slots region
@@ -226,7 +226,9 @@ Layout make_layout(const Dims& d, int32_t k, int entry) {
     L.zero_end = off;
     L.sel = off;
     off = align256(off + U * (size_t)k * 4);
+    // the filter's candidate positions, then the corrected entries' second scores
     L.cand = off;
+    L.scores2 = off + U * (size_t)d.max_ctx * 4;
     off = align256(off + U * (size_t)d.max_ctx * 8);
     if (d.max_ctx > kBitmapLdsBits) {
       L.bm_words = (d.max_ctx + 31) / 32;
@@ -357,10 +359,11 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
   a.coarse = at<uint32_t>(ws, L.coarse);
   a.ctrl = at<uint32_t>(ws, L.ctrl);
   a.sel = at<int32_t>(ws, L.sel);
-  a.cand = at<uint2>(ws, L.cand);
+  a.cand = at<uint32_t>(ws, L.cand);
   a.bitmap = L.bm_words ? at<uint32_t>(ws, L.bitmap) : nullptr;
   a.idx = idx;
   a.n_sel = n_sel;
+  a.idx2 = a.n_sel2 = nullptr;
   a.bm_words = L.bm_words;
   a.Hkv = d.Hkv;
   a.max_ctx = d.max_ctx;
@@ -407,6 +410,9 @@ ScoreArgs score_args(const Dims& d, const Layout& L, const uint16_t* q,
   a.hist_part = nullptr;
   a.min_range = 1;
   a.tails = 0;
+  a.q2 = nullptr;
+  a.scores2 = nullptr;
+  a.hist2 = a.coarse2 = a.hist_part2 = nullptr;
   return a;
 }
 
@@ -1310,30 +1316,48 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   CKV_DEBUG_CHECK(stream, ctx_lens, idx_pred, n_pred, k);
   hipStream_t s = (hipStream_t)stream;
   float* scores = at<float>(ws, L.scores);
-  // 1. the current token's own selection
+  // 1. the current token's own selection and the next step's, both from one
+  //    pass over the keys (one selection, written twice, when there is one query)
+  // A caller may let the next step's sets take the place of the prediction:
+  // then they are written after 2. has read it.
+  const int64_t entries = (int64_t)d.U * k;
+  const bool in_place = (idx_next < idx_pred + entries && idx_pred < idx_next + entries) ||
+                        (n_next < n_pred + d.U && n_pred < n_next + d.U);
+  const bool one = q_sel == q_att && !in_place;
   SelectArgs s1 = select_args(d, L, ws, scores, ctx_lens, k, idx_true, n_true);
-  ScoreArgs c1 = score_args(d, L, q_att, k_score, ctx_lens, scale, scores, &s1);
-  // the next step's selection (4. below) is scored by the dual kernel
-  SelectArgs s2 = select_args(d, L, ws, scores, ctx_lens, k, idx_next, n_next);
+  SelectArgs s2 = select_args(d, L, ws, at<float>(ws, L.scores2), ctx_lens, k, idx_next, n_next);
   s2.hist = at<uint32_t>(ws, L.hist2);
   s2.coarse = at<uint32_t>(ws, L.coarse2);
   s2.ctrl = at<uint32_t>(ws, L.ctrl2);
-  ScoreArgs c2 = score_args(d, L, q_sel, k_score, ctx_lens, scale, scores, &s2);
-  // static ranges: beside this call's own gather of the misses, claims made
-  // the long-context loop slower (137.2 against 136.7 ms per step)
-  c2.claim = nullptr;
-  const int nwg1 = score_blocks(c1, d.G, ScoreKind::kHist);
-  const int nwg2 = score_blocks(c2, d.G, ScoreKind::kDualIndexed);
-  if (use_partials(d, L, nwg1) && use_partials(d, L, nwg2)) {
-    // both selections use the slots in turn: the first reads them before the
-    // dual launch writes them again
-    set_partials(ws, L, nwg1, &c1, &s1);
-    set_partials(ws, L, nwg2, &c2, &s2);
+  ScoreArgs sc = score_args(d, L, q_att, k_score, ctx_lens, scale, scores, &s1);
+  if (one) {
+    s1.idx2 = idx_next;
+    s1.n_sel2 = n_next;
+  } else {
+    sc.q2 = q_sel;
+    sc.scores2 = at<float>(ws, L.scores2);
+    sc.hist2 = s2.hist;
+    sc.coarse2 = s2.coarse;
+  }
+  const int nwg = score_blocks(sc, d.G, one ? ScoreKind::kHist : ScoreKind::kTwo);
+  const size_t slots_bytes = (size_t)(d.U + nwg) * kHistBins * 4;
+  if (use_partials(d, L, nwg) && (one || 2 * slots_bytes <= L.hist_part_bytes)) {
+    set_partials(ws, L, nwg, &sc, &s1);
+    if (!one) {  // the second query's slots after the first's
+      sc.hist_part2 = at<uint32_t>(ws, L.hist_part + slots_bytes);
+      s2.hist_part = sc.hist_part2;
+      s2.score_nwg = nwg;
+      s2.min_range = s1.min_range;
+    }
   } else if (!hist_clean) {
     CKV_TRY_HIP(launch_zero(ws, L.zero_end, s), "zero launch");
   }
-  CKV_TRY_HIP(launch_score(c1, d.G, true, nwg1, s), "score launch");
-  if ((rc = run_select_tail(s1, d.U, s))) return rc;
+  CKV_TRY_HIP(launch_score(sc, d.G, true, nwg, s), "score launch");
+  const bool pair = !one && !in_place && d.max_ctx <= kFusedSelectMaxCtx;
+  if (pair)
+    CKV_TRY_HIP(launch_select_pair(s1, s2, s), "select launch");
+  else if ((rc = run_select_tail(s1, d.U, s)))
+    return rc;
   // 2. hits and misses against the predicted set; misses into free slots
   MissArgs m;
   m.idx_true = idx_true;
@@ -1348,6 +1372,7 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   m.free_slot = L.free_slot ? at<int32_t>(ws, L.free_slot) : nullptr;
   m.k = k;
   CKV_TRY_HIP(launch_miss(m, d.U, s), "miss launch");
+  if (!one && !pair && (rc = run_select_tail(s2, d.U, s))) return rc;
   GatherArgs g;
   g.k_src = k_src;
   g.v_src = v_src;
@@ -1368,14 +1393,13 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
     CKV_TRY_HIP(launch_gather(g, gather_blocks(src_kind), s), "miss gather launch");
   }
   // 3. attention over exactly the selected rows, now all in the buffer (read
-  //    through the slot list), in one launch with 4. the next step's scoring
+  //    through the slot list)
   // the buffer as an indexed source: unit u's slot r is row r of [U][k][d]
   Dims db = d;
   db.max_ctx = k;
   AttnArgs at_ = attn_args(db, L, ws, q_att, k_buf, v_buf, m.slot_of, n_true, kD, k, scale,
                            out);
-  CKV_TRY_HIP(launch_dual(at_, c2, d.G, true, d.U, nwg2, s), "dual launch");
-  return select_and_merge(s2, at_, d, s);
+  return run_attention(at_, d, true, s);
 }
 
 extern "C" {

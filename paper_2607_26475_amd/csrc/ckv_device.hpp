@@ -89,6 +89,14 @@ struct ScoreArgs {
   int chunk;                // rows per scored entry: n_b rows give ceil(n_b/chunk) entries
   int min_range;            // fewest groups of a workgroup's range (range_groups)
   int tails;                // write -inf to every score at or past n_b (score_keys)
+  // A second query over the same keys in the same pass (the corrected
+  // entries: the current and the speculative token), with its own scores and
+  // histograms; q2 NULL: none.
+  const uint16_t* q2;
+  float* scores2;
+  uint32_t* hist2;
+  uint32_t* coarse2;
+  uint32_t* hist_part2;
 };
 
 struct SelectArgs {
@@ -103,10 +111,13 @@ struct SelectArgs {
   int units;
   int32_t* sel;             // [U][k]   positions above the digit-1 bin, then
                             //          the chosen candidates
-  uint2* cand;              // [U][max_ctx] (order key, position)
+  uint32_t* cand;           // [U][max_ctx] positions inside the digit-1 bin (the
+                            //   filter's; a one-workgroup selection has no list)
   uint32_t* bitmap;         // [U][bm_words] when max_ctx > kBitmapLdsBits
   int32_t* idx;             // [U][k]
   int32_t* n_sel;           // [U]
+  int32_t* idx2;            // non-null: a second copy of idx and n_sel
+  int32_t* n_sel2;
   int64_t bm_words;
   int Hkv, max_ctx, k, tiles;
   int chunk;                // as in ScoreArgs

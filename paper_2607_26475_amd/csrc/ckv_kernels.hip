@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 namespace ckv {
 
@@ -42,6 +43,18 @@ __global__ __launch_bounds__(HIST ? 64 * kHistScoreWaves : kScoreThreads) void k
   if (!HIST && a.tails) fill_tails(a, blockIdx.x, gridDim.x);
 }
 
+// The pass for two queries over the same keys (the corrected entries).  Each
+// key is read once for both: 64 units of 30 to 64 Ki positions were scored for
+// the current token (131 us) and again in the attention's launch for the
+// speculative one (144 us).  LDS (bytes): two histograms and the stages.
+template <int G>
+__global__ __launch_bounds__(64 * kHistScoreWaves) void k_score_two(ScoreArgs a) {
+  __shared__ uint32_t lds_hist[2 * kHistBins];
+  __shared__ __attribute__((aligned(16)))
+  uint32_t lds_stage[kHistScoreWaves * (kStageDwords + kFlushGroups * kStageRows)];
+  score_range<G, true, kHistScoreWaves, false, false, true>(a, blockIdx.x, gridDim.x, lds_hist,
+                                                            lds_stage);
+}
 
 // The same pass over chunk landmarks (a kernel of its own only so that
 // traces and profiles keep the two workloads apart).
@@ -74,7 +87,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_hist(SelectArgs a) {
 }
 
 // Selects positions above the first-digit bin of the m-th largest key and
-// collects the positions inside that bin as candidates.
+// collects the positions inside that bin as candidates (their scores are read
+// again by the finish).
 __global__ __launch_bounds__(kFilterThreads) void k_filter(SelectArgs a) {
   constexpr int kPer = kFilterTile / kFilterThreads;  // 16 positions per thread
   __shared__ uint32_t sh[4];
@@ -97,16 +111,12 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter(SelectArgs a) {
                    a.hist + (int64_t)unit * kHistBins, (uint32_t)m, sh);
   __syncthreads();
   const uint32_t b1 = sh[0];
-  uint32_t keys[kPer];
   uint32_t selmask = 0u, candmask = 0u;
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     const int j = j0 + r * kFilterThreads + threadIdx.x;
-    keys[r] = 0u;
     if (j < n) {
-      const uint32_t key = order_key(sv[r]);
-      const uint32_t d1 = key >> (32 - kHistBits);
-      keys[r] = key;
+      const uint32_t d1 = order_key(sv[r]) >> (32 - kHistBits);
       if (d1 > b1) selmask |= 1u << r;
       else if (d1 == b1) candmask |= 1u << r;
     }
@@ -123,12 +133,12 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter(SelectArgs a) {
   __syncthreads();
   uint32_t os = sh[2] + (excl & 0xffffu), oc = sh[3] + (excl >> 16);
   int32_t* sel = a.sel + (int64_t)unit * a.k;
-  uint2* cand = a.cand + (int64_t)unit * a.max_ctx;
+  uint32_t* cand = a.cand + (int64_t)unit * a.max_ctx;
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     const int j = j0 + r * kFilterThreads + threadIdx.x;
     if ((selmask >> r) & 1u) sel[os++] = j;
-    else if ((candmask >> r) & 1u) cand[oc++] = make_uint2(keys[r], (uint32_t)j);
+    else if ((candmask >> r) & 1u) cand[oc++] = (uint32_t)j;
   }
 }
 
@@ -146,6 +156,16 @@ __device__ __forceinline__ void clear_unit_hist(const SelectArgs& a, int unit) {
   *reinterpret_cast<uint2*>(a.hist + (int64_t)unit * kHistBins + 2 * t) = make_uint2(0u, 0u);
   if (t < kCoarseBins) a.coarse[(int64_t)unit * kCoarseBins + t] = 0u;
   if (t < kCtrlWords) a.ctrl[(int64_t)unit * kCtrlWords + t] = 0u;
+}
+
+// The unit's finished selection of m positions again into idx2 / n_sel2, when
+// they are set (all kFinishThreads threads).
+__device__ __forceinline__ void copy_selection(const SelectArgs& a, int unit, int m) {
+  if (!a.idx2) return;
+  __syncthreads();  // idx is written, and visible to the workgroup
+  const int64_t row = (int64_t)unit * a.k;
+  for (int i = threadIdx.x; i < a.k; i += kFinishThreads) a.idx2[row + i] = a.idx[row + i];
+  if (threadIdx.x == 0) a.n_sel2[unit] = m;
 }
 
 // Writes set bits of bm[0, words) as ascending positions to out[0, limit)
@@ -195,8 +215,9 @@ __device__ __forceinline__ uint32_t emit_bitmap(const uint32_t* bm, int words, i
   return total;
 }
 
-// Radix select among candidates (order key, position) that share the first
-// digit b1: the need largest by (key descending, position ascending).
+// Radix select among the candidates, those of cs's nc entries for which
+// cs.get gives (order key, position); all share the first digit b1: the need
+// largest by (key descending, position ascending).
 // Returns the threshold key T; candidates with key > T are all chosen, and of
 // those equal to T the ones with position <= *pmax.  All NT threads call
 // this; hist needs 2048 words.
@@ -210,8 +231,10 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
   static_assert(kHistBits == 11, "digits 11 + 11 + 10");
   for (int i = tid; i < 2048; i += NT) hist[i] = 0u;
   __syncthreads();
-  for (uint32_t i = tid; i < nc; i += NT)
-    atomicAdd(&hist[(cs[i].x >> 10) & 2047u], 1u);
+  for (uint32_t i = tid; i < nc; i += NT) {
+    uint2 c;
+    if (cs.get(i, &c)) atomicAdd(&hist[(c.x >> 10) & 2047u], 1u);
+  }
   __syncthreads();
   uint32_t need2;
   const uint32_t b2 = find_bin_block<true, NT>(hist, 2048, need, tmp, misc, &need2);
@@ -219,8 +242,8 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
   for (int i = tid; i < 1024; i += NT) hist[i] = 0u;
   __syncthreads();
   for (uint32_t i = tid; i < nc; i += NT) {
-    const uint32_t key = cs[i].x;
-    if (((key >> 10) & 2047u) == b2) atomicAdd(&hist[key & 1023u], 1u);
+    uint2 c;
+    if (cs.get(i, &c) && ((c.x >> 10) & 2047u) == b2) atomicAdd(&hist[c.x & 1023u], 1u);
   }
   __syncthreads();
   uint32_t need3;
@@ -239,8 +262,8 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
       __syncthreads();
       const uint32_t hi_mask = shift == 24 ? 0u : (0xffffffffu << (shift + 8));
       for (uint32_t i = tid; i < nc; i += NT) {
-        const uint2 c = cs[i];
-        if (c.x == T && (c.y & hi_mask) == prefix) atomicAdd(&hist[(c.y >> shift) & 255u], 1u);
+        uint2 c;
+        if (cs.get(i, &c) && c.x == T && (c.y & hi_mask) == prefix) atomicAdd(&hist[(c.y >> shift) & 255u], 1u);
       }
       __syncthreads();
       uint32_t rest;
@@ -252,6 +275,23 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
   }
   return T;
 }
+
+// The finish's candidates: (order key, position) in LDS, or, past its
+// capacity, the filter's list of positions and their scores.
+struct ListCands {
+  const uint2* lds;  // null: the list
+  const uint32_t* pos;
+  const float* srow;
+  __device__ __forceinline__ bool get(uint32_t i, uint2* c) const {
+    if (lds) {
+      *c = lds[i];
+    } else {
+      const uint32_t p = pos[i];
+      *c = make_uint2(order_key(srow[p]), p);
+    }
+    return true;
+  }
+};
 
 __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
   __shared__ uint2 area[kCandLds];  // candidates, later the position bitmap
@@ -267,18 +307,23 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
   if (m >= n) {  // uniform; every position (possibly none) is selected
     for (int i = tid; i < a.k; i += kFinishThreads) idx[i] = i < n ? i : -1;
     if (tid == 0) a.n_sel[unit] = m;
+    copy_selection(a, unit, m);
     clear_unit_hist(a, unit);
     return;
   }
   const uint32_t* ctrl = a.ctrl + (int64_t)unit * kCtrlWords;
   const uint32_t above = ctrl[0], nc = ctrl[1], b1 = ctrl[2];
   const uint32_t need = (uint32_t)m - above;  // >= 1 and <= nc
-  const uint2* cg = a.cand + (int64_t)unit * a.max_ctx;
+  const uint32_t* cg = a.cand + (int64_t)unit * a.max_ctx;
+  const float* srow = a.scores + (int64_t)unit * a.max_ctx;
   const bool in_lds = nc <= (uint32_t)kCandLds;
   if (in_lds) {
-    for (uint32_t i = tid; i < nc; i += kFinishThreads) area[i] = cg[i];
+    for (uint32_t i = tid; i < nc; i += kFinishThreads) {
+      const uint32_t p = cg[i];
+      area[i] = make_uint2(order_key(srow[p]), p);
+    }
   }
-  const uint2* cs = in_lds ? area : cg;
+  const ListCands cs{in_lds ? area : nullptr, cg, srow};
   uint32_t pmax;
   const uint32_t T = refine_threshold(cs, nc, need, b1, hist, tmp, misc, &pmax);
 
@@ -291,7 +336,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
     bool take = false;
     uint2 c = make_uint2(0u, 0u);
     if (i < nc) {
-      c = cs[i];
+      cs.get(i, &c);
       take = c.x > T || (c.x == T && c.y <= pmax);
     }
     const uint32_t slot = wave_append(take, &misc[4]);
@@ -313,6 +358,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
   emit_bitmap(bm, words, idx, (uint32_t)a.k, tmp);
   for (int i = m + tid; i < a.k; i += kFinishThreads) idx[i] = -1;
   if (tid == 0) a.n_sel[unit] = m;
+  copy_selection(a, unit, m);
   clear_unit_hist(a, unit);
 }
 
@@ -350,18 +396,35 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Candidate slots of the fused selection: the first CAP in LDS, any beyond
-// (heavy ties) in the unit's global candidate area.
+// Candidates of the one-workgroup selection: (fp32 bits, position) in LDS.
+// When there are more than CAP of them (heavy ties) the list is not used:
+// every position is looked at again (RescanCands), which needs no memory and
+// costs a pass over the unit's scores (256 KiB at most) per digit.
 template <int CAP = kCandLds>
-struct SplitCands {
+struct LdsCands {
   uint2* lds;
-  uint2* glob;
-  __device__ __forceinline__ uint2 operator[](uint32_t i) const {
-    return i < (uint32_t)CAP ? lds[i] : glob[i];
-  }
   __device__ __forceinline__ void put(uint32_t i, uint2 v) const {
     if (i < (uint32_t)CAP) lds[i] = v;
-    else glob[i] = v;
+  }
+  __device__ __forceinline__ bool get(uint32_t i, uint2* c) const {
+    const uint2 v = lds[i];
+    *c = make_uint2(order_key(__uint_as_float(v.x)), v.y);
+    return true;
+  }
+};
+
+template <bool COH>
+struct RescanCands {
+  const float* srow;
+  uint32_t b1;
+  __device__ __forceinline__ bool get(uint32_t i, uint2* c) const {
+    float x;
+    if constexpr (COH)
+      x = __hip_atomic_load(srow + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      x = srow[i];
+    *c = make_uint2(order_key(x), i);
+    return c->x >> (32 - kHistBits) == b1 && x == x;
   }
 };
 
@@ -372,7 +435,7 @@ struct SplitCands {
 // per wave).  Positions at or past n_b must hold NaN (then neither holds).
 template <int NT = kFinishThreads, int CAP = kCandLds>
 __device__ __forceinline__ void classify_batch(const float (&sv)[kSelPer], int j0, float g_lo,
-                                               float g_hi, uint32_t* bm, const SplitCands<CAP>& cs,
+                                               float g_hi, uint32_t* bm, const LdsCands<CAP>& cs,
                                                uint32_t* ctr) {
   static_assert(2 * kSelPer == 64, "one bitmap word per lane and batch");
   const int tid = threadIdx.x, lane = tid & 63;
@@ -417,17 +480,6 @@ __device__ __forceinline__ void classify_batch(const float (&sv)[kSelPer], int j
     }
   }
 }
-
-// The candidates as (order key, position): the fused selection stores the
-// scores' fp32 bits and converts on every read.
-template <int CAP = kCandLds>
-struct KeyedCands {
-  SplitCands<CAP> c;
-  __device__ __forceinline__ uint2 operator[](uint32_t i) const {
-    const uint2 v = c[i];
-    return make_uint2(order_key(__uint_as_float(v.x)), v.y);
-  }
-};
 
 // Pipelined calls: merges the attention partials of the launch before the
 // selection for one unit into the output, as the merge kernel does and in
@@ -566,7 +618,7 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   lds_barrier();
   if (tid < 64) find_first_bin_lds(lhist, (uint32_t)m, misc + 4);
   lds_barrier();
-  const SplitCands<CAP> cs{cand, a.cand + (int64_t)unit * a.max_ctx};
+  const LdsCands<CAP> cs{cand};
   const uint32_t b1 = misc[4], above = misc[5];
   const float g_lo = __uint_as_float(key_floor_bits((uint64_t)b1 << (32 - kHistBits)));
   const float g_hi = __uint_as_float(key_floor_bits((uint64_t)(b1 + 1u) << (32 - kHistBits)));
@@ -590,13 +642,20 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   __syncthreads();
   const uint32_t nc = misc[7];
   const uint32_t need = (uint32_t)m - above;
-  const KeyedCands<CAP> kc{cs};
-  uint32_t pmax;
-  const uint32_t T = refine_threshold<KeyedCands<CAP>, NT>(kc, nc, need, b1, lhist, tmp, misc, &pmax);
-  for (uint32_t i = tid; i < nc; i += NT) {
-    const uint2 c = kc[i];
-    if (c.x > T || (c.x == T && c.y <= pmax)) atomicOr(&bm[c.y >> 5], 1u << (c.y & 31));
-  }
+  auto resolve = [&](const auto& cands, uint32_t count) {
+    uint32_t pmax;
+    const uint32_t T = refine_threshold<std::remove_cv_t<std::remove_reference_t<decltype(cands)>>, NT>(
+        cands, count, need, b1, lhist, tmp, misc, &pmax);
+    for (uint32_t i = tid; i < count; i += NT) {
+      uint2 c;
+      if (cands.get(i, &c) && (c.x > T || (c.x == T && c.y <= pmax)))
+        atomicOr(&bm[c.y >> 5], 1u << (c.y & 31));
+    }
+  };
+  if (nc <= (uint32_t)CAP)
+    resolve(cs, nc);
+  else
+    resolve(RescanCands<COH>{srow, b1}, (uint32_t)n);
   __syncthreads();
   // m positions for scores as specified (fewer only with NaN scores)
   const int got = (int)min(emit_bitmap<NT>(bm, (n + 31) >> 5, write ? idx : nullptr,
@@ -619,10 +678,27 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_fused(SelectArgs a) {
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
   __shared__ uint32_t misc[8];
   const int unit = blockIdx.x;
-  select_unit(a, unit, SelLds{cand, bm, lhist, tmp, misc}, true, nullptr, 0, 0, true);
+  const int m =
+      select_unit(a, unit, SelLds{cand, bm, lhist, tmp, misc}, true, nullptr, 0, 0, true);
+  copy_selection(a, unit, m);
   // one call site, so that the merge appears once (a second inlined copy
   // kept more of the selection's registers live)
   if (a.mpart) merge_partials(a, unit, lhist);
+}
+
+// Two selections of the same units (the corrected entries: the current token's
+// and the next step's) side by side: a unit's selection is one workgroup's
+// serial chain (18 us at 64 Ki positions), and two fit beside each other.
+__global__ __launch_bounds__(kFinishThreads) void k_select_pair(SelectArgs s1, SelectArgs s2) {
+  __shared__ uint2 cand[kCandLds];
+  __shared__ uint32_t bm[kFusedSelectMaxCtx / 32];
+  __shared__ uint32_t lhist[2048];
+  __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
+  __shared__ uint32_t misc[8];
+  const bool second = (int)blockIdx.x >= s1.units;
+  const SelectArgs a = second ? s2 : s1;
+  const int unit = blockIdx.x - (second ? s1.units : 0);
+  select_unit(a, unit, SelLds{cand, bm, lhist, tmp, misc}, true, nullptr, 0, 0, true);
 }
 
 // ---- selection and attention in one launch ------------------------------------
@@ -1562,6 +1638,7 @@ static const void* score_kernel(ScoreKind kind, int chunk) {
     case ScoreKind::kPlain: return (const void*)k_score<G, false>;
     case ScoreKind::kHist:
       return chunk > 1 ? (const void*)k_score_chunks<G> : (const void*)k_score<G, true>;
+    case ScoreKind::kTwo: return (const void*)k_score_two<G>;
     case ScoreKind::kDual: return (const void*)k_dual<G, false, false>;
     case ScoreKind::kDualIndexed: return (const void*)k_dual<G, true, false>;
     case ScoreKind::kDual2:
@@ -1605,7 +1682,8 @@ int score_blocks(const ScoreArgs& a, int G, ScoreKind kind) {
   }
   if (!fn) return 0;
   const int64_t groups = (int64_t)a.units * ((a.max_ctx + kStageRows - 1) / kStageRows);
-  const bool wide = kind == ScoreKind::kHist && a.chunk <= 1;  // k_score<G, true>
+  const bool wide =  // k_score<G, true>, k_score_two<G>
+      (kind == ScoreKind::kHist && a.chunk <= 1) || kind == ScoreKind::kTwo;
   int64_t slots = resident_blocks(fn, wide ? 64 * kHistScoreWaves : kScoreThreads);
   if (slots > kMaxScoreWgs) slots = kMaxScoreWgs;
   return (int)(groups < slots ? groups : slots);
@@ -1614,7 +1692,8 @@ int score_blocks(const ScoreArgs& a, int G, ScoreKind kind) {
 template <int G>
 static void launch_score_g(const ScoreArgs& a, bool hist, int nwg, hipStream_t s) {
   const dim3 grid(nwg), block(kScoreThreads);
-  if (a.chunk > 1) launch_kernel(CKV_K_SCORE, k_score_chunks<G>, grid, block, s, a);
+  if (a.q2) launch_kernel(CKV_K_SCORE, k_score_two<G>, grid, dim3(64 * kHistScoreWaves), s, a);
+  else if (a.chunk > 1) launch_kernel(CKV_K_SCORE, k_score_chunks<G>, grid, block, s, a);
   else if (hist) launch_kernel(CKV_K_SCORE, k_score<G, true>, grid, dim3(64 * kHistScoreWaves), s, a);
   else launch_kernel(CKV_K_SCORE, k_score<G, false>, grid, block, s, a);
 }
@@ -1649,6 +1728,12 @@ hipError_t launch_finish(const SelectArgs& a, int units, hipStream_t s) {
 
 hipError_t launch_select_fused(const SelectArgs& a, int units, hipStream_t s) {
   launch_kernel(CKV_K_FINISH, k_select_fused, dim3(units), dim3(kFinishThreads), s, a);
+  return launch_status();
+}
+
+hipError_t launch_select_pair(const SelectArgs& s1, const SelectArgs& s2, hipStream_t s) {
+  if (s1.units != s2.units) return hipErrorInvalidValue;
+  launch_kernel(CKV_K_FINISH, k_select_pair, dim3(2 * s1.units), dim3(kFinishThreads), s, s1, s2);
   return launch_status();
 }
 

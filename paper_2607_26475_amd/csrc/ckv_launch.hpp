@@ -50,8 +50,9 @@ hipError_t launch_fill(void* p, size_t bytes, uint32_t pattern, hipStream_t s);
 // first-digit histogram (chunk landmarks when a.chunk > 1), or the scoring
 // role of the one-launch attend-and-score kernel (buffer or rows in place).
 // kDual2*: the same with the two tokens' 2G head rows attending (G <= 8).
+// kTwo: the standalone pass for two queries (ScoreArgs::q2).
 enum class ScoreKind {
-  kPlain, kHist, kDual, kDualIndexed, kDual2, kDual2Indexed, kDualSel, kDualSelIndexed,
+  kPlain, kHist, kTwo, kDual, kDualIndexed, kDual2, kDual2Indexed, kDualSel, kDualSelIndexed,
   kDual2Sel, kDual2SelIndexed
 };
 // Workgroups of that scoring pass for these arguments.  A call computes it
@@ -63,6 +64,8 @@ hipError_t launch_hist(const SelectArgs& a, int units, hipStream_t s);
 hipError_t launch_filter(const SelectArgs& a, int units, hipStream_t s);
 hipError_t launch_finish(const SelectArgs& a, int units, hipStream_t s);
 hipError_t launch_select_fused(const SelectArgs& a, int units, hipStream_t s);
+// two selections of the same units in one launch, as launch_select_fused
+hipError_t launch_select_pair(const SelectArgs& s1, const SelectArgs& s2, hipStream_t s);
 hipError_t launch_attn(const AttnArgs& a, int G, bool indexed, int units, hipStream_t s);
 // same-step selection and attention in one launch: heads == 1, nsplit shares
 // of rows per unit (partials [U][nsplit][G] for k_combine when nsplit > 1);

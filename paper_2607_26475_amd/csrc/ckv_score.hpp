@@ -71,52 +71,87 @@ __device__ __forceinline__ void store_hist_coherent(const uint32_t* lds_hist, ui
 // jb) into out[0, kStageRows): the MFMA products with the G query rows, the
 // maximum over the heads, the scale; rows at or past n get -inf and are not
 // counted.  If HIST, counts the first radix digit of the others in lds_hist.
-template <int G, bool HIST>
+// TWO: rows [G, 2G) of the products are a second query's, whose scores go to
+// out[stride2 ..] and are counted in the next kHistBins bins.
+template <int G, bool HIST, bool TWO = false>
 __device__ __forceinline__ void score_group(const uint32_t* stage, const bf16x8* qa, int jb,
                                             int n, float scale, uint32_t* lds_hist,
-                                            float* out) {
+                                            float* out, int stride2 = 0) {
   const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, kg = lane >> 4;
+  // with two queries each lane's result is set `set`'s: both in the first 32
+  // lanes, or with 2G = 16 rows, after one exchange, in lanes 0..15 and 32..47
+  const int set = TWO ? (G == 8 ? lane >> 5 : (lane >> 4) & 1) : 0;
+  const bool writer = TWO ? (G == 8 ? (lane & 16) == 0 : lane < 32) : lane < 16;
 #pragma unroll
   for (int u = 0; u < kStageRows / 16; ++u) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const uint4 kv = *reinterpret_cast<const uint4*>(
           stage + (16 * u + r16) * kStageRowDwords + 4 * (4 * t + kg));
       acc = mfma_16x16x32(qa[t], as_bf16x8(kv), acc);
+      if (TWO && G == 16) acc2 = mfma_16x16x32(qa[4 + t], as_bf16x8(kv), acc2);
     }
     float sc = -INFINITY;
+    if constexpr (TWO && G <= 2) {  // both queries' rows in lane group 0
+      float s1 = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * kg + i < G) sc = fmaxf(sc, acc[i]);
-    if (G > 4) sc = fmaxf(sc, __shfl_xor(sc, 16));
-    if (G > 8) sc = fmaxf(sc, __shfl_xor(sc, 32));
+      for (int i = 0; i < G; ++i) {
+        sc = fmaxf(sc, acc[i]);
+        s1 = fmaxf(s1, acc[G + i]);
+      }
+      s1 = __shfl(s1, r16);
+      sc = set ? s1 : sc;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * kg + i < (TWO && G < 16 ? 2 * G : G)) sc = fmaxf(sc, acc[i]);
+      if (G > 4) sc = fmaxf(sc, __shfl_xor(sc, 16));
+      if (G > 8) sc = fmaxf(sc, __shfl_xor(sc, 32));
+      if constexpr (TWO && G == 16) {
+        float s1 = fmaxf(fmaxf(acc2[0], acc2[1]), fmaxf(acc2[2], acc2[3]));
+        s1 = fmaxf(s1, __shfl_xor(s1, 16));
+        s1 = fmaxf(s1, __shfl_xor(s1, 32));
+        sc = set ? s1 : sc;
+      }
+    }
     sc *= scale;
-    const int j = jb + 16 * u + lane;
-    if (lane < 16) {
+    const int j = jb + 16 * u + (TWO ? r16 : lane);
+    if (writer) {
       if (j < n) {
-        if (HIST) atomicAdd(&lds_hist[order_key(sc) >> (32 - kHistBits)], 1u);
+        if (HIST)
+          atomicAdd(&lds_hist[set * kHistBins + (order_key(sc) >> (32 - kHistBits))], 1u);
       } else {
         sc = -INFINITY;
       }
-      out[16 * u + lane] = sc;
+      out[set * stride2 + 16 * u + (TWO ? r16 : lane)] = sc;
     }
   }
 }
 
-// The G query rows of a unit as MFMA A operands (rows past G are zero).
-template <int G>
+// The G query rows of a unit as MFMA A operands (rows past G are zero); TWO:
+// the second query's rows follow as rows [G, 2G), or, at G = 16, as a second
+// operand (qa[4..7]).
+template <int G, bool TWO = false>
 __device__ __forceinline__ void load_query(const ScoreArgs& a, int unit, bf16x8* qa) {
   const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, kg = lane >> 4;
   const int b = unit / a.Hkv, h = unit - b * a.Hkv;
-  const uint16_t* qrow = a.q + ((int64_t)b * a.Hq + (int64_t)h * G + r16) * kD + 8 * kg;
+  const int64_t row0 = (int64_t)b * a.Hq + (int64_t)h * G;
+  constexpr int kRows = TWO && G < 16 ? 2 * G : G;
+  const bool second = TWO && G < 16 && r16 >= G;
+  const uint16_t* qrow = (second ? a.q2 : a.q) + (row0 + (second ? r16 - G : r16)) * kD + 8 * kg;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r16 < G) v = ld16(qrow + 32 * t);
+    if (r16 < kRows) v = ld16(qrow + 32 * t);
     qa[t] = as_bf16x8(v);
+  }
+  if constexpr (TWO && G == 16) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      qa[4 + t] = as_bf16x8(ld16(a.q2 + (row0 + r16) * kD + 8 * kg + 32 * t));
   }
 }
 
@@ -183,11 +218,19 @@ __device__ __forceinline__ void fill_tails(const ScoreArgs& a, int wg, int nwg) 
 // may have more than NW waves, the others only join its barriers; scores and
 // slots are stored device-coherent, 8 bytes per lane over whole lines, and
 // each finished (unit, slot) is handed over through fs (FusedSync).
-template <int G, bool HIST, int NW = 4, bool HALVES = false, bool FUSED = false>
+//
+// TWO: the pass scores two queries (a.q and a.q2) against each key it reads,
+// into two score arrays and two histograms (lds_hist holds both); a wave's
+// score buffer is shared by the two, so it is flushed twice as often.
+template <int G, bool HIST, int NW = 4, bool HALVES = false, bool FUSED = false, bool TWO = false>
 __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
                                             uint32_t* lds_hist,
                                             uint32_t* lds_stage, FusedSync fs = FusedSync{}) {
   static_assert(!FUSED || (HIST && !HALVES), "the fused scoring role counts histograms");
+  static_assert(!TWO || (HIST && !FUSED), "two queries: the pass with histograms");
+  constexpr int kSets = TWO ? 2 : 1;
+  constexpr int kFlush = kFlushGroups / kSets;      // groups of scores held per query
+  constexpr int kSetStride = kFlush * kStageRows;
   constexpr int NT = 64 * NW;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -228,119 +271,126 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
     const uint32_t ubase = it.base + h * it.vg;
     const uint32_t seg_end = min(g1, ubase + it.vg);
     const int n = it.n;
-    float* srow = a.scores + (int64_t)unit * a.max_ctx;
-    {
-      if (HIST) {
-        if (!FUSED || tid < NT)
-          for (int i = tid; i < kHistBins; i += NT) lds_hist[i] = 0u;
-        __syncthreads();
-      }
-      bf16x8 qa[4];
-      load_query<G>(a, unit, qa);
-      const uint16_t* kunit = a.keys + (int64_t)unit * a.max_ctx * a.key_stride;
-      // Rows at or past n_b load row n_b - 1 instead (their scores are
-      // replaced by -inf): lane-conditional loads would make the compiler
-      // wait for every outstanding load at each use.
-      // loads [i0, i1) of a group's kLoads
-      auto load_part = [&](uint32_t gg, uint4* v, int i0, int i1) {
-        const int jb = (int)(gg - ubase) * kStageRows;
+    if (HIST) {
+      if (!FUSED || tid < NT)
+        for (int i = tid; i < kSets * kHistBins; i += NT) lds_hist[i] = 0u;
+      __syncthreads();
+    }
+    bf16x8 qa[TWO && G == 16 ? 8 : 4];
+    load_query<G, TWO>(a, unit, qa);
+    const uint16_t* kunit = a.keys + (int64_t)unit * a.max_ctx * a.key_stride;
+    // Rows at or past n_b load row n_b - 1 instead (their scores are
+    // replaced by -inf): lane-conditional loads would make the compiler
+    // wait for every outstanding load at each use.
+    // loads [i0, i1) of a group's kLoads
+    auto load_part = [&](uint32_t gg, uint4* v, int i0, int i1) {
+      const int jb = (int)(gg - ubase) * kStageRows;
 #pragma unroll
-        for (int i = i0; i < i1; ++i) {
-          const int j = min(jb + 4 * i + lrow, n - 1);
-          v[i] = ld16_nt(kunit + (int64_t)j * a.key_stride + 8 * lchunk);
-        }
-      };
-      auto load_group = [&](uint32_t gg, uint4* v) { load_part(gg, v, 0, kLoads); };
-      // writes the scores of the nb buffered groups [first, first + nb): one
-      // contiguous run, 16 bytes per lane when rows are 16-byte aligned
-      auto flush = [&](uint32_t first, int nb) {
-        __builtin_amdgcn_wave_barrier();
-        const int jb = (int)(first - ubase) * kStageRows;
-        const int count = nb * kStageRows;
-        if constexpr (FUSED) {
-          // 8 bytes per lane, consecutive lanes on consecutive pairs: each
-          // instruction covers whole 128-byte lines of four groups
-          for (int c = 2 * lane; c < count; c += 128) {
-            const int j = jb + (c / kStageRows) * NW * kStageRows + c % kStageRows;
-            const float2 v = *reinterpret_cast<const float2*>(sbuf + c);
-            if ((a.max_ctx & 1) == 0 && j + 1 < a.max_ctx) {
-              const uint64_t w = (uint64_t)__float_as_uint(v.x) |
-                                 ((uint64_t)__float_as_uint(v.y) << 32);
-              __hip_atomic_store(reinterpret_cast<uint64_t*>(srow + j), w, __ATOMIC_RELAXED,
+      for (int i = i0; i < i1; ++i) {
+        const int j = min(jb + 4 * i + lrow, n - 1);
+        v[i] = ld16_nt(kunit + (int64_t)j * a.key_stride + 8 * lchunk);
+      }
+    };
+    auto load_group = [&](uint32_t gg, uint4* v) { load_part(gg, v, 0, kLoads); };
+    // writes the scores of `count` buffered positions of one query, the
+    // wave's groups from position jb on: one contiguous run, 16 bytes per
+    // lane when rows are 16-byte aligned
+    auto flush_rows = [&](float* scores, const float* buf, int jb, int count) {
+      float* const srow = scores + (int64_t)unit * a.max_ctx;
+      if constexpr (FUSED) {
+        // 8 bytes per lane, consecutive lanes on consecutive pairs: each
+        // instruction covers whole 128-byte lines of four groups
+        for (int c = 2 * lane; c < count; c += 128) {
+          const int j = jb + (c / kStageRows) * NW * kStageRows + c % kStageRows;
+          const float2 v = *reinterpret_cast<const float2*>(buf + c);
+          if ((a.max_ctx & 1) == 0 && j + 1 < a.max_ctx) {
+            const uint64_t w = (uint64_t)__float_as_uint(v.x) |
+                               ((uint64_t)__float_as_uint(v.y) << 32);
+            __hip_atomic_store(reinterpret_cast<uint64_t*>(srow + j), w, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+          } else {
+            if (j < a.max_ctx)
+              __hip_atomic_store(srow + j, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (j + 1 < a.max_ctx)
+              __hip_atomic_store(srow + j + 1, v.y, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-              if (j < a.max_ctx)
-                __hip_atomic_store(srow + j, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              if (j + 1 < a.max_ctx)
-                __hip_atomic_store(srow + j + 1, v.y, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-          }
-        } else if ((a.max_ctx & 3) == 0) {
-          for (int c = 4 * lane; c < count; c += 256) {
-            const float4 v = *reinterpret_cast<const float4*>(sbuf + c);
-            const int j = jb + (c / kStageRows) * NW * kStageRows + c % kStageRows;
-            if (j + 3 < a.max_ctx) {
-              *reinterpret_cast<float4*>(srow + j) = v;
-            } else {
-              if (j < a.max_ctx) srow[j] = v.x;
-              if (j + 1 < a.max_ctx) srow[j + 1] = v.y;
-              if (j + 2 < a.max_ctx) srow[j + 2] = v.z;
-            }
-          }
-        } else {
-          for (int c = lane; c < count; c += 64) {
-            const int j = jb + (c / kStageRows) * NW * kStageRows + c % kStageRows;
-            if (j < a.max_ctx) srow[j] = sbuf[c];
           }
         }
-        __builtin_amdgcn_wave_barrier();
-      };
-      // this wave's groups of the segment: every NW-th one (none for the waves
-      // past NW of the fused role)
-      const uint32_t w1 = seg_end, w0 = active ? seg + wave : w1;
-      uint4 cur[kLoads], nxt[kLoads];
-      uint32_t gg = w0;
-      uint32_t first = gg;
-      int nb = 0;
-      if (gg < w1) load_group(gg, cur);
+      } else if ((a.max_ctx & 3) == 0) {
+        for (int c = 4 * lane; c < count; c += 256) {
+          const float4 v = *reinterpret_cast<const float4*>(buf + c);
+          const int j = jb + (c / kStageRows) * NW * kStageRows + c % kStageRows;
+          if (j + 3 < a.max_ctx) {
+            *reinterpret_cast<float4*>(srow + j) = v;
+          } else {
+            if (j < a.max_ctx) srow[j] = v.x;
+            if (j + 1 < a.max_ctx) srow[j + 1] = v.y;
+            if (j + 2 < a.max_ctx) srow[j + 2] = v.z;
+          }
+        }
+      } else {
+        for (int c = lane; c < count; c += 64) {
+          const int j = jb + (c / kStageRows) * NW * kStageRows + c % kStageRows;
+          if (j < a.max_ctx) srow[j] = buf[c];
+        }
+      }
+    };
+    // the nb buffered groups from group `first` on
+    auto flush = [&](uint32_t first, int nb) {
+      __builtin_amdgcn_wave_barrier();
+      const int jb = (int)(first - ubase) * kStageRows;
+      flush_rows(a.scores, sbuf, jb, nb * kStageRows);
+      if (TWO) flush_rows(a.scores2, sbuf + kSetStride, jb, nb * kStageRows);
+      __builtin_amdgcn_wave_barrier();
+    };
+    // this wave's groups of the segment: every NW-th one (none for the waves
+    // past NW of the fused role)
+    const uint32_t w1 = seg_end, w0 = active ? seg + wave : w1;
+    uint4 cur[kLoads], nxt[kLoads];
+    uint32_t gg = w0;
+    uint32_t first = gg;
+    int nb = 0;
+    if (gg < w1) load_group(gg, cur);
 #pragma unroll 1
-      for (; gg < w1; gg += NW) {
+    for (; gg < w1; gg += NW) {
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i)
-          *reinterpret_cast<uint4*>(stage + (4 * i + lrow) * kStageRowDwords + 4 * lchunk) =
-              cur[i];
-        const bool more = gg + NW < w1;
-        if (more) load_part(gg + NW, nxt, 0, HALVES ? kLoads / 2 : kLoads);
-        __builtin_amdgcn_wave_barrier();
-        score_group<G, HIST>(stage, qa, (int)(gg - ubase) * kStageRows, n, a.scale, lds_hist,
-                             sbuf + nb * kStageRows);
-        if (HALVES && more) {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          load_part(gg + NW, nxt, kLoads / 2, kLoads);
-        }
-        if (++nb == kFlushGroups) {
-          flush(first, nb);
-          first = gg + NW;
-          nb = 0;
-        }
-        __builtin_amdgcn_wave_barrier();
+      for (int i = 0; i < kLoads; ++i)
+        *reinterpret_cast<uint4*>(stage + (4 * i + lrow) * kStageRowDwords + 4 * lchunk) =
+            cur[i];
+      const bool more = gg + NW < w1;
+      if (more) load_part(gg + NW, nxt, 0, HALVES ? kLoads / 2 : kLoads);
+      __builtin_amdgcn_wave_barrier();
+      score_group<G, HIST, TWO>(stage, qa, (int)(gg - ubase) * kStageRows, n, a.scale,
+                                lds_hist, sbuf + nb * kStageRows, kSetStride);
+      if (HALVES && more) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        load_part(gg + NW, nxt, kLoads / 2, kLoads);
+      }
+      if (++nb == kFlush) {
+        flush(first, nb);
+        first = gg + NW;
+        nb = 0;
+      }
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i) cur[i] = nxt[i];
+      for (int i = 0; i < kLoads; ++i) cur[i] = nxt[i];
+    }
+    if (nb) flush(first, nb);
+    if (HIST) {
+      __syncthreads();
+      if constexpr (FUSED) {
+        if (tid < NT) store_hist_coherent<NT>(lds_hist, a.hist_part + slot * kHistBins);
+      } else if (a.hist_part) {
+        store_hist<NT>(lds_hist, a.hist_part + slot * kHistBins);
+        if (TWO) store_hist<NT>(lds_hist + kHistBins, a.hist_part2 + slot * kHistBins);
+      } else {
+        flush_hist<NT>(lds_hist, a.hist + (int64_t)unit * kHistBins,
+                       a.coarse + (int64_t)unit * kCoarseBins);
+        if (TWO)
+          flush_hist<NT>(lds_hist + kHistBins, a.hist2 + (int64_t)unit * kHistBins,
+                         a.coarse2 + (int64_t)unit * kCoarseBins);
       }
-      if (nb) flush(first, nb);
-      if (HIST) {
-        __syncthreads();
-        if constexpr (FUSED) {
-          if (tid < NT) store_hist_coherent<NT>(lds_hist, a.hist_part + slot * kHistBins);
-        } else if (a.hist_part) {
-          store_hist<NT>(lds_hist, a.hist_part + slot * kHistBins);
-        } else {
-          flush_hist<NT>(lds_hist, a.hist + (int64_t)unit * kHistBins,
-                         a.coarse + (int64_t)unit * kCoarseBins);
-        }
-        __syncthreads();
-      }
+      __syncthreads();
     }
     seg = seg_end;
   }

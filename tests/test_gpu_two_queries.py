@@ -1,0 +1,89 @@
+"""Two queries scored in one pass over the keys (MI355X only).
+
+The corrected entry selects the current token's set and the next step's from
+one pass.  Every group size has its own placement of the two queries' head
+rows in the matrix products; histograms go to slots (many units) or are added
+(few units, long contexts); heavy ties exceed a selection's candidate list.
+The caller may pass one query for both (the set is then written twice) and
+may let the next step's sets take the place of the prediction.  Sets against
+the oracle, outputs against the oracle's attention over the sets.
+"""
+from __future__ import annotations
+
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_26475_amd as ckv
+import synth
+from helpers import (ATOL_OUT, SCALE, check_index_sets, device, make_prediction,
+                     oracle_attn_over, orc, u16)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # name, B, Hkv, G, stored rows, k, queries, next set in the prediction's place
+    ("g1", 2, 2, 1, 1031, 96, 2, False),
+    ("g2", 2, 2, 2, 1030, 96, 2, False),
+    ("g4", 2, 2, 4, 4500, 256, 2, True),
+    ("g8", 2, 2, 8, 1028, 300, 2, False),
+    ("g16", 2, 1, 16, 1027, 96, 2, False),
+    ("slots", 16, 8, 4, 700, 64, 2, False),
+    ("slots_g16", 64, 2, 16, 300, 64, 2, True),
+    ("one_query", 3, 2, 4, 2000, 128, 1, False),
+    ("one_query_in_place", 3, 2, 4, 2000, 128, 1, True),
+    ("long", 1, 2, 4, 70001, 500, 2, False),
+    ("long_in_place", 1, 2, 4, 70001, 500, 2, True),
+    ("long_one", 1, 2, 4, 70001, 500, 1, False),
+    ("ties", 1, 2, 4, 40000, 700, 2, False),
+]
+
+
+@pytest.mark.parametrize("name,B,Hkv,G,n,k,queries,in_place", CASES, ids=[c[0] for c in CASES])
+def test_two_queries(name, B, Hkv, G, n, k, queries, in_place):
+    print("two queries", name, flush=True)
+    dev = device()
+    w = dataclasses.replace(synth.WORKLOADS["dual64_s"], name=f"twoq_{name}", batch=B,
+                            q_heads=G * Hkv, kv_heads=Hkv, max_ctx=n, ctx_min=max(1, n // 3), k=k,
+                            layers=1)
+    t = synth.make_layer(w, seed=51, device=dev)
+    if B >= 3:
+        t["ctx_lens"][0], t["ctx_lens"][1], t["ctx_lens"][2] = 0, k - 1, n
+    if name == "ties":  # almost every score equal
+        t["k"][:, :, 100:] = t["k"][:, :, 100:101].clone()
+    lens = t["ctx_lens"].cpu().numpy()
+    q, K, V = u16(t["q"]), u16(t["k"]), u16(t["v"])
+    qs = u16(t["q_sel"]) if queries == 2 else q
+    o = orc()
+    so = o.shape(B, G * Hkv, Hkv, w.head_dim, n)
+    S = [o.score_keys(so, x, K, lens, SCALE, nthreads=8) for x in (q, qs)]
+    want = [o.select_topk(so, s, lens, k, nthreads=8) for s in S]
+    pred, npred = make_prediction("half", S[0], S[1], lens, k, n, np.random.default_rng(3))
+
+    s = ckv.shape_for(B, G * Hkv, Hkv, n)
+    i32 = dict(dtype=torch.int32, device=dev)
+    idx_pred, n_pred = torch.from_numpy(pred).to(dev), torch.from_numpy(npred).to(dev)
+    kb = torch.zeros((B, Hkv, k, w.head_dim), dtype=torch.bfloat16, device=dev)
+    vb = torch.zeros_like(kb)
+    ckv.gather_kv(s, t["k"], t["v"], ckv.SRC_DEVICE, idx_pred, n_pred, k, kb, vb)
+    idx_true, n_true = torch.full((B, Hkv, k), -9, **i32), torch.full((B, Hkv), -9, **i32)
+    idx_next = idx_pred if in_place else torch.full((B, Hkv, k), -9, **i32)
+    n_next = n_pred if in_place else torch.full((B, Hkv), -9, **i32)
+    hits = torch.full((B, Hkv), -9, **i32)
+    out = torch.full((B, G * Hkv, w.head_dim), float("nan"), device=dev)
+    ws = ckv.workspace(s, k, ckv.ENTRY_CORRECTED_ATTN)
+    ws.fill_(0xA5)
+    ckv.corrected_attn(s, t["q"], t["q_sel"] if queries == 2 else None, t["k"], t["ctx_lens"], k,
+                       SCALE, t["k"], t["v"], ckv.SRC_DEVICE, idx_pred, n_pred, kb, vb, idx_true,
+                       n_true, hits, idx_next, n_next, out, ws)
+    torch.cuda.synchronize()
+    g_true, g_nt = idx_true.cpu().numpy(), n_true.cpu().numpy()
+    check_index_sets(g_true, g_nt, *want[0], S[0], lens)
+    check_index_sets(idx_next.cpu().numpy(), n_next.cpu().numpy(), *want[1], S[1], lens)
+    for b in range(B):
+        for h in range(Hkv):
+            both = np.intersect1d(g_true[b, h, :g_nt[b, h]], pred[b, h, :npred[b, h]])
+            assert int(hits[b, h]) == len(both), (b, h)
+    ref = oracle_attn_over(so, q, K, V, g_true, g_nt, k)
+    assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
