@@ -226,7 +226,7 @@ Layout make_layout(const Dims& d, int32_t k, int entry) {
     L.zero_end = off;
     L.sel = off;
     off = align256(off + U * (size_t)k * 4);
-    // the filter's candidate positions, then the corrected entries' second scores
+    // the filter's candidates; the corrected entries' second scores take half
     L.cand = off;
     L.scores2 = off + U * (size_t)d.max_ctx * 4;
     off = align256(off + U * (size_t)d.max_ctx * 8);
@@ -360,6 +360,7 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
   a.ctrl = at<uint32_t>(ws, L.ctrl);
   a.sel = at<int32_t>(ws, L.sel);
   a.cand = at<uint32_t>(ws, L.cand);
+  a.cand_keys = 1;
   a.bitmap = L.bm_words ? at<uint32_t>(ws, L.bitmap) : nullptr;
   a.idx = idx;
   a.n_sel = n_sel;
@@ -1338,6 +1339,7 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
     sc.scores2 = at<float>(ws, L.scores2);
     sc.hist2 = s2.hist;
     sc.coarse2 = s2.coarse;
+    s1.cand_keys = s2.cand_keys = 0;  // the second scores take that space
   }
   const int nwg = score_blocks(sc, d.G, one ? ScoreKind::kHist : ScoreKind::kTwo);
   const size_t slots_bytes = (size_t)(d.U + nwg) * kHistBins * 4;

@@ -19,6 +19,7 @@ constexpr int kStageRowDwords = 68;  // 256-byte row + 16-byte pad (bank spread)
 constexpr int kStageDwords = kStageRows * kStageRowDwords;
 constexpr int kFlushGroups = 64;   // groups of scores held per wave in LDS
 constexpr int kClaimGroups = 64;   // groups per claim of the dynamic scoring pass
+constexpr int kStaticEighths = 4;  // of a unit's claims, those scored as static ranges
 constexpr int kMinClaimsPerWg = 4; // claims per workgroup from which a pass takes claims
 constexpr int kScoreLdsDwords = 4 * kStageDwords + 4 * kFlushGroups * kStageRows;
 
@@ -30,8 +31,8 @@ constexpr int kHistBins = 1 << kHistBits;
 constexpr int kCoarseBins = 64;
 constexpr int kCtrlWords = 4;      // per unit: above, cand, digit-1 bin, and (unit 0
 constexpr int kCtrlClaim = 3;      //   only) the scoring pass's claim counter
-constexpr int kFilterThreads = 256;
-constexpr int kFilterTile = 4096;  // positions per filter workgroup
+constexpr int kFilterThreads = 1024;
+constexpr int kFilterTile = 16384; // positions per filter workgroup
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishLdsBytes = 128 * 1024;   // candidates or bitmap
 constexpr int kCandLds = kFinishLdsBytes / 8;  // (key, pos) pairs held in LDS
@@ -111,8 +112,10 @@ struct SelectArgs {
   int units;
   int32_t* sel;             // [U][k]   positions above the digit-1 bin, then
                             //          the chosen candidates
-  uint32_t* cand;           // [U][max_ctx] positions inside the digit-1 bin (the
-                            //   filter's; a one-workgroup selection has no list)
+  uint32_t* cand;           // the filter's candidates, inside the digit-1 bin:
+  int cand_keys;            //   [U][max_ctx] (order key, position), or with
+                            //   cand_keys 0 positions only (half the memory; the
+                            //   finish then gathers their scores)
   uint32_t* bitmap;         // [U][bm_words] when max_ctx > kBitmapLdsBits
   int32_t* idx;             // [U][k]
   int32_t* n_sel;           // [U]
@@ -344,20 +347,6 @@ __device__ __forceinline__ float wave_sum(float x) {
 }
 
 
-// Wave-aggregated append: lanes with `flag` get consecutive slots from the
-// counter at *ctr (one atomic per wave); returns this lane's slot.
-__device__ __forceinline__ uint32_t wave_append(bool flag, uint32_t* ctr) {
-  const unsigned long long mask = __ballot(flag);
-  const uint32_t cnt = (uint32_t)__popcll(mask);
-  const uint32_t lo = (uint32_t)mask, hi = (uint32_t)(mask >> 32);
-  const uint32_t rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-  const int leader = cnt ? __ffsll(mask) - 1 : 0;
-  uint32_t base = 0u;
-  if (cnt && (int)(threadIdx.x & 63) == leader) base = atomicAdd(ctr, cnt);
-  base = __builtin_amdgcn_readlane(base, leader);
-  return base + rank;
-}
-
 template <int CTRL, int ROW_MASK, bool ZERO_FILL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xF, ZERO_FILL);
@@ -403,8 +392,9 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
 // requests (mult units each), or, for the XCD-affine ranges of the one-launch
 // kernel, units x, x + 8, ... of XCD x.  Valid groups fit in 32 bits: a group is
 // 8 KiB of keys.  All functions are wave-uniform and need all 64 lanes.
+template <int ROWS = kStageRows>
 __device__ __forceinline__ uint32_t groups_of(int n) {
-  return (uint32_t)(n + kStageRows - 1) / kStageRows;
+  return ((uint32_t)n + ROWS - 1) / ROWS;
 }
 
 struct GroupScan {
@@ -412,16 +402,16 @@ struct GroupScan {
   uint32_t s;  // inclusive sum of its groups
 };
 
-// Sum of the groups of the ni items (one unit each); *first: the scan of
-// items 0..63.  len(i): item i's entries per unit.
-template <class LEN>
+// Sum of the groups of ROWS positions of the ni items (one unit each); *first:
+// the scan of items 0..63.  len(i): item i's entries per unit.
+template <int ROWS = kStageRows, class LEN>
 __device__ __forceinline__ uint32_t sum_groups(int ni, LEN len, GroupScan* first) {
   const int lane = threadIdx.x & 63;
   first->n = lane < ni ? len(lane) : 0;
-  first->s = wave_incl_scan(groups_of(first->n));
+  first->s = wave_incl_scan(groups_of<ROWS>(first->n));
   uint32_t t = __builtin_amdgcn_readlane(first->s, 63);
   for (int i0 = 64; i0 < ni; i0 += 64)
-    t += wave_sum_u32(i0 + lane < ni ? groups_of(len(i0 + lane)) : 0u);
+    t += wave_sum_u32(i0 + lane < ni ? groups_of<ROWS>(len(i0 + lane)) : 0u);
   return t;
 }
 
@@ -448,7 +438,7 @@ struct GroupItem {
   int item, n;
   uint32_t vg, base;
 };
-template <class LEN>
+template <int ROWS = kStageRows, class LEN>
 __device__ __forceinline__ GroupItem find_item(int ni, LEN len, GroupScan first, uint32_t mult,
                                                uint32_t g) {
   const int lane = threadIdx.x & 63;
@@ -458,16 +448,23 @@ __device__ __forceinline__ GroupItem find_item(int ni, LEN len, GroupScan first,
     base += mult * __builtin_amdgcn_readlane(first.s, 63);
     i0 += 64;
     first.n = i0 + lane < ni ? len(i0 + lane) : 0;
-    first.s = wave_incl_scan(groups_of(first.n));
+    first.s = wave_incl_scan(groups_of<ROWS>(first.n));
   }
   const uint64_t past = __ballot(base + mult * first.s > g);
   const int l = past ? __ffsll((unsigned long long)past) - 1 : 63;
   GroupItem r;
   r.item = i0 + l;
   r.n = __builtin_amdgcn_readlane(first.n, l);
-  r.vg = groups_of(r.n);
+  r.vg = groups_of<ROWS>(r.n);
   r.base = base + mult * (__builtin_amdgcn_readlane(first.s, l) - r.vg);
   return r;
+}
+
+// The rows of a unit of n positions that a pass with claims scores as static
+// ranges before it takes claims: whole claims, and never the last one.
+__device__ __forceinline__ int static_rows(int n) {
+  constexpr int kRows = kClaimGroups * kStageRows;
+  return (int)((groups_of<kRows>(n) * kStaticEighths) >> 3) * kRows;
 }
 
 // Groups per range: an equal share of the total, at least min_range (the host

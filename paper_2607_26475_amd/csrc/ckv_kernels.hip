@@ -7,7 +7,6 @@
 
 #include <algorithm>
 #include <mutex>
-#include <type_traits>
 
 namespace ckv {
 
@@ -67,7 +66,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_chunks(ScoreArgs a) {
 
 // ---- selection -----------------------------------------------------------
 // First-digit histogram of given scores (standalone selection entry).
-__global__ __launch_bounds__(kScoreThreads) void k_hist(SelectArgs a) {
+__global__ __launch_bounds__(kFilterThreads) void k_hist(SelectArgs a) {
   __shared__ uint32_t lds_hist[kHistBins];
   const int unit = blockIdx.x / a.tiles;
   const int tile = blockIdx.x - unit * a.tiles;
@@ -76,19 +75,21 @@ __global__ __launch_bounds__(kScoreThreads) void k_hist(SelectArgs a) {
   const int j0 = tile * kFilterTile;
   if (j0 >= n) return;
   const int jend = min(j0 + kFilterTile, n);
-  for (int i = threadIdx.x; i < kHistBins; i += kScoreThreads) lds_hist[i] = 0u;
+  for (int i = threadIdx.x; i < kHistBins; i += kFilterThreads) lds_hist[i] = 0u;
   __syncthreads();
   const float* srow = a.scores + (int64_t)unit * a.max_ctx;
-  for (int j = j0 + threadIdx.x; j < jend; j += kScoreThreads)
+  for (int j = j0 + threadIdx.x; j < jend; j += kFilterThreads)
     atomicAdd(&lds_hist[order_key(srow[j]) >> (32 - kHistBits)], 1u);
   __syncthreads();
-  flush_hist(lds_hist, a.hist + (int64_t)unit * kHistBins,
-             a.coarse + (int64_t)unit * kCoarseBins);
+  flush_hist<kFilterThreads>(lds_hist, a.hist + (int64_t)unit * kHistBins,
+                             a.coarse + (int64_t)unit * kCoarseBins);
 }
 
 // Selects positions above the first-digit bin of the m-th largest key and
-// collects the positions inside that bin as candidates (their scores are read
-// again by the finish).
+// collects the positions inside that bin as candidates.  A workgroup reserves its output slots with one atomic
+// on the unit's control words, which share a cache line with other units':
+// with 256-thread workgroups of 4096 positions and two atomics each, a million
+// positions per unit (8 units) took 37.5 us, all of it those atomics' queue.
 __global__ __launch_bounds__(kFilterThreads) void k_filter(SelectArgs a) {
   constexpr int kPer = kFilterTile / kFilterThreads;  // 16 positions per thread
   __shared__ uint32_t sh[4];
@@ -111,34 +112,46 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter(SelectArgs a) {
                    a.hist + (int64_t)unit * kHistBins, (uint32_t)m, sh);
   __syncthreads();
   const uint32_t b1 = sh[0];
+  uint32_t keys[kPer];
   uint32_t selmask = 0u, candmask = 0u;
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     const int j = j0 + r * kFilterThreads + threadIdx.x;
+    keys[r] = order_key(sv[r]);
     if (j < n) {
-      const uint32_t d1 = order_key(sv[r]) >> (32 - kHistBits);
+      const uint32_t d1 = keys[r] >> (32 - kHistBits);
       if (d1 > b1) selmask |= 1u << r;
       else if (d1 == b1) candmask |= 1u << r;
     }
   }
   const uint32_t cnt = (uint32_t)__popc(selmask) | ((uint32_t)__popc(candmask) << 16);
+  static_assert(kFilterTile < 65536, "counts of a tile in 16 bits each");
   uint32_t total;
   const uint32_t excl = block_incl_scan<kFilterThreads / 64>(cnt, scan_tmp, &total) - cnt;
   if (threadIdx.x == 0) {
     uint32_t* ctrl = a.ctrl + (int64_t)unit * kCtrlWords;
-    sh[2] = (total & 0xffffu) ? atomicAdd(&ctrl[0], total & 0xffffu) : 0u;
-    sh[3] = (total >> 16) ? atomicAdd(&ctrl[1], total >> 16) : 0u;
+    // words 0 and 1 (selected, candidates) as one 64-bit counter
+    const unsigned long long add = (total & 0xffffu) | ((unsigned long long)(total >> 16) << 32);
+    const unsigned long long at =
+        total ? atomicAdd(reinterpret_cast<unsigned long long*>(ctrl), add) : 0ull;
+    sh[2] = (uint32_t)at;
+    sh[3] = (uint32_t)(at >> 32);
     if (tile == 0) ctrl[2] = b1;
   }
   __syncthreads();
   uint32_t os = sh[2] + (excl & 0xffffu), oc = sh[3] + (excl >> 16);
   int32_t* sel = a.sel + (int64_t)unit * a.k;
-  uint32_t* cand = a.cand + (int64_t)unit * a.max_ctx;
+  uint2* pairs = reinterpret_cast<uint2*>(a.cand) + (int64_t)unit * a.max_ctx;
+  uint32_t* plain = a.cand + (int64_t)unit * a.max_ctx;
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     const int j = j0 + r * kFilterThreads + threadIdx.x;
-    if ((selmask >> r) & 1u) sel[os++] = j;
-    else if ((candmask >> r) & 1u) cand[oc++] = (uint32_t)j;
+    if ((selmask >> r) & 1u) {
+      sel[os++] = j;
+    } else if ((candmask >> r) & 1u) {
+      if (a.cand_keys) pairs[oc++] = make_uint2(keys[r], (uint32_t)j);
+      else plain[oc++] = (uint32_t)j;
+    }
   }
 }
 
@@ -215,15 +228,14 @@ __device__ __forceinline__ uint32_t emit_bitmap(const uint32_t* bm, int words, i
   return total;
 }
 
-// Radix select among the candidates, those of cs's nc entries for which
-// cs.get gives (order key, position); all share the first digit b1: the need
-// largest by (key descending, position ascending).
+// Radix select among the candidates, which cs.each(f) presents as f(order key,
+// position), each by one of the NT threads; all share the first digit b1: the
+// need largest by (key descending, position ascending).
 // Returns the threshold key T; candidates with key > T are all chosen, and of
 // those equal to T the ones with position <= *pmax.  All NT threads call
-// this; hist needs 2048 words.
-template <class Cands, int NT = kFinishThreads>
-__device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t nc,
-                                                     uint32_t need, uint32_t b1,
+// this; hist needs 2048 words, misc 4.
+template <int NT, class Cands>
+__device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t need, uint32_t b1,
                                                      uint32_t* hist, uint32_t* tmp,
                                                      uint32_t* misc, uint32_t* pmax) {
   const int tid = threadIdx.x;
@@ -231,26 +243,22 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
   static_assert(kHistBits == 11, "digits 11 + 11 + 10");
   for (int i = tid; i < 2048; i += NT) hist[i] = 0u;
   __syncthreads();
-  for (uint32_t i = tid; i < nc; i += NT) {
-    uint2 c;
-    if (cs.get(i, &c)) atomicAdd(&hist[(c.x >> 10) & 2047u], 1u);
-  }
+  cs.each([&](uint32_t key, uint32_t) { atomicAdd(&hist[(key >> 10) & 2047u], 1u); });
   __syncthreads();
-  uint32_t need2;
-  const uint32_t b2 = find_bin_block<true, NT>(hist, 2048, need, tmp, misc, &need2);
+  if (tid < 64) find_first_bin_lds<2048>(hist, need, misc);
+  __syncthreads();
+  const uint32_t b2 = misc[0], need2 = need - misc[1];
   // Third digit: bits 9..0, among candidates whose second digit is b2.
   for (int i = tid; i < 1024; i += NT) hist[i] = 0u;
   __syncthreads();
-  for (uint32_t i = tid; i < nc; i += NT) {
-    uint2 c;
-    if (cs.get(i, &c) && ((c.x >> 10) & 2047u) == b2) atomicAdd(&hist[c.x & 1023u], 1u);
-  }
+  cs.each([&](uint32_t key, uint32_t) {
+    if (((key >> 10) & 2047u) == b2) atomicAdd(&hist[key & 1023u], 1u);
+  });
   __syncthreads();
-  uint32_t need3;
-  const uint32_t b3 = find_bin_block<true, NT>(hist, 1024, need2, tmp, misc, &need3);
-  const uint32_t T = (b1 << 21) | (b2 << 10) | b3;
-  const uint32_t eq = hist[b3];  // candidates with key == T
+  if (tid < 64) find_first_bin_lds<1024>(hist, need2, misc);
   __syncthreads();
+  const uint32_t T = (b1 << 21) | (b2 << 10) | misc[0];
+  const uint32_t need3 = need2 - misc[1], eq = misc[2];  // eq candidates have key T
 
   // Ties at T: keep the need3 lowest positions (radix select on position,
   // ascending, 8 bits at a time).
@@ -258,16 +266,16 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
   if (eq > need3) {
     uint32_t prefix = 0u, want = need3;
     for (int shift = 24; shift >= 0; shift -= 8) {
+      __syncthreads();  // misc and hist of the step before have been read
       for (int i = tid; i < 256; i += NT) hist[i] = 0u;
       __syncthreads();
       const uint32_t hi_mask = shift == 24 ? 0u : (0xffffffffu << (shift + 8));
-      for (uint32_t i = tid; i < nc; i += NT) {
-        uint2 c;
-        if (cs.get(i, &c) && c.x == T && (c.y & hi_mask) == prefix) atomicAdd(&hist[(c.y >> shift) & 255u], 1u);
-      }
+      cs.each([&](uint32_t key, uint32_t pos) {
+        if (key == T && (pos & hi_mask) == prefix) atomicAdd(&hist[(pos >> shift) & 255u], 1u);
+      });
       __syncthreads();
       uint32_t rest;
-      const uint32_t bb = find_bin_block<false, NT>(hist, 256, want, tmp, misc, &rest);
+      const uint32_t bb = find_bin_block<NT>(hist, 256, want, tmp, misc, &rest);
       prefix |= bb << shift;
       want = rest;
     }
@@ -276,26 +284,52 @@ __device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t n
   return T;
 }
 
-// The finish's candidates: (order key, position) in LDS, or, past its
-// capacity, the filter's list of positions and their scores.
+// The finish's candidates: in registers, kRegCands per thread, or, past that
+// many, the filter's list.
+constexpr int kRegCands = 16;
+
 struct ListCands {
-  const uint2* lds;  // null: the list
-  const uint32_t* pos;
+  const uint2* pairs;
+  const uint32_t* plain;  // non-null: the list holds positions only
   const float* srow;
-  __device__ __forceinline__ bool get(uint32_t i, uint2* c) const {
-    if (lds) {
-      *c = lds[i];
-    } else {
-      const uint32_t p = pos[i];
-      *c = make_uint2(order_key(srow[p]), p);
+  uint32_t nc;
+  __device__ __forceinline__ uint2 listed(uint32_t i) const {
+    if (!plain) return pairs[i];
+    const uint32_t p = plain[i];
+    return make_uint2(order_key(srow[p]), p);
+  }
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+    for (uint32_t i = threadIdx.x; i < nc; i += kFinishThreads) {
+      const uint2 c = listed(i);
+      f(c.x, c.y);
     }
-    return true;
   }
 };
 
+struct RegCands {
+  uint2 c[kRegCands];
+  uint32_t nc;
+  __device__ __forceinline__ void load(const ListCands& l) {
+    nc = l.nc;
+#pragma unroll
+    for (int u = 0; u < kRegCands; ++u)  // unconditional (clamped) loads, all in flight
+      c[u] = l.listed(min((uint32_t)(u * kFinishThreads) + threadIdx.x, nc - 1u));
+  }
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+#pragma unroll
+    for (int u = 0; u < kRegCands; ++u)
+      if (u * kFinishThreads + threadIdx.x < nc) f(c[u].x, c[u].y);
+  }
+};
+
+// One workgroup per unit, a serial chain of passes over its candidates.  They
+// stay in registers (a million positions: 10 Ki of them), so the position
+// bitmap has the LDS to itself from the start and is marked directly.
 __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
-  __shared__ uint2 area[kCandLds];  // candidates, later the position bitmap
-  __shared__ uint32_t hist[2048];
+  __shared__ uint32_t lds_bm[kBitmapLdsBits / 32];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[2048];
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
   __shared__ uint32_t misc[8];
   const int unit = blockIdx.x;
@@ -314,45 +348,31 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
   const uint32_t* ctrl = a.ctrl + (int64_t)unit * kCtrlWords;
   const uint32_t above = ctrl[0], nc = ctrl[1], b1 = ctrl[2];
   const uint32_t need = (uint32_t)m - above;  // >= 1 and <= nc
-  const uint32_t* cg = a.cand + (int64_t)unit * a.max_ctx;
-  const float* srow = a.scores + (int64_t)unit * a.max_ctx;
-  const bool in_lds = nc <= (uint32_t)kCandLds;
-  if (in_lds) {
-    for (uint32_t i = tid; i < nc; i += kFinishThreads) {
-      const uint32_t p = cg[i];
-      area[i] = make_uint2(order_key(srow[p]), p);
-    }
-  }
-  const ListCands cs{in_lds ? area : nullptr, cg, srow};
-  uint32_t pmax;
-  const uint32_t T = refine_threshold(cs, nc, need, b1, hist, tmp, misc, &pmax);
-
-  // Append the chosen candidates after the positions selected by the filter.
-  if (tid == 0) misc[4] = above;
-  __syncthreads();
-  int32_t* sel = a.sel + (int64_t)unit * a.k;
-  for (uint32_t i0 = 0; i0 < nc; i0 += kFinishThreads) {
-    const uint32_t i = i0 + tid;
-    bool take = false;
-    uint2 c = make_uint2(0u, 0u);
-    if (i < nc) {
-      cs.get(i, &c);
-      take = c.x > T || (c.x == T && c.y <= pmax);
-    }
-    const uint32_t slot = wave_append(take, &misc[4]);
-    if (take) sel[slot] = (int32_t)c.y;
-  }
-  __syncthreads();
-
-  // Mark the m chosen positions in a bitmap and emit them in ascending order.
+  const int64_t row = (int64_t)unit * a.max_ctx;
+  const ListCands list{reinterpret_cast<const uint2*>(a.cand) + row,
+                       a.cand_keys ? nullptr : a.cand + row, a.scores + row, nc};
   const int words = (n + 31) >> 5;
-  uint32_t* bm = n <= kBitmapLdsBits ? reinterpret_cast<uint32_t*>(area)
-                                     : a.bitmap + (int64_t)unit * a.bm_words;
-  for (int w = tid; w < words; w += kFinishThreads) bm[w] = 0u;
-  __syncthreads();
-  for (int i = tid; i < m; i += kFinishThreads) {
-    const int p = sel[i];
-    atomicOr(&bm[p >> 5], 1u << (p & 31));
+  uint32_t* bm = n <= kBitmapLdsBits ? lds_bm : a.bitmap + (int64_t)unit * a.bm_words;
+  auto mark = [&](uint32_t p) { atomicOr(&bm[p >> 5], 1u << (p & 31)); };
+  auto choose = [&](const auto& cs) {
+    for (int w = tid; w < words; w += kFinishThreads) bm[w] = 0u;
+    __syncthreads();
+    // the positions that the filter selected outright
+    const int32_t* sel = a.sel + (int64_t)unit * a.k;
+    for (uint32_t i = tid; i < above; i += kFinishThreads) mark((uint32_t)sel[i]);
+    uint32_t pmax;
+    const uint32_t T =
+        refine_threshold<kFinishThreads>(cs, need, b1, hist, tmp, misc, &pmax);
+    cs.each([&](uint32_t key, uint32_t pos) {
+      if (key > T || (key == T && pos <= pmax)) mark(pos);
+    });
+  };
+  if (nc - 1u < (uint32_t)(kRegCands * kFinishThreads)) {  // 1 .. that many
+    RegCands cs;
+    cs.load(list);
+    choose(cs);
+  } else {
+    choose(list);
   }
   __syncthreads();
   emit_bitmap(bm, words, idx, (uint32_t)a.k, tmp);
@@ -400,31 +420,37 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 // When there are more than CAP of them (heavy ties) the list is not used:
 // every position is looked at again (RescanCands), which needs no memory and
 // costs a pass over the unit's scores (256 KiB at most) per digit.
-template <int CAP = kCandLds>
+template <int NT, int CAP>
 struct LdsCands {
   uint2* lds;
+  uint32_t nc;
   __device__ __forceinline__ void put(uint32_t i, uint2 v) const {
     if (i < (uint32_t)CAP) lds[i] = v;
   }
-  __device__ __forceinline__ bool get(uint32_t i, uint2* c) const {
-    const uint2 v = lds[i];
-    *c = make_uint2(order_key(__uint_as_float(v.x)), v.y);
-    return true;
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+    for (uint32_t i = threadIdx.x; i < nc; i += NT) {
+      const uint2 v = lds[i];
+      f(order_key(__uint_as_float(v.x)), v.y);
+    }
   }
 };
 
-template <bool COH>
+template <int NT, bool COH>
 struct RescanCands {
   const float* srow;
-  uint32_t b1;
-  __device__ __forceinline__ bool get(uint32_t i, uint2* c) const {
-    float x;
-    if constexpr (COH)
-      x = __hip_atomic_load(srow + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-      x = srow[i];
-    *c = make_uint2(order_key(x), i);
-    return c->x >> (32 - kHistBits) == b1 && x == x;
+  uint32_t n, b1;
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+    for (uint32_t i = threadIdx.x; i < n; i += NT) {
+      float x;
+      if constexpr (COH)
+        x = __hip_atomic_load(srow + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        x = srow[i];
+      const uint32_t key = order_key(x);
+      if (key >> (32 - kHistBits) == b1 && x == x) f(key, i);
+    }
   }
 };
 
@@ -435,7 +461,7 @@ struct RescanCands {
 // per wave).  Positions at or past n_b must hold NaN (then neither holds).
 template <int NT = kFinishThreads, int CAP = kCandLds>
 __device__ __forceinline__ void classify_batch(const float (&sv)[kSelPer], int j0, float g_lo,
-                                               float g_hi, uint32_t* bm, const LdsCands<CAP>& cs,
+                                               float g_hi, uint32_t* bm, const LdsCands<NT, CAP>& cs,
                                                uint32_t* ctr) {
   static_assert(2 * kSelPer == 64, "one bitmap word per lane and batch");
   const int tid = threadIdx.x, lane = tid & 63;
@@ -618,7 +644,7 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   lds_barrier();
   if (tid < 64) find_first_bin_lds(lhist, (uint32_t)m, misc + 4);
   lds_barrier();
-  const LdsCands<CAP> cs{cand};
+  LdsCands<NT, CAP> cs{cand, 0u};
   const uint32_t b1 = misc[4], above = misc[5];
   const float g_lo = __uint_as_float(key_floor_bits((uint64_t)b1 << (32 - kHistBits)));
   const float g_hi = __uint_as_float(key_floor_bits((uint64_t)(b1 + 1u) << (32 - kHistBits)));
@@ -642,20 +668,18 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   __syncthreads();
   const uint32_t nc = misc[7];
   const uint32_t need = (uint32_t)m - above;
-  auto resolve = [&](const auto& cands, uint32_t count) {
+  auto resolve = [&](const auto& cands) {
     uint32_t pmax;
-    const uint32_t T = refine_threshold<std::remove_cv_t<std::remove_reference_t<decltype(cands)>>, NT>(
-        cands, count, need, b1, lhist, tmp, misc, &pmax);
-    for (uint32_t i = tid; i < count; i += NT) {
-      uint2 c;
-      if (cands.get(i, &c) && (c.x > T || (c.x == T && c.y <= pmax)))
-        atomicOr(&bm[c.y >> 5], 1u << (c.y & 31));
-    }
+    const uint32_t T = refine_threshold<NT>(cands, need, b1, lhist, tmp, misc, &pmax);
+    cands.each([&](uint32_t key, uint32_t pos) {
+      if (key > T || (key == T && pos <= pmax)) atomicOr(&bm[pos >> 5], 1u << (pos & 31));
+    });
   };
+  cs.nc = nc;
   if (nc <= (uint32_t)CAP)
-    resolve(cs, nc);
+    resolve(cs);
   else
-    resolve(RescanCands<COH>{srow, b1}, (uint32_t)n);
+    resolve(RescanCands<NT, COH>{srow, (uint32_t)n, b1});
   __syncthreads();
   // m positions for scores as specified (fewer only with NaN scores)
   const int got = (int)min(emit_bitmap<NT>(bm, (n + 31) >> 5, write ? idx : nullptr,
@@ -674,7 +698,7 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
 __global__ __launch_bounds__(kFinishThreads) void k_select_fused(SelectArgs a) {
   __shared__ uint2 cand[kCandLds];
   __shared__ uint32_t bm[kFusedSelectMaxCtx / 32];
-  __shared__ uint32_t lhist[2048];
+  __shared__ __attribute__((aligned(16))) uint32_t lhist[2048];
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
   __shared__ uint32_t misc[8];
   const int unit = blockIdx.x;
@@ -692,7 +716,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_fused(SelectArgs a) {
 __global__ __launch_bounds__(kFinishThreads) void k_select_pair(SelectArgs s1, SelectArgs s2) {
   __shared__ uint2 cand[kCandLds];
   __shared__ uint32_t bm[kFusedSelectMaxCtx / 32];
-  __shared__ uint32_t lhist[2048];
+  __shared__ __attribute__((aligned(16))) uint32_t lhist[2048];
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
   __shared__ uint32_t misc[8];
   const bool second = (int)blockIdx.x >= s1.units;
@@ -1049,9 +1073,11 @@ __global__ __launch_bounds__(kAttnThreads) void k_attn(AttnArgs a) {
 template <int G, bool CLAIMS>
 __device__ __forceinline__ void score_role(const ScoreArgs& a, int wg, int nwg, uint32_t* lds_hist,
                                            uint32_t* lds_stage, uint32_t* lds_claim) {
-  if constexpr (CLAIMS)
+  if constexpr (CLAIMS) {
+    score_range<G, true, 4, true, false, false, true>(a, wg, nwg, lds_hist, lds_stage);
+    __syncthreads();
     score_claims<G>(a, nwg, lds_hist, lds_stage, lds_claim);
-  else
+  } else
     score_range<G, true, 4, true>(a, wg, nwg, lds_hist, lds_stage);
 }
 
@@ -1712,7 +1738,7 @@ hipError_t launch_score(const ScoreArgs& a, int G, bool hist, int nwg, hipStream
 }
 
 hipError_t launch_hist(const SelectArgs& a, int units, hipStream_t s) {
-  launch_kernel(CKV_K_HIST, k_hist, dim3(units * a.tiles), dim3(kScoreThreads), s, a);
+  launch_kernel(CKV_K_HIST, k_hist, dim3(units * a.tiles), dim3(kFilterThreads), s, a);
   return launch_status();
 }
 

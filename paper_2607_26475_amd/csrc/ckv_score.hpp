@@ -222,7 +222,8 @@ __device__ __forceinline__ void fill_tails(const ScoreArgs& a, int wg, int nwg) 
 // TWO: the pass scores two queries (a.q and a.q2) against each key it reads,
 // into two score arrays and two histograms (lds_hist holds both); a wave's
 // score buffer is shared by the two, so it is flushed twice as often.
-template <int G, bool HIST, int NW = 4, bool HALVES = false, bool FUSED = false, bool TWO = false>
+template <int G, bool HIST, int NW = 4, bool HALVES = false, bool FUSED = false, bool TWO = false,
+          bool PART = false>
 __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
                                             uint32_t* lds_hist,
                                             uint32_t* lds_stage, FusedSync fs = FusedSync{}) {
@@ -243,7 +244,8 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
   const int items = FUSED ? (a.units >> 3) : a.units / a.Hkv;
   const uint32_t mult = FUSED ? 1u : (uint32_t)a.Hkv;
   auto len = [&](int i) {
-    return unit_len(a.ctx_lens[FUSED ? (8 * i + xcd) / a.Hkv : i], a.max_ctx, a.chunk);
+    const int n = unit_len(a.ctx_lens[FUSED ? (8 * i + xcd) / a.Hkv : i], a.max_ctx, a.chunk);
+    return PART ? static_rows(n) : n;
   };
   GroupScan first_items;
   const uint32_t total = mult * sum_groups(items, len, &first_items);
@@ -412,13 +414,20 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
   }
 }
 
-// The same pass with dynamic work distribution, for the added histograms
-// of the pipelined attend-and-score launch (a.claim set, a.hist_part null).
-// The groups of each unit are cut into claims of kClaimGroups; workgroups
-// take claims in increasing order from the counter a.claim, so a workgroup
-// on a CU slowed by other work (the zero-copy gather running beside the
-// pass) takes fewer of them and the pass is not held up by its slowest CUs.
-// Within a claim the four waves take its groups round-robin as above.
+// The dynamic part of that pass, for the added histograms of the pipelined
+// attend-and-score launch (a.claim set, a.hist_part null).  The first
+// kStaticEighths / 8 of each unit were scored as ranges (score_range, PART); the
+// valid groups after them are cut into claims of kClaimGroups.
+// Workgroups take claims in increasing order from the counter a.claim, so a
+// workgroup on a CU slowed by other work (the zero-copy gather running beside
+// the pass) takes fewer of them and the pass is not held up by its slowest
+// CUs.  A claim costs a workgroup about 8 us whatever its size: all workgroups
+// ask the one counter at about the same time, and their device-scope atomics
+// queue.  So half the work needs no claim, and claims are large.  A million
+// positions of 8 units: all claims 414 us, all static 352, half and half 357
+// (claims of 32 groups 431, three quarters static 357); beside the gather of
+// the million-token loop, per layer with the same selection: 662, -, 650 us
+// (three quarters static 690).
 //
 // Thread 0 takes claims two ahead of the one being scored, at the start of
 // each claim, and passes them through a two-entry LDS ring (one barrier per
@@ -447,32 +456,38 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
   constexpr int kLoads = kStageRows / 4;
   constexpr int kPerWave = kClaimGroups / 4;       // a wave's groups of one claim
   constexpr int kRecs = kFlushGroups / kPerWave;   // claims per score flush
+  constexpr int kClaimRows = kClaimGroups * kStageRows;
   static_assert(kClaimGroups % 4 == 0 && kFlushGroups % kPerWave == 0, "claim layout");
-  const int gpu_groups = (a.max_ctx + kStageRows - 1) / kStageRows;  // per unit
-  const int cpu = (gpu_groups + kClaimGroups - 1) / kClaimGroups;     // claims per unit
-  const uint32_t total = (uint32_t)a.units * (uint32_t)cpu;
+  const int items = a.units / a.Hkv;
+  const uint32_t mult = (uint32_t)a.Hkv;
+  auto full = [&](int i) { return unit_len(a.ctx_lens[i], a.max_ctx, a.chunk); };
+  auto len = [&](int i) {
+    const int n = full(i);
+    return n - static_rows(n);
+  };
+  GroupScan first_items;
+  const uint32_t total = mult * sum_groups<kClaimRows>(items, len, &first_items);
   uint32_t* stage = lds_stage + wave * kStageDwords;
   float* sbuf = reinterpret_cast<float*>(lds_stage + 4 * kStageDwords) +
                 wave * kFlushGroups * kStageRows;
 
-  // thread 0: a new claim; the one that makes the counter reach total + nwg
-  // is the last of the launch and resets it
-  auto take = [&]() -> uint32_t {
-    const uint32_t c = atomicAdd(a.claim, 1u);
+  // thread 0: the claim that makes the counter reach total + nwg is the last
+  // of the launch, and whoever holds it resets the counter
+  auto last_resets = [&](uint32_t c) {
     if (c == total + (uint32_t)nwg - 1u) atomicExch(a.claim, 0u);
-    return c;
   };
-  // a claim's unit, valid length, and groups [g0, g1) of which [g0, v1) lie below n_b
+  // a claim's unit, valid length, and groups [g0, v1)
   struct Geo {
-    int unit, n, g0, g1, v1;
+    int unit, n, g0, v1;
   };
   auto geo = [&](uint32_t c) {
+    const GroupItem it = find_item<kClaimRows>(items, len, first_items, mult, c);
+    const uint32_t h = (c - it.base) / it.vg;
     Geo r;
-    r.unit = (int)(c / (uint32_t)cpu);
-    r.g0 = (int)(c - (uint32_t)r.unit * (uint32_t)cpu) * kClaimGroups;
-    r.g1 = min(r.g0 + kClaimGroups, gpu_groups);
-    r.n = unit_len(a.ctx_lens[r.unit / a.Hkv], a.max_ctx, a.chunk);
-    r.v1 = max(r.g0, min(r.g1, (r.n + kStageRows - 1) / kStageRows));
+    r.unit = it.item * a.Hkv + (int)h;
+    r.n = full(it.item);
+    r.g0 = (r.n - it.n) / kStageRows + (int)(c - it.base - h * it.vg) * kClaimGroups;
+    r.v1 = min(r.g0 + kClaimGroups, (int)groups_of(r.n));
     return r;
   };
   auto load_group = [&](const Geo& c, int g, uint4* v) {
@@ -520,9 +535,11 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
   };
 
   if (tid == 0) {  // claims 0 and 1
-    const uint32_t c0 = take();
+    const uint32_t c0 = atomicAdd(a.claim, 1u);
+    const uint32_t c1 = c0 < total ? atomicAdd(a.claim, 1u) : c0;
+    last_resets(max(c0, c1));  // claims increase
     lds_claim[0] = c0;
-    lds_claim[1] = c0 < total ? take() : c0;
+    lds_claim[1] = c1;
   }
   __syncthreads();
   uint32_t cur = lds_claim[0], nxt = lds_claim[1];
@@ -534,7 +551,8 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
   for (int i = 0; cur < total; ++i) {  // cur is uniform over the workgroup
     const Geo c = geo(cur);
     uint32_t ahead = 0;  // claim i + 2 (none once a claim has failed)
-    if (tid == 0) ahead = nxt < total ? take() : nxt;
+    const bool takes = tid == 0 && nxt < total;
+    if (takes) ahead = atomicAdd(a.claim, 1u);
     if (c.unit != cur_unit) {
       if (cur_unit >= 0) {
         __syncthreads();
@@ -546,12 +564,6 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
       __syncthreads();
       load_query<G>(a, c.unit, qa);
       cur_unit = c.unit;
-    }
-    // groups of the claim at or past n_b hold -inf only
-    for (int g = c.v1; g < c.g1; ++g) {
-      const int j = g * kStageRows + (tid & (kStageRows - 1));
-      if (tid < kStageRows && j < a.max_ctx)
-        a.scores[(int64_t)c.unit * a.max_ctx + j] = -INFINITY;
     }
     const int w0 = c.g0 + wave;
     if (!have && w0 < c.v1) load_group(c, w0, cbuf);
@@ -594,7 +606,10 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
         }
       if (++nrec == kRecs) flush();
     }
-    if (tid == 0) lds_claim[i & 1] = ahead;
+    if (tid == 0) {
+      if (takes) last_resets(ahead);
+      lds_claim[i & 1] = takes ? ahead : nxt;
+    }
     __syncthreads();  // publishes claim i + 2
     cur = nxt;
     nxt = lds_claim[i & 1];

@@ -43,13 +43,15 @@ __device__ __forceinline__ void find_first_bin(const uint32_t* coarse,
   }
 }
 
-// Wave 0: lane l holds the count c of coarse range cb = 63 - l, whose 32 fine
-// bins are at stage[cb*32 ..]; finds the bin holding the m-th largest key by
-// two wave scans (ranges, then the chosen range's bins, both descending).
-// out[0] = bin, out[1] = keys in higher bins, out[2] = keys in the bin.
+// Wave 0: lane l holds the count c of coarse range cb = 63 - l, whose NB / 64
+// fine bins are at stage[cb * NB / 64 ..]; finds the bin holding the m-th
+// largest key by two wave scans (ranges, then the chosen range's bins, both
+// descending).  out[0] = bin, out[1] = keys in higher bins, out[2] = keys in
+// the bin.
+template <int NB = kHistBins>
 __device__ __forceinline__ void walk_first_bin(const uint32_t* stage, uint32_t c, uint32_t m,
                                                uint32_t* out) {
-  constexpr int kFine = kHistBins / 64;
+  constexpr int kFine = NB / 64;
   static_assert(kFine <= 64, "one lane per fine bin");
   const int lane = threadIdx.x & 63;
   const uint32_t s = wave_incl_scan(c);
@@ -115,12 +117,14 @@ __device__ __forceinline__ void store_hist_sum(const uint2 (&v)[kMaxPartials][kH
   }
 }
 
-// Wave 0 only: the bin holding the m-th largest key, from the histogram in
-// LDS (lhist).  out[0] = bin, out[1] = keys in higher bins, out[2] = keys in
-// the bin.
+// Wave 0 only: the bin holding the m-th largest key, from the histogram of
+// NB bins in LDS (lhist).  out[0] = bin, out[1] = keys in higher bins, out[2] =
+// keys in the bin.  One wave and one barrier after it: a workgroup-wide scan
+// takes four.
+template <int NB = kHistBins>
 __device__ __forceinline__ void find_first_bin_lds(const uint32_t* lhist, uint32_t m,
                                                    uint32_t* out) {
-  constexpr int kFine = kHistBins / 64;
+  constexpr int kFine = NB / 64;
   const int cb = 63 - (threadIdx.x & 63);
   uint32_t c = 0u;
 #pragma unroll
@@ -128,44 +132,28 @@ __device__ __forceinline__ void find_first_bin_lds(const uint32_t* lhist, uint32
     const uint4 v = reinterpret_cast<const uint4*>(lhist + cb * kFine)[i];
     c += v.x + v.y + v.z + v.w;
   }
-  walk_first_bin(lhist, c, m, out);
+  walk_first_bin<NB>(lhist, c, m, out);
 }
 
-// All threads of an NT-thread workgroup: given a histogram of nb bins in
-// LDS (nb a multiple of NT or at most NT), find the
-// bin where the running count (from the top bin down when DESC, else from
-// bin 0 up) first reaches `need`.  Returns the bin and sets *rest to the
-// number still needed inside that bin.
-template <bool DESC, int NT = kFinishThreads>
-__device__ __forceinline__ uint32_t find_bin_block(const uint32_t* hist, int nb,
-                                                   uint32_t need, uint32_t* tmp,
-                                                   uint32_t* misc,
+// All threads of an NT-thread workgroup: given a histogram of nb <= NT bins in
+// LDS, find the bin where the running count from bin 0 up first reaches
+// `need`.  Returns the bin and sets *rest to the number still needed inside
+// that bin.
+template <int NT = kFinishThreads>
+__device__ __forceinline__ uint32_t find_bin_block(const uint32_t* hist, int nb, uint32_t need,
+                                                   uint32_t* tmp, uint32_t* misc,
                                                    uint32_t* rest) {
   const int t = threadIdx.x;
   if (t == 0) {
     misc[0] = 0u;
     misc[1] = 0u;
   }
-  const int per = nb > NT ? nb / NT : 1;
-  // thread t owns scan positions [t*per, t*per + per)
-  auto bin_at = [&](int pos) { return DESC ? nb - 1 - pos : pos; };
-  uint32_t v = 0u;
-  if (t * per < nb)
-    for (int i = 0; i < per; ++i) v += hist[bin_at(t * per + i)];
+  const uint32_t v = t < nb ? hist[t] : 0u;
   uint32_t total;
   const uint32_t incl = block_incl_scan<NT / 64>(v, tmp, &total);
-  if (t * per < nb && incl >= need && incl - v < need) {
-    uint32_t run = incl - v;
-    for (int i = 0; i < per; ++i) {
-      const int bin = bin_at(t * per + i);
-      const uint32_t c = hist[bin];
-      if (run + c >= need) {
-        misc[0] = (uint32_t)bin;
-        misc[1] = need - run;
-        break;
-      }
-      run += c;
-    }
+  if (t < nb && incl >= need && incl - v < need) {
+    misc[0] = (uint32_t)t;
+    misc[1] = need - (incl - v);
   }
   __syncthreads();
   const uint32_t b = misc[0];

@@ -37,6 +37,10 @@ CASES = [  # name, B, Hkv, G, stored rows, k, queries, next set in the predictio
     ("long_in_place", 1, 2, 4, 70001, 500, 2, True),
     ("long_one", 1, 2, 4, 70001, 500, 1, False),
     ("ties", 1, 2, 4, 40000, 700, 2, False),
+    # more candidates than the many-workgroup selection keeps in registers, its
+    # list with positions only and with keys
+    ("ties_long", 1, 2, 4, 70001, 500, 2, False),
+    ("ties_long_one", 1, 2, 4, 70001, 500, 1, False),
 ]
 
 
@@ -50,7 +54,7 @@ def test_two_queries(name, B, Hkv, G, n, k, queries, in_place):
     t = synth.make_layer(w, seed=51, device=dev)
     if B >= 3:
         t["ctx_lens"][0], t["ctx_lens"][1], t["ctx_lens"][2] = 0, k - 1, n
-    if name == "ties":  # almost every score equal
+    if name.startswith("ties"):  # almost every score equal
         t["k"][:, :, 100:] = t["k"][:, :, 100:101].clone()
     lens = t["ctx_lens"].cpu().numpy()
     q, K, V = u16(t["q"]), u16(t["k"]), u16(t["v"])
