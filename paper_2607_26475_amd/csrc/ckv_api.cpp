@@ -338,7 +338,7 @@ ReconArgs recon_args(const Dims& d, int32_t rank, const uint16_t* u_fac, const u
   r.n_sel = n_sel;
   r.slots = slots;
   r.k_dst = k_dst;
-  r.items = (int64_t)d.U * k * 16;
+  r.tiles = (int64_t)d.U * ((k + kRecRows - 1) / kRecRows);
   r.max_ctx = d.max_ctx;
   r.k = k;
   r.rank = rank;
@@ -767,6 +767,7 @@ int ckv::gather_kv_width(const ckv_shape* shape, const uint16_t* k_src, const ui
   a.items = (int64_t)d.U * k * 32;
   a.max_ctx = d.max_ctx;
   a.k = k;
+  a.units = d.U;
   CKV_TRY_HIP(launch_gather(a, workgroups ? workgroups : gather_blocks(src_kind),
                             (hipStream_t)stream),
               "gather launch");
@@ -1384,9 +1385,10 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   g.k_dst = rank > 0 ? nullptr : k_buf;
   g.v_dst = v_buf;
   g.row_stride = d.kv_stride;
-  g.items = (int64_t)d.U * k * 32;
+  g.items = (int64_t)d.U * k * (rank > 0 ? 16 : 32);
   g.max_ctx = d.max_ctx;
   g.k = k;
+  g.units = d.U;
   if (rank > 0) {
     ReconArgs r = recon_args(d, rank, u_fac, w_fac, m.miss_pos, m.n_miss, m.miss_slot, k,
                              k_buf);

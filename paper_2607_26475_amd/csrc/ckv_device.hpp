@@ -69,6 +69,12 @@ constexpr int kSelAttnMaxSplit = 8;
 constexpr int kGatherThreads = 256;
 constexpr int kGatherUnroll = 4;
 
+// Key reconstruction: a workgroup rebuilds kRecRows rows, kRecRanks ranks of
+// the factors staged at a time.
+constexpr int kRecRows = 32;
+constexpr int kRecRanks = 64;
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -184,8 +190,8 @@ struct GatherArgs {
   uint16_t* k_dst;
   uint16_t* v_dst;
   int64_t row_stride;
-  int64_t items;            // U * k * 32
-  int max_ctx, k;
+  int64_t items;            // U * k * 32 (16 without k_dst)
+  int max_ctx, k, units;
 };
 
 // Chunk landmarks: the mean key of every chunk of `chunk` rows.
@@ -206,7 +212,7 @@ struct ReconArgs {
   const int32_t* n_sel;     // [U]
   const int32_t* slots;     // [U][k] destination slot of entry i; NULL: slot i
   uint16_t* k_dst;          // [U][k][d]
-  int64_t items;            // U * k * 16
+  int64_t tiles;            // U * ceil(k / kRecRows)
   int max_ctx, k, rank;
 };
 
@@ -292,6 +298,10 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
 
 __device__ __forceinline__ f32x4 mfma_16x16x32(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f64x4 mfma_f64_16x16x4(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // Exact widening of the 8 bf16 values packed in v (lowest element first).

@@ -1374,42 +1374,120 @@ __global__ __launch_bounds__(kGatherThreads) void k_expand(ExpandArgs a) {
 }
 
 // ---- low-rank key reconstruction -------------------------------------------------
-// One item = 8 channels of one rebuilt key: the fp64 sum over the rank in
-// ascending order (bf16 products are exact in fp64), rounded once to bf16.
-__device__ __forceinline__ void reconstruct_range(const ReconArgs& a, int blk, int nblk) {
-  const int64_t stride = (int64_t)nblk * kGatherThreads;
-  for (int64_t it = (int64_t)blk * kGatherThreads + threadIdx.x; it < a.items;
-       it += stride) {
-    const int part = (int)(it & 15);
-    const int64_t slot = it >> 4;
-    const int64_t unit = slot / a.k;
-    const int i = (int)(slot - unit * a.k);
-    if (i >= clamp_len(a.n_sel[unit], a.k)) continue;
-    const int row = a.idx[slot];
-    const int di = a.slots ? a.slots[slot] : i;
-    if (row < 0 || row >= a.max_ctx || di < 0 || di >= a.k) continue;
-    const uint16_t* u = a.u_fac + (unit * a.max_ctx + row) * a.rank;
-    const uint16_t* w = a.w_fac + unit * a.rank * kD + 8 * part;
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int j = 0; j < a.rank; ++j) {
-      const double uj = (double)__uint_as_float((uint32_t)u[j] << 16);
-      float wf[8];
-      unpack8(ld16(w + (int64_t)j * kD), wf);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += uj * (double)wf[e];
+// A workgroup rebuilds tiles of kRecRows rows of one unit: U rows [32 x rank]
+// times W [rank x 128] on the fp64 matrix cores.  A 16x16x4 product adds its
+// four products to the accumulator one after the other in ascending j, each sum
+// rounded (bf16 products are exact in fp64), so the result is the ordered fp64
+// sum bit for bit, then rounded once to bf16.  Each of the four waves takes 32
+// channels for all 32 rows, so a converted factor entry serves two products.
+// The factors are staged kRecRanks ranks at a time, the next ranks' loads in
+// flight during the products; padding ranks are zero in both.  Bound by
+// the loads' latency for a few hundred misses per unit and by the matrix rate
+// (256 flops per CU and clock) for whole sets.  One thread per 8 channels, whose
+// rows each read all of W through the cache, took 49 us for 16 units of about
+// 300 misses at rank 64.
+struct RecLds {
+  // row strides chosen for the operand reads: 288 bytes put the four ranks of a
+  // step on different banks, 144 bytes the sixteen rows
+  uint16_t w[kRecRanks][kD + 16];
+  uint16_t u[kRecRows][kRecRanks + 8];
+  int32_t row[kRecRows], slot[kRecRows];
+};
+
+__device__ __forceinline__ void reconstruct_range(const ReconArgs& a, int blk, int nblk,
+                                                  RecLds& L) {
+  static_assert(kGatherThreads == 256 && kRecRows == 32 && kRecRanks == 64 && kD == 128,
+                "four waves of 32 channels, one 16-byte chunk of U per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int per_unit = (a.k + kRecRows - 1) / kRecRows;
+  const bool aligned = (a.rank & 7) == 0;  // U rows start on 16 bytes
+  auto bf = [](uint16_t x) { return (double)__uint_as_float((uint32_t)x << 16); };
+  for (int64_t tile = blk; tile < a.tiles; tile += nblk) {
+    const int64_t unit = tile / per_unit;
+    const int i0 = (int)(tile - unit * per_unit) * kRecRows;
+    const int n = clamp_len(a.n_sel[unit], a.k);
+    if (i0 >= n) continue;  // uniform over the workgroup
+    __syncthreads();        // the tile before is done with the LDS
+    if (tid < kRecRows) {
+      int row = -1, di = -1;
+      if (i0 + tid < n) {
+        const int64_t e = unit * a.k + i0 + tid;
+        row = a.idx[e];
+        di = a.slots ? a.slots[e] : i0 + tid;
+      }
+      const bool ok = row >= 0 && row < a.max_ctx && di >= 0 && di < a.k;
+      L.row[tid] = ok ? row : 0;
+      L.slot[tid] = ok ? di : -1;
     }
-    uint32_t o[4];
+    __syncthreads();
+    const uint16_t* wsrc = a.w_fac + unit * a.rank * kD;
+    const uint16_t* usrc = a.u_fac + (unit * a.max_ctx + L.row[tid >> 3]) * a.rank;
+    uint4 wv[4], uv;
+    auto fetch = [&](int j0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      o[e] = (uint32_t)f64_to_bf16_rne(acc[2 * e]) |
-             ((uint32_t)f64_to_bf16_rne(acc[2 * e + 1]) << 16);
-    *reinterpret_cast<uint4*>(a.k_dst + (unit * a.k + di) * kD + 8 * part) =
-        make_uint4(o[0], o[1], o[2], o[3]);
+      for (int q = 0; q < 4; ++q) {
+        const int e = tid + q * kGatherThreads, j = j0 + (e >> 4);
+        wv[q] = make_uint4(0u, 0u, 0u, 0u);
+        if (j < a.rank) wv[q] = ld16(wsrc + (int64_t)j * kD + 8 * (e & 15));
+      }
+      const int j = j0 + 8 * (tid & 7);
+      uv = make_uint4(0u, 0u, 0u, 0u);
+      if (aligned) {
+        if (j < a.rank) uv = ld16(usrc + j);
+      } else {
+        uint32_t x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = j + q < a.rank ? usrc[j + q] : 0u;
+        uv = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16),
+                        x[6] | (x[7] << 16));
+      }
+    };
+    f64x4 acc[2][2];  // [16 rows][16 channels]: row 4 * i + kq, channel r16
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[x >> 1][x & 1] = f64x4{0., 0., 0., 0.};
+    fetch(0);
+    for (int j0 = 0; j0 < a.rank; j0 += kRecRanks) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = tid + q * kGatherThreads;
+        *reinterpret_cast<uint4*>(&L.w[e >> 4][8 * (e & 15)]) = wv[q];
+      }
+      *reinterpret_cast<uint4*>(&L.u[tid >> 3][8 * (tid & 7)]) = uv;
+      __syncthreads();
+      if (j0 + kRecRanks < a.rank) fetch(j0 + kRecRanks);
+      const int steps = min(kRecRanks, a.rank - j0);
+      for (int t0 = 0; t0 < steps; t0 += 16) {  // ranks past `steps` are staged as zeros
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int j = t0 + 4 * q + kq;
+          const double u0 = bf(L.u[r16][j]), u1 = bf(L.u[16 + r16][j]);
+          const double w0 = bf(L.w[j][32 * wave + r16]);
+          const double w1 = bf(L.w[j][32 * wave + 16 + r16]);
+          acc[0][0] = mfma_f64_16x16x4(u0, w0, acc[0][0]);
+          acc[0][1] = mfma_f64_16x16x4(u0, w1, acc[0][1]);
+          acc[1][0] = mfma_f64_16x16x4(u1, w0, acc[1][0]);
+          acc[1][1] = mfma_f64_16x16x4(u1, w1, acc[1][1]);
+        }
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int di = L.slot[16 * x + 4 * i + kq];
+        if (di < 0) continue;
+        uint16_t* dst = a.k_dst + (unit * a.k + di) * kD + 32 * wave + r16;
+        dst[0] = f64_to_bf16_rne(acc[x][0][i]);
+        dst[16] = f64_to_bf16_rne(acc[x][1][i]);
+      }
   }
 }
 
 __global__ __launch_bounds__(kGatherThreads) void k_reconstruct(ReconArgs a) {
-  reconstruct_range(a, blockIdx.x, gridDim.x);
+  __shared__ __attribute__((aligned(16))) RecLds lds;
+  reconstruct_range(a, blockIdx.x, gridDim.x, lds);
 }
 
 // ---- miss detection -----------------------------------------------------------
@@ -1502,12 +1580,18 @@ __global__ __launch_bounds__(kMissThreads) void k_miss(MissArgs a) {
 }
 
 // ---- gather ----------------------------------------------------------------
-// Item it = ((unit*k + slot)*2 + kv)*16 + part moves 16 bytes; the 32 items of
-// one slot are its K row then its V row (contiguous for K|V interleaved rows).
-// With a slot list, entry slot of the unit lands in slot slots[unit][slot].
-// K items are skipped when k_dst is NULL.
-__device__ __forceinline__ void gather_range(const GatherArgs& a, int blk, int nblk) {
+// An item moves 16 bytes; the 32 items of one row are its K row then its V row
+// (contiguous for K|V interleaved rows), or 16 items without k_dst (values
+// only).  Whole sets are walked unit by unit.  With a slot list (misses: a few
+// hundred of a unit's k entries, entry i landing in slot slots[unit][i]) the
+// entries i of all units come before any entry i + 1, so that the first items
+// hold all the work and a single pass of the grid has every row in flight.
+// Walked unit by unit, 16 units of about 300 missing values over the host link
+// took 36 us, four passes of mostly empty items.
+template <bool LIST>
+__device__ __forceinline__ void gather_items(const GatherArgs& a, int blk, int nblk) {
   const int64_t step = (int64_t)nblk * kGatherThreads * kGatherUnroll;
+  const int row_bits = a.k_dst ? 5 : 4;
   for (int64_t it0 = (int64_t)blk * kGatherThreads * kGatherUnroll; it0 < a.items;
        it0 += step) {
     uint4 v[kGatherUnroll];
@@ -1518,18 +1602,19 @@ __device__ __forceinline__ void gather_range(const GatherArgs& a, int blk, int n
       dst[u] = nullptr;
       if (it < a.items) {
         const int part = (int)(it & 15);
-        const int kv = (int)((it >> 4) & 1);
-        const int64_t slot = it >> 5;
-        const int64_t unit = slot / a.k;
-        const int i = (int)(slot - unit * a.k);
+        const bool key = a.k_dst && !((it >> 4) & 1);
+        const int64_t row = it >> row_bits;
+        const int64_t unit = LIST ? row % a.units : row / a.k;
+        const int i = (int)(LIST ? row / a.units : row - unit * a.k);
         if (i < a.n_sel[unit]) {
-          const int pos = a.idx[slot];
-          const int di = a.slots ? a.slots[slot] : i;
-          if (pos >= 0 && pos < a.max_ctx && di >= 0 && di < a.k && (kv || a.k_dst)) {
-            const uint16_t* src = (kv ? a.v_src : a.k_src) +
-                                  (unit * a.max_ctx + pos) * a.row_stride + part * 8;
+          const int64_t e = unit * a.k + i;
+          const int pos = a.idx[e];
+          const int di = LIST ? a.slots[e] : i;
+          if (pos >= 0 && pos < a.max_ctx && di >= 0 && di < a.k) {
+            const uint16_t* src =
+                (key ? a.k_src : a.v_src) + (unit * a.max_ctx + pos) * a.row_stride + part * 8;
             v[u] = ld16(src);
-            dst[u] = (kv ? a.v_dst : a.k_dst) + (unit * a.k + di) * kD + part * 8;
+            dst[u] = (key ? a.k_dst : a.v_dst) + (unit * a.k + di) * kD + part * 8;
           }
         }
       }
@@ -1538,6 +1623,11 @@ __device__ __forceinline__ void gather_range(const GatherArgs& a, int blk, int n
     for (int u = 0; u < kGatherUnroll; ++u)
       if (dst[u]) *reinterpret_cast<uint4*>(dst[u]) = v[u];
   }
+}
+
+__device__ __forceinline__ void gather_range(const GatherArgs& a, int blk, int nblk) {
+  if (a.slots) gather_items<true>(a, blk, nblk);
+  else gather_items<false>(a, blk, nblk);
 }
 
 __global__ __launch_bounds__(kGatherThreads) void k_gather(GatherArgs a) {
@@ -1549,10 +1639,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(GatherArgs a) {
 // transfer and the arithmetic overlap in one launch.
 __global__ __launch_bounds__(kGatherThreads) void k_miss_fill(GatherArgs g, ReconArgs r,
                                                               int nfetch) {
+  __shared__ __attribute__((aligned(16))) RecLds lds;
   if ((int)blockIdx.x < nfetch)
     gather_range(g, blockIdx.x, nfetch);
   else
-    reconstruct_range(r, blockIdx.x - nfetch, gridDim.x - nfetch);
+    reconstruct_range(r, blockIdx.x - nfetch, gridDim.x - nfetch, lds);
 }
 
 // ---- fixed scratch for callers that cannot allocate -------------------------
@@ -2034,7 +2125,7 @@ hipError_t launch_landmarks(const LandmarkArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_reconstruct(const ReconArgs& a, hipStream_t s) {
-  const int blocks = blocks_for(a.items, kGatherThreads, 8192);
+  const int blocks = blocks_for(a.tiles, 1, 8192);
   launch_kernel(CKV_K_RECONSTRUCT, k_reconstruct, dim3(blocks), dim3(kGatherThreads), s, a);
   return launch_status();
 }
@@ -2042,7 +2133,7 @@ hipError_t launch_reconstruct(const ReconArgs& a, hipStream_t s) {
 hipError_t launch_miss_fill(const GatherArgs& g, int fetch_blocks, const ReconArgs& r,
                             hipStream_t s) {
   const int nf = blocks_for(g.items, kGatherThreads * kGatherUnroll, fetch_blocks);
-  const int nr = blocks_for(r.items, kGatherThreads, 8192);
+  const int nr = blocks_for(r.tiles, 1, 8192);
   launch_kernel(CKV_K_RECONSTRUCT, k_miss_fill, dim3(nf + nr), dim3(kGatherThreads), s, g, r,
                 nf);
   return launch_status();
