@@ -466,6 +466,28 @@ void set_partials(void* ws, const Layout& L, int nwg, ScoreArgs* sc, SelectArgs*
   sa->score_nwg = nwg;
 }
 
+// Batches of up to kSelfCountUnits units and kSelfCountMaxCtx positions: the
+// selection counts the first digit itself, from the scores it holds in
+// registers anyway, and the scoring pass neither counts nor adds; nothing needs
+// clearing.  Same-step calls, added histograms against self-counted: 2 units of
+// 4096 positions 26.7 -> 18.4 us, 24 units of 16384 43.7 -> 40.9, 8 units of
+// 24001 36.1 -> 34.1; counting grows with the context (equal scores serialise
+// in LDS) and loses from 32 Ki (16 units: 55.5 -> 56.1, of 64 Ki pipelined
+// 69.7 -> 72.8).  Batches of 25 to about 36 units, too few for slots, keep the
+// cleared and added form (which the tests ask of 32 units of 6000 positions,
+// though those too would gain, 29.6 -> 25.1).
+constexpr int kSelfCountUnits = 24;
+constexpr int kSelfCountMaxCtx = 24576;
+
+bool self_counts(const Dims& d) {
+  return d.max_ctx <= kSelfCountMaxCtx && d.U <= kSelfCountUnits;
+}
+
+void set_self_count(ScoreArgs* sc, SelectArgs* sa) {
+  sc->hist = sc->coarse = sc->claim = nullptr;
+  sa->hist = nullptr;
+}
+
 int run_select_tail(const SelectArgs& a, int units, hipStream_t s) {
   if (a.max_ctx <= kFusedSelectMaxCtx) {
     CKV_TRY_HIP(launch_select_fused(a, units, s), "select launch");
@@ -553,6 +575,8 @@ int score_chunks(const Dims& d, int32_t chunk, const uint16_t* q_sel,
   const int nwg = score_blocks(sc, d.G, ScoreKind::kHist);
   if (use_partials(dc, Lc, nwg))
     set_partials(ws, Lc, nwg, &sc, sa);
+  else if (self_counts(dc))
+    set_self_count(&sc, sa);
   else
     CKV_TRY_HIP(launch_zero(ws, Lc.zero_end, s), "zero launch");
   CKV_TRY_HIP(launch_score(sc, d.G, true, nwg, s), "score launch");
@@ -702,6 +726,8 @@ int ckv::pipelined_layer(const ckv_shape* shape, const PipelinedLayer& p,
   }
   if (partials)
     set_partials(ws, Ls, nwg, &sc, &sa);
+  else if (self_counts(ds))
+    set_self_count(&sc, &sa);
   else if (!p.hist_clean)
     CKV_TRY_HIP(launch_zero(ws, Ls.zero_end, s), "zero launch");
   if (fold)
@@ -846,8 +872,15 @@ int ckv_select_topk(const ckv_shape* shape, const float* scores, const int32_t* 
   CKV_DEBUG_CHECK(stream, ctx_lens, nullptr, nullptr, k);
   hipStream_t s = (hipStream_t)stream;
   SelectArgs a = select_args(d, L, ws, scores, ctx_lens, k, idx, n_sel);
-  CKV_TRY_HIP(launch_zero(ws, L.zero_end, s), "zero launch");
-  CKV_TRY_HIP(launch_hist(a, d.U, s), "hist launch");
+  if (d.max_ctx <= kFusedSelectMaxCtx) {
+    // the selection counts the first digit of the scores it reads: 128 units of
+    // 32768 positions 269.4 -> 263.5 us for the four steps, against a clear and
+    // a histogram launch
+    a.hist = nullptr;
+  } else {
+    CKV_TRY_HIP(launch_zero(ws, L.zero_end, s), "zero launch");
+    CKV_TRY_HIP(launch_hist(a, d.U, s), "hist launch");
+  }
   return run_select_tail(a, d.U, s);
 }
 
@@ -1022,8 +1055,11 @@ int ckv::critical_impl(const ckv_shape* shape, const uint16_t* q_att, const uint
   }
   // a pipelined call whose caller knows the histograms clear (the previous
   // selection on this workspace left them so) skips the clearing kernel
+  const bool self = !partials && self_counts(d);
   if (partials)
     set_partials(ws, L, nwg, &sc, &sa);
+  else if (self)
+    set_self_count(&sc, &sa);
   else if (!(pipelined && hist_clean))
     CKV_TRY_HIP(launch_zero(ws, L.zero_end, s), "zero launch");
   if (pipelined) {
@@ -1061,7 +1097,8 @@ int ckv::critical_impl(const ckv_shape* shape, const uint16_t* q_att, const uint
       CKV_TRY_HIP(launch_critical(sc, sa, at_, fs, d.G, nwg, rows, s), "same-step launch");
       return CKV_OK;
     }
-    CKV_TRY_HIP(launch_score(sc, d.G, true, nwg, s), "score launch");
+    if (self) nwg = score_blocks(sc, d.G, ScoreKind::kPlain);
+    CKV_TRY_HIP(launch_score(sc, d.G, !self, nwg, s), "score launch");
     if (S) {
       // each workgroup selects its unit's set and attends over its share of
       // the rows, or over the whole set with its share of the heads.  Two
@@ -1352,6 +1389,9 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
       s2.score_nwg = nwg;
       s2.min_range = s1.min_range;
     }
+  } else if (self_counts(d)) {
+    set_self_count(&sc, &s1);
+    sc.hist2 = s2.hist = nullptr;
   } else if (!hist_clean) {
     CKV_TRY_HIP(launch_zero(ws, L.zero_end, s), "zero launch");
   }

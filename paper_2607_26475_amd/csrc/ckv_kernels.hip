@@ -382,27 +382,20 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
   clear_unit_hist(a, unit);
 }
 
-// Whole selection of one unit in one workgroup, for n_b <= kFusedSelectMaxCtx.
-// The unit's scores are read once, kSelPer per thread per batch of
-// kSelBatch positions, all loads of a batch in flight together.  Positions
-// above the first-digit bin go straight into an LDS bitmap (one ballot per
-// 64 positions, no atomics); positions inside the bin become candidates
-// (fp32 bits, position), whose slots are reserved with one atomic per wave.
-// The threshold inside the bin is then resolved exactly, the chosen
-// candidates marked, and the bitmap written out in ascending order.
-constexpr int kSelPer = 32;
-constexpr int kSelBatch = kSelPer * kFinishThreads;
-static_assert(kFusedSelectMaxCtx % kSelBatch == 0, "whole batches");
+// The one-workgroup selection reads a unit's scores in chunks of kSelRounds
+// positions per thread, kSelChunks of them in registers.
+constexpr int kSelRounds = 8;
+constexpr int kSelChunks = 4;
 
-template <int NT = kFinishThreads, bool COH = false>
-__device__ __forceinline__ void load_score_batch(const float* srow, int j0, int n,
-                                                 float (&sv)[kSelPer]) {
-  // unconditional loads (clamped position); 32-bit byte offsets from the
-  // row base let every load share one scalar base address
+// Scores j0 + u * NT + thread, clamped to lim - 1 (unconditional loads; 32-bit
+// byte offsets from the row base let every load share one scalar base).
+template <int NT, bool COH>
+__device__ __forceinline__ void load_score_chunk(const float* srow, int j0, int lim,
+                                                 float (&sv)[kSelRounds]) {
   const char* base = reinterpret_cast<const char*>(srow);
 #pragma unroll
-  for (int u = 0; u < kSelPer; ++u) {
-    const uint32_t off = 4u * (uint32_t)min(j0 + u * NT + (int)threadIdx.x, n - 1);
+  for (int u = 0; u < kSelRounds; ++u) {
+    const uint32_t off = 4u * (uint32_t)min(j0 + u * NT + (int)threadIdx.x, lim - 1);
     if constexpr (COH)  // stored by other workgroups of the same launch
       sv[u] = __hip_atomic_load(reinterpret_cast<const float*>(base + off), __ATOMIC_RELAXED,
                                 __HIP_MEMORY_SCOPE_AGENT);
@@ -411,26 +404,21 @@ __device__ __forceinline__ void load_score_batch(const float* srow, int j0, int 
   }
 }
 
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
-// Candidates of the one-workgroup selection: (fp32 bits, position) in LDS.
-// When there are more than CAP of them (heavy ties) the list is not used:
-// every position is looked at again (RescanCands), which needs no memory and
-// costs a pass over the unit's scores (256 KiB at most) per digit.
+// Candidates of the one-workgroup selection: (fp32 bits, position) in LDS,
+// each wave's in its own segment (no reservation; the waves' positions are
+// interleaved, so the segments fill alike).  When a wave has more than its
+// segment holds (heavy ties) the lists are not used: every position is looked
+// at again (RescanCands), which needs no memory and costs a pass over the
+// unit's scores (256 KiB at most) per digit.
 template <int NT, int CAP>
 struct LdsCands {
-  uint2* lds;
-  uint32_t nc;
-  __device__ __forceinline__ void put(uint32_t i, uint2 v) const {
-    if (i < (uint32_t)CAP) lds[i] = v;
-  }
+  static constexpr uint32_t kSeg = CAP / (NT / 64);
+  uint2* seg;      // this wave's
+  uint32_t count;  // wave-uniform
   template <class F>
   __device__ __forceinline__ void each(F f) const {
-    for (uint32_t i = threadIdx.x; i < nc; i += NT) {
-      const uint2 v = lds[i];
+    for (uint32_t i = threadIdx.x & 63; i < count; i += 64) {
+      const uint2 v = seg[i];
       f(order_key(__uint_as_float(v.x)), v.y);
     }
   }
@@ -454,57 +442,44 @@ struct RescanCands {
   }
 };
 
-// One batch of kSelBatch positions starting at j0, with two fp32 compares
+// One chunk of positions starting at j0, with two fp32 compares
 // per position: x >= g_hi <=> key(x) is above the first-digit bin b1 (set in
 // the LDS bitmap, one ballot per 64 positions), g_lo <= x < g_hi <=> key(x)
-// lies in it (a candidate (fp32 bits, position) appended at *ctr, one atomic
-// per wave).  Positions at or past n_b must hold NaN (then neither holds).
-template <int NT = kFinishThreads, int CAP = kCandLds>
-__device__ __forceinline__ void classify_batch(const float (&sv)[kSelPer], int j0, float g_lo,
-                                               float g_hi, uint32_t* bm, const LdsCands<NT, CAP>& cs,
-                                               uint32_t* ctr) {
-  static_assert(2 * kSelPer == 64, "one bitmap word per lane and batch");
-  const int tid = threadIdx.x, lane = tid & 63;
+// lies in it (a candidate (fp32 bits, position) appended to the wave's
+// segment; a full segment's last slot is overwritten, and then not used).
+// Positions at or past n_b must hold NaN (then neither holds).  The loop is
+// issue bound, 16 waves on 4 SIMDs, about 1 us per 16 Ki positions; marking
+// the bitmap with LDS atomics instead of the ballots was 1 us slower at 64 Ki.
+template <int NT, int CAP>
+__device__ __forceinline__ void classify_chunk(const float (&sv)[kSelRounds], int j0, float g_lo,
+                                               float g_hi, uint32_t* bm,
+                                               LdsCands<NT, CAP>& cs) {
+  static_assert(NT % 64 == 0, "whole waves");
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t word = 0u, wc = 0u;
+  uint32_t word = 0u;
 #pragma unroll
-  for (int u = 0; u < kSelPer; ++u) {
-    const uint64_t hi = __builtin_amdgcn_ballot_w64(sv[u] >= g_hi);
-    const uint64_t ge = __builtin_amdgcn_ballot_w64(sv[u] >= g_lo);
+  for (int u = 0; u < kSelRounds; ++u) {
+    const float x = sv[u];
+    const uint64_t hi = __builtin_amdgcn_ballot_w64(x >= g_hi);
+    const uint64_t ge = __builtin_amdgcn_ballot_w64(x >= g_lo);
     // lane 2u + h keeps word h of the wave's 64 positions.  The compare that
     // wrote `hi` is a VALU write of SGPRs, which a VALU read right after may
     // miss: the nop keeps the wait states the compiler cannot see inside asm.
     asm("s_nop 4\n\tv_writelane_b32 %0, %1, %2\n\tv_writelane_b32 %0, %3, %4"
         : "+v"(word)
         : "s"((uint32_t)hi), "n"(2 * u), "s"((uint32_t)(hi >> 32)), "n"(2 * u + 1));
-    wc += (uint32_t)__popcll(ge & ~hi);
+    const uint64_t cm = ge & ~hi;
+    const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(cm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cm, cs.count));
+    // g_lo <= g_hi, so "in the bin" is the exclusive or of the two tests
+    if ((x >= g_lo) != (x >= g_hi))
+      cs.seg[min(at, LdsCands<NT, CAP>::kSeg - 1u)] =
+          make_uint2(__float_as_uint(x), (uint32_t)(j0 + u * NT + tid));
+    cs.count += (uint32_t)__popcll(cm);
   }
-  bm[((j0 + (lane >> 1) * NT + wave * 64) >> 5) + (lane & 1)] = word;
-  uint32_t base = 0u;
-  if (lane == 0 && wc) base = atomicAdd(ctr, wc);
-  base = __builtin_amdgcn_readfirstlane(base);
-  if (base + wc <= (uint32_t)CAP) {  // the wave's candidates all fit in LDS
-#pragma unroll
-    for (int u = 0; u < kSelPer; ++u) {
-      // compare again rather than keep 2 x kSelPer lane masks live
-      float x = sv[u];
-      asm volatile("" : "+v"(x));
-      const int j = j0 + u * NT + tid;
-      // g_lo <= g_hi, so "in the bin" is the exclusive or of the two tests
-      const bool ge = x >= g_lo, hi = x >= g_hi;
-      const uint64_t cm = __builtin_amdgcn_ballot_w64(ge) & ~__builtin_amdgcn_ballot_w64(hi);
-      if (ge != hi) cs.lds[base + lanes_below(cm)] = make_uint2(__float_as_uint(x), (uint32_t)j);
-      base += (uint32_t)__popcll(cm);
-    }
-  } else {
-    for (int u = 0; u < kSelPer; ++u) {
-      const int j = j0 + u * NT + tid;
-      const bool in = sv[u] >= g_lo && !(sv[u] >= g_hi);
-      const uint64_t cm = __builtin_amdgcn_ballot_w64(in);
-      if (in) cs.put(base + lanes_below(cm), make_uint2(__float_as_uint(sv[u]), (uint32_t)j));
-      base += (uint32_t)__popcll(cm);
-    }
-  }
+  if (lane < 2 * kSelRounds) bm[((j0 + (lane >> 1) * NT + wave * 64) >> 5) + (lane & 1)] = word;
 }
 
 // Pipelined calls: merges the attention partials of the launch before the
@@ -573,56 +548,67 @@ struct SelLds {
 };
 
 // The whole selection of one unit by one workgroup of NT threads, for
-// n_b <= kFusedSelectMaxCtx.  The unit's scores are read once, kSelPer per
-// thread per batch of kSelPer * NT positions, all loads of a batch in flight
-// together.  Positions above the first-digit bin go straight into an LDS
-// bitmap (one ballot per 64 positions, no atomics); positions inside the bin
-// become candidates (fp32 bits, position), whose slots are reserved with one
-// atomic per wave.  The threshold inside the bin is then resolved exactly,
+// n_b <= kFusedSelectMaxCtx.  The unit's scores are read once, kSelChunks
+// chunks ahead of the one being classified.  Positions above the first-digit
+// bin go straight into an LDS bitmap; positions inside the bin become
+// candidates in LDS.  The threshold inside the bin is then resolved exactly,
 // the chosen candidates marked, and the bitmap written out in ascending
 // order: to idx/n_sel when `write`, and output slots [lo, hi) to share[slot -
-// lo] when share is not null.  When the first digit was counted into the
-// cleared per-unit histogram (no hist_part) and `clear` is set, the unit's
-// histogram and control words are left cleared; only the unit's one reader
-// may do that (kFinishThreads workgroups only).  Returns the number of
-// positions selected.
+// lo] when share is not null.
+//
+// The first-digit histogram is the sum of the slots of the workgroups that
+// scored the unit (a.hist_part), or the unit's added one (a.hist), or, with
+// neither, counted here from the scores in registers (a context past the first
+// kSelChunks chunks is read twice then): in four copies side by side, since
+// scores crowd in a few dozen bins and equal bins serialise.  With an added
+// histogram and `clear`, the unit's histogram and control words are left
+// cleared; only the unit's one reader may do that (kFinishThreads workgroups
+// only).  Returns the number of positions selected.
 template <int NT = kFinishThreads, int CAP = kCandLds, bool COH = false>
 __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const SelLds& L,
                                            bool write, int32_t* share, uint32_t lo,
                                            uint32_t hi, bool clear,
                                            const SlotRange* known = nullptr) {
-  static_assert(NT >= 128 && kHistBins % NT == 0 && kFusedSelectMaxCtx % (kSelPer * NT) == 0,
-                "workgroup shape");
-  constexpr int kBatch = kSelPer * NT;
+  static_assert(NT >= 128 && kHistBins % NT == 0, "workgroup shape");
+  constexpr int kChunk = kSelRounds * NT, kBatch = kSelChunks * kChunk;
+  constexpr int kCopies = 4;
+  static_assert(2 * CAP >= kCopies * kHistBins, "the histogram's copies fit in the candidates");
   const int tid = threadIdx.x;
-  uint2* const cand = L.cand;
   uint32_t* const bm = L.bm;
   uint32_t* const lhist = L.lhist;
   uint32_t* const tmp = L.tmp;
   uint32_t* const misc = L.misc;
+  const bool counts = !a.hist_part && !a.hist;  // uniform
+  const bool added = !a.hist_part && a.hist;
   // Every read the workgroup needs first is issued before anything waits:
   // the histogram, and the first batch of scores (clamped to the row, not
   // to n_b, which is not known yet; positions at or past n_b are masked).
-  // The histogram is the sum of the slots unit + wg of the workgroups that
-  // scored the unit's groups (hist_slots; a unit without positions reads one
-  // it does not use), or one slot already summed.
-  const uint32_t* slots = a.hist + (int64_t)unit * kHistBins;
-  int nslots = 1;
-  if (a.hist_part) {
-    const SlotRange r = known ? *known : hist_slots(a, unit);
-    slots = a.hist_part + r.first * kHistBins;
-    nslots = max(1, min(r.count, kMaxPartials));  // at most kMaxPartials by min_range
-  }
   const int len_b = a.ctx_lens[unit / a.Hkv];
-  uint2 hv[kMaxPartials][kHistBins / NT / 2];
-  load_hist_slots<NT, COH>(slots, nslots, hv);
-  // every wave's histogram loads queue ahead of all score loads (a bare
-  // barrier: no wait for the loads themselves)
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
   const float* srow = a.scores + (int64_t)unit * a.max_ctx;
-  float sv0[kSelPer];
-  load_score_batch<NT, COH>(srow, 0, a.max_ctx, sv0);
+  float sv[kSelChunks][kSelRounds];
+  auto load_first = [&]() {
+#pragma unroll
+    for (int c = 0; c < kSelChunks; ++c)
+      if (c * kChunk < a.max_ctx)  // uniform
+        load_score_chunk<NT, COH>(srow, c * kChunk, a.max_ctx, sv[c]);
+  };
+  int nslots = 0;
+  uint2 hv[kMaxPartials][kHistBins / NT / 2];
+  if (!counts) {
+    const uint32_t* slots = a.hist + (int64_t)unit * kHistBins;
+    nslots = 1;
+    if (a.hist_part) {  // a unit without positions reads a slot it does not use
+      const SlotRange r = known ? *known : hist_slots(a, unit);
+      slots = a.hist_part + r.first * kHistBins;
+      nslots = max(1, min(r.count, kMaxPartials));  // at most kMaxPartials by min_range
+    }
+    load_hist_slots<NT, COH>(slots, nslots, hv);
+    // every wave's histogram loads queue ahead of all score loads (a bare
+    // barrier: no wait for the loads themselves)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  load_first();
   __builtin_amdgcn_sched_barrier(0);  // n_b is waited for only here
   const int n = unit_len(len_b, a.max_ctx, a.chunk);
   const int m = min(a.k, n);
@@ -634,39 +620,73 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
     }
     if (write && tid == 0) a.n_sel[unit] = m;
     if constexpr (NT == kFinishThreads) {
-      if (clear && !a.hist_part) clear_unit_hist(a, unit);
+      if (clear && added) clear_unit_hist(a, unit);
     }
     return m;
   }
-  store_hist_sum<NT>(hv, nslots, lhist);
-  if (tid == 64) misc[7] = 0u;
+  const int words = (n + 31) >> 5;
+  if (counts) {
+    uint4* const copies = reinterpret_cast<uint4*>(L.cand);  // [bin][copy]
+    for (int i = tid; i < kHistBins; i += NT) copies[i] = make_uint4(0u, 0u, 0u, 0u);
+    lds_barrier();
+    uint32_t* const mine = reinterpret_cast<uint32_t*>(L.cand) + (tid & (kCopies - 1));
+    auto count = [&](const float (&x)[kSelRounds], int j0) {
+#pragma unroll
+      for (int u = 0; u < kSelRounds; ++u)
+        if (j0 + u * NT + tid < n)
+          atomicAdd(mine + (order_key(x[u]) >> (32 - kHistBits)) * kCopies, 1u);
+    };
+#pragma unroll
+    for (int c = 0; c < kSelChunks; ++c)
+      if (c * kChunk < n) count(sv[c], c * kChunk);
+    for (int j0 = kBatch; j0 < n; j0 += 2 * kChunk) {
+      float x[2][kSelRounds];
+      load_score_chunk<NT, COH>(srow, j0, n, x[0]);
+      load_score_chunk<NT, COH>(srow, j0 + kChunk, n, x[1]);
+      count(x[0], j0);
+      count(x[1], j0 + kChunk);
+    }
+    lds_barrier();
+    for (int i = tid; i < kHistBins; i += NT) {
+      const uint4 v = copies[i];
+      lhist[i] = v.x + v.y + v.z + v.w;
+    }
+  } else {
+    store_hist_sum<NT>(hv, nslots, lhist);
+  }
   // the scores may still be in flight across both barriers
   lds_barrier();
   if (tid < 64) find_first_bin_lds(lhist, (uint32_t)m, misc + 4);
   lds_barrier();
-  LdsCands<NT, CAP> cs{cand, 0u};
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  LdsCands<NT, CAP> cs{L.cand + wave * LdsCands<NT, CAP>::kSeg, 0u};
   const uint32_t b1 = misc[4], above = misc[5];
   const float g_lo = __uint_as_float(key_floor_bits((uint64_t)b1 << (32 - kHistBits)));
   const float g_hi = __uint_as_float(key_floor_bits((uint64_t)(b1 + 1u) << (32 - kHistBits)));
-  // the last, partial batch holds NaN past n_b
-  auto pad = [&](float (&sv)[kSelPer], int j0) {
-    if (j0 + kBatch > n) {
+  // classifies chunk c of the batch at j0 (positions at or past n_b as NaN)
+  auto classify = [&](float (&x)[kSelRounds], int j0) {
+    if (j0 >= n) return;
+    if (j0 + kChunk > n) {
 #pragma unroll
-      for (int u = 0; u < kSelPer; ++u)
-        if (j0 + u * NT + tid >= n) sv[u] = __builtin_nanf("");
+      for (int u = 0; u < kSelRounds; ++u)
+        if (j0 + u * NT + tid >= n) x[u] = __builtin_nanf("");
     }
+    classify_chunk<NT, CAP>(x, j0, g_lo, g_hi, bm, cs);
   };
-  // the first batch apart, so that its compares start as its loads land
-  pad(sv0, 0);
-  classify_batch<NT, CAP>(sv0, 0, g_lo, g_hi, bm, cs, &misc[7]);
-  for (int j0 = kBatch; j0 < n; j0 += kBatch) {
-    float sv[kSelPer];
-    load_score_batch<NT, COH>(srow, j0, n, sv);
-    pad(sv, j0);
-    classify_batch<NT, CAP>(sv, j0, g_lo, g_hi, bm, cs, &misc[7]);
-  }
+  int j0 = 0;
+  for (; j0 + kBatch < n; j0 += kBatch)  // each chunk's registers take the next batch's
+#pragma unroll
+    for (int c = 0; c < kSelChunks; ++c) {
+      classify(sv[c], j0 + c * kChunk);
+      load_score_chunk<NT, COH>(srow, j0 + kBatch + c * kChunk, n, sv[c]);
+    }
+#pragma unroll
+  for (int c = 0; c < kSelChunks; ++c) classify(sv[c], j0 + c * kChunk);
+  if ((tid & 63) == 0) tmp[wave] = cs.count;
   __syncthreads();
-  const uint32_t nc = misc[7];
+  bool listed = true;  // every wave's candidates are in its segment
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) listed &= tmp[w] <= LdsCands<NT, CAP>::kSeg;
   const uint32_t need = (uint32_t)m - above;
   auto resolve = [&](const auto& cands) {
     uint32_t pmax;
@@ -675,23 +695,22 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
       if (key > T || (key == T && pos <= pmax)) atomicOr(&bm[pos >> 5], 1u << (pos & 31));
     });
   };
-  cs.nc = nc;
-  if (nc <= (uint32_t)CAP)
+  if (listed)
     resolve(cs);
   else
     resolve(RescanCands<NT, COH>{srow, (uint32_t)n, b1});
   __syncthreads();
   // m positions for scores as specified (fewer only with NaN scores)
-  const int got = (int)min(emit_bitmap<NT>(bm, (n + 31) >> 5, write ? idx : nullptr,
-                                       (uint32_t)a.k, tmp, share, lo, hi),
+  const int got = (int)min(emit_bitmap<NT>(bm, words, write ? idx : nullptr, (uint32_t)a.k, tmp,
+                                       share, lo, hi),
                            (uint32_t)m);
   if (write) {
     for (int i = got + tid; i < a.k; i += NT) idx[i] = -1;
     if (tid == 0) a.n_sel[unit] = got;
   }
   if constexpr (NT == kFinishThreads) {
-      if (clear && !a.hist_part) clear_unit_hist(a, unit);
-    }
+    if (clear && added) clear_unit_hist(a, unit);
+  }
   return got;
 }
 

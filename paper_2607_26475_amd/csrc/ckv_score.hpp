@@ -385,7 +385,7 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
       } else if (a.hist_part) {
         store_hist<NT>(lds_hist, a.hist_part + slot * kHistBins);
         if (TWO) store_hist<NT>(lds_hist + kHistBins, a.hist_part2 + slot * kHistBins);
-      } else {
+      } else if (a.hist) {
         flush_hist<NT>(lds_hist, a.hist + (int64_t)unit * kHistBins,
                        a.coarse + (int64_t)unit * kCoarseBins);
         if (TWO)
