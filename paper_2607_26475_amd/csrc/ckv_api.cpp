@@ -450,12 +450,13 @@ AttnArgs attn_args(const Dims& d, const Layout& L, void* ws, const uint16_t* q,
 // and no atomics) when the fused selection reads them and no unit needs more
 // than kMaxPartials of them; then the call has nothing to clear.  Otherwise
 // the histograms are added into cleared per-unit counts.
-bool use_partials(const Dims& d, const Layout& L, int nwg) {
+// slots: how many a unit may have.
+bool use_partials(const Dims& d, const Layout& L, int nwg, int slots = kMaxPartials) {
   if (!L.hist_part_bytes || d.max_ctx > kFusedSelectMaxCtx || nwg < 1) return false;
   // a unit's gu groups meet at most ceil(gu / shortest range) + 1 ranges
   const int64_t gu = (d.max_ctx + kStageRows - 1) / kStageRows;
   const int64_t shortest = gu * d.U / nwg;
-  return shortest >= 1 && (gu + shortest - 1) / shortest + 1 <= kMaxPartials;
+  return shortest >= 1 && (gu + shortest - 1) / shortest + 1 <= slots;
 }
 
 void set_partials(void* ws, const Layout& L, int nwg, ScoreArgs* sc, SelectArgs* sa) {
@@ -1041,14 +1042,16 @@ int ckv::critical_impl(const ckv_shape* shape, const uint16_t* q_att, const uint
   ScoreArgs sc = score_args(d, L, q_sel, k_score, ctx_lens, scale, scores, &sa);
   int nwg = score_blocks(
       sc, d.G, !pipelined ? ScoreKind::kHist : in_place ? ScoreKind::kDualIndexed : ScoreKind::kDual);
-  bool partials = use_partials(d, L, nwg);
+  // same-step calls of shorter contexts read one round of slots at most
+  const int slots = pipelined || d.max_ctx > kSelfCountMaxCtx ? kMaxPartials : kFirstPartials;
+  bool partials = use_partials(d, L, nwg, slots);
   // the previous layer's pending selection joins this launch when this
   // launch is the one-token kernel with static ranges and slots
   bool fold = false;
   if (link && link->prev) {
     const int nwg_sel = score_blocks(
         sc, d.G, in_place ? ScoreKind::kDualSelIndexed : ScoreKind::kDualSel);
-    fold = partials && nwg_sel > 0 && use_partials(d, L, nwg_sel) &&
+    fold = partials && nwg_sel > 0 && use_partials(d, L, nwg_sel, slots) &&
            d.max_ctx <= kFusedSelectMaxCtx && link->prev->units == d.U;
     if (fold) nwg = nwg_sel;
     else CKV_TRY_HIP(launch_select_fused(*link->prev, link->prev->units, s), "select launch");

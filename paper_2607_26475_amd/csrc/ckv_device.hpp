@@ -45,10 +45,12 @@ constexpr int kFusedSelectMaxCtx = 65536;
 // slots u + wg over the workgroups wg whose range meets the unit's groups
 // below n_b (both sides derive the ranges from ctx_lens); slot u + wg is
 // unique because ranges and units are both in group order.  The selection
-// reads at most kMaxPartials slots per unit (min_range keeps it so), else the
-// histograms are added with atomics.
+// reads at most kMaxPartials slots per unit (min_range keeps it so), the first
+// kFirstPartials of them in one round trip; batches of so few units that a unit
+// would meet more ranges add the histograms with atomics or count them later.
 constexpr int kMaxScoreWgs = 1024;
-constexpr int kMaxPartials = 8;
+constexpr int kMaxPartials = 16;
+constexpr int kFirstPartials = 8;
 
 // Attention: one workgroup reduces kAttnRows gathered rows of one unit into a
 // partial (running max, sum of weights, weighted V) per query head; each of

@@ -593,9 +593,10 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
         load_score_chunk<NT, COH>(srow, c * kChunk, a.max_ctx, sv[c]);
   };
   int nslots = 0;
-  uint2 hv[kMaxPartials][kHistBins / NT / 2];
+  const uint32_t* slots = nullptr;
+  uint2 hv[kFirstPartials][kHistBins / NT / 2];
   if (!counts) {
-    const uint32_t* slots = a.hist + (int64_t)unit * kHistBins;
+    slots = a.hist + (int64_t)unit * kHistBins;
     nslots = 1;
     if (a.hist_part) {  // a unit without positions reads a slot it does not use
       const SlotRange r = known ? *known : hist_slots(a, unit);
@@ -653,6 +654,10 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
     }
   } else {
     store_hist_sum<NT>(hv, nslots, lhist);
+    if (nslots > kFirstPartials) {  // uniform: a second round trip
+      load_hist_slots<NT, COH>(slots + kFirstPartials * kHistBins, nslots - kFirstPartials, hv);
+      store_hist_sum<NT, true>(hv, nslots - kFirstPartials, lhist);
+    }
   }
   // the scores may still be in flight across both barriers
   lds_barrier();

@@ -73,17 +73,17 @@ __device__ __forceinline__ void walk_first_bin(const uint32_t* stage, uint32_t c
 }
 
 // All NT threads: the first-digit histogram is the sum of nslots (1 ..
-// kMaxPartials) consecutive slots of kHistBins counts.  Every thread loads
+// kFirstPartials) consecutive slots of kHistBins counts.  Every thread loads
 // its kHistBins / NT consecutive bins of every slot at once (one round trip;
 // slots past nslots repeat slot 0 and are not added) ...
 template <int NT = kFinishThreads, bool COH = false>
 __device__ __forceinline__ void load_hist_slots(const uint32_t* hist, int nslots,
-                                                uint2 (&v)[kMaxPartials][kHistBins / NT / 2]) {
+                                                uint2 (&v)[kFirstPartials][kHistBins / NT / 2]) {
   constexpr int kPairs = kHistBins / NT / 2;
   static_assert(kPairs >= 1, "two bins per thread at least");
   const int t = threadIdx.x;
 #pragma unroll
-  for (int p = 0; p < kMaxPartials; ++p)
+  for (int p = 0; p < kFirstPartials; ++p)
 #pragma unroll
     for (int q = 0; q < kPairs; ++q) {
       const uint32_t* src =
@@ -98,22 +98,23 @@ __device__ __forceinline__ void load_hist_slots(const uint32_t* hist, int nslots
     }
 }
 
-// ... and stores the sums to lhist (LDS); the caller synchronises before
-// reading it.
-template <int NT = kFinishThreads>
-__device__ __forceinline__ void store_hist_sum(const uint2 (&v)[kMaxPartials][kHistBins / NT / 2],
-                                               int nslots, uint32_t* lhist) {
+// ... and stores the sums to lhist (LDS), or adds them to what the same thread
+// stored before (ADD); the caller synchronises before reading it.
+template <int NT = kFinishThreads, bool ADD = false>
+__device__ __forceinline__ void store_hist_sum(
+    const uint2 (&v)[kFirstPartials][kHistBins / NT / 2], int nslots, uint32_t* lhist) {
   constexpr int kPairs = kHistBins / NT / 2;
 #pragma unroll
   for (int q = 0; q < kPairs; ++q) {
-    uint2 acc = make_uint2(0u, 0u);
+    uint2* const at = reinterpret_cast<uint2*>(lhist + 2 * (kPairs * threadIdx.x + q));
+    uint2 acc = ADD ? *at : make_uint2(0u, 0u);
 #pragma unroll
-    for (int p = 0; p < kMaxPartials; ++p)
+    for (int p = 0; p < kFirstPartials; ++p)
       if (p < nslots) {
         acc.x += v[p][q].x;
         acc.y += v[p][q].y;
       }
-    *reinterpret_cast<uint2*>(lhist + 2 * (kPairs * threadIdx.x + q)) = acc;
+    *at = acc;
   }
 }
 

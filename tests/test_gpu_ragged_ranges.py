@@ -37,6 +37,9 @@ CASES = [  # name, B, Hq, Hkv, stored rows, k, lengths
     ("many_requests", 130, 4, 1, 1500, 256, _few_long(130, 1500, 900)),
     ("many_long", 70, 4, 1, 66000, 128, _few_long(70, 66000, 300)),
     ("all_empty", 16, 32, 8, 3000, 512, [0] * 16),
+    # more slots per unit than one round of the selection's loads takes
+    ("many_slots", 6, 32, 8, 20000, 256, [20000, 19000, 0, 20000, 7000, 20000]),
+    ("many_slots_long", 3, 32, 8, 26000, 600, [26000, 25000, 26000]),
 ]
 
 
