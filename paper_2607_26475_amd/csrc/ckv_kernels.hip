@@ -186,18 +186,38 @@ __device__ __forceinline__ void copy_selection(const SelectArgs& a, int unit, in
 // are lane-consecutive), and returns the number of set bits.  Output slots
 // [lo, hi) also go to share[slot - lo] when share is not null.  The bitmap
 // holds exactly m <= limit bits for scores as specified; the limit only keeps
-// other input (NaN scores) inside the row.
-template <int NT = kFinishThreads>
+// other input (NaN scores) inside the row.  PER words per lane and step: 4 for
+// sparse bitmaps of long contexts, whose steps are bound by their own latency
+// (a million positions: 13.4 us with one), else 1; the words of a group of 4
+// past `words` must be zero then.
+template <int NT = kFinishThreads, int PER = 1>
 __device__ __forceinline__ uint32_t emit_bitmap(const uint32_t* bm, int words, int32_t* out,
                                                 uint32_t limit, uint32_t* tmp,
                                                 int32_t* share = nullptr, uint32_t lo = 0,
                                                 uint32_t hi = 0) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kW = NT / 64;
-  const int per = (((words + kW - 1) / kW) + 63) & ~63;
+  constexpr int kW = NT / 64, kStep = 64 * PER;
+  const int per = (((words + kW - 1) / kW) + kStep - 1) / kStep * kStep;
   const int w0 = wave * per, w1 = min(w0 + per, words);
+  auto load = [&](int w, uint32_t (&bits)[PER]) {
+    if constexpr (PER == 4) {
+      uint4 v = make_uint4(0u, 0u, 0u, 0u);
+      if (w < w1) v = *reinterpret_cast<const uint4*>(bm + w);
+      bits[0] = v.x;
+      bits[1] = v.y;
+      bits[2] = v.z;
+      bits[3] = v.w;
+    } else {
+      bits[0] = w < w1 ? bm[w] : 0u;
+    }
+  };
   uint32_t cnt = 0;
-  for (int w = w0 + lane; w < w1; w += 64) cnt += (uint32_t)__popc(bm[w]);
+  for (int ws = w0; ws < w1; ws += kStep) {
+    uint32_t bits[PER];
+    load(ws + PER * lane, bits);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) cnt += (uint32_t)__popc(bits[q]);
+  }
   cnt = wave_sum_u32(cnt);
   if (lane == 0) tmp[wave] = cnt;
   __syncthreads();
@@ -207,21 +227,26 @@ __device__ __forceinline__ uint32_t emit_bitmap(const uint32_t* bm, int words, i
     base += i < wave ? t : 0u;
     total += t;
   }
-  for (int ws = w0; ws < w1; ws += 64) {
-    const int w = ws + lane;
-    uint32_t bits = w < w1 ? bm[w] : 0u;
-    const uint32_t c = (uint32_t)__popc(bits);
+  for (int ws = w0; ws < w1; ws += kStep) {
+    const int w = ws + PER * lane;
+    uint32_t bits[PER];
+    load(w, bits);
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) c += (uint32_t)__popc(bits[q]);
     const uint32_t incl = wave_incl_scan(c);
     uint32_t o = base + incl - c;
-    while (bits) {
-      const int bit = __ffs(bits) - 1;
-      if (o < limit) {
-        if (out) out[o] = w * 32 + bit;
-        if (share && o >= lo && o < hi) share[o - lo] = w * 32 + bit;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      while (bits[q]) {
+        const int bit = __ffs(bits[q]) - 1;
+        if (o < limit) {
+          if (out) out[o] = (w + q) * 32 + bit;
+          if (share && o >= lo && o < hi) share[o - lo] = (w + q) * 32 + bit;
+        }
+        ++o;
+        bits[q] &= bits[q] - 1u;
       }
-      ++o;
-      bits &= bits - 1u;
-    }
     base += __builtin_amdgcn_readlane(incl, 63);
   }
   __syncthreads();
@@ -328,7 +353,7 @@ struct RegCands {
 // stay in registers (a million positions: 10 Ki of them), so the position
 // bitmap has the LDS to itself from the start and is marked directly.
 __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
-  __shared__ uint32_t lds_bm[kBitmapLdsBits / 32];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_bm[kBitmapLdsBits / 32];
   __shared__ __attribute__((aligned(16))) uint32_t hist[2048];
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
   __shared__ uint32_t misc[8];
@@ -352,10 +377,16 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
   const ListCands list{reinterpret_cast<const uint2*>(a.cand) + row,
                        a.cand_keys ? nullptr : a.cand + row, a.scores + row, nc};
   const int words = (n + 31) >> 5;
-  uint32_t* bm = n <= kBitmapLdsBits ? lds_bm : a.bitmap + (int64_t)unit * a.bm_words;
+  const bool in_lds = n <= kBitmapLdsBits;
+  uint32_t* bm = in_lds ? lds_bm : a.bitmap + (int64_t)unit * a.bm_words;
   auto mark = [&](uint32_t p) { atomicOr(&bm[p >> 5], 1u << (p & 31)); };
   auto choose = [&](const auto& cs) {
-    for (int w = tid; w < words; w += kFinishThreads) bm[w] = 0u;
+    if (in_lds) {
+      for (int w = 4 * tid; w < words; w += 4 * kFinishThreads)
+        *reinterpret_cast<uint4*>(lds_bm + w) = make_uint4(0u, 0u, 0u, 0u);
+    } else {  // a unit's words in memory need not be whole groups of 4
+      for (int w = tid; w < words; w += kFinishThreads) bm[w] = 0u;
+    }
     __syncthreads();
     // the positions that the filter selected outright
     const int32_t* sel = a.sel + (int64_t)unit * a.k;
@@ -375,7 +406,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
     choose(list);
   }
   __syncthreads();
-  emit_bitmap(bm, words, idx, (uint32_t)a.k, tmp);
+  if (in_lds)
+    emit_bitmap<kFinishThreads, 4>(lds_bm, words, idx, (uint32_t)a.k, tmp);
+  else
+    emit_bitmap(bm, words, idx, (uint32_t)a.k, tmp);
   for (int i = m + tid; i < a.k; i += kFinishThreads) idx[i] = -1;
   if (tid == 0) a.n_sel[unit] = m;
   copy_selection(a, unit, m);
@@ -1351,6 +1385,7 @@ __device__ __forceinline__ uint16_t f64_to_bf16_rne(double x) {
 template <int BATCH>
 __global__ __launch_bounds__(kGatherThreads) void k_landmarks(LandmarkArgs a) {
   const int64_t stride = (int64_t)gridDim.x * kGatherThreads;
+  const bool small = a.items < (1ll << 35);  // landmark numbers fit in 32 bits
   for (int64_t it = (int64_t)blockIdx.x * kGatherThreads + threadIdx.x; it < a.items;
        it += stride) {
     const int part = (int)(it & 15);
@@ -1404,7 +1439,6 @@ __global__ __launch_bounds__(kGatherThreads) void k_landmarks(LandmarkArgs a) {
 // and the valid rows form a prefix.
 __global__ __launch_bounds__(kGatherThreads) void k_expand(ExpandArgs a) {
   const int unit = blockIdx.y;
-  const bool small = a.items < (1ll << 35);  // landmark numbers fit in 32 bits
   const int i = blockIdx.x * kGatherThreads + threadIdx.x;
   const int n = clamp_len(a.ctx_lens[unit / a.Hkv], a.max_ctx);
   const int m = clamp_len(a.n_chunks[unit], a.kc);
