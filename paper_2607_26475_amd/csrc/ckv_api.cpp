@@ -1399,11 +1399,6 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
     CKV_TRY_HIP(launch_zero(ws, L.zero_end, s), "zero launch");
   }
   CKV_TRY_HIP(launch_score(sc, d.G, true, nwg, s), "score launch");
-  const bool pair = !one && !in_place && d.max_ctx <= kFusedSelectMaxCtx;
-  if (pair)
-    CKV_TRY_HIP(launch_select_pair(s1, s2, s), "select launch");
-  else if ((rc = run_select_tail(s1, d.U, s)))
-    return rc;
   // 2. hits and misses against the predicted set; misses into free slots
   MissArgs m;
   m.idx_true = idx_true;
@@ -1417,8 +1412,16 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   m.hits = hits;
   m.free_slot = L.free_slot ? at<int32_t>(ws, L.free_slot) : nullptr;
   m.k = k;
-  CKV_TRY_HIP(launch_miss(m, d.U, s), "miss launch");
-  if (!one && !pair && (rc = run_select_tail(s2, d.U, s))) return rc;
+  // the selections, with the misses where one workgroup holds both sets
+  const bool with_miss = d.max_ctx <= kFusedSelectMaxCtx && k <= kMissLds;
+  const bool beside = with_miss && !one && !in_place;  // both selections in that launch
+  if (with_miss) {
+    CKV_TRY_HIP(launch_select_miss(s1, beside ? &s2 : nullptr, m, s), "select launch");
+  } else {
+    if ((rc = run_select_tail(s1, d.U, s))) return rc;
+    CKV_TRY_HIP(launch_miss(m, d.U, s), "miss launch");
+  }
+  if (!one && !beside && (rc = run_select_tail(s2, d.U, s))) return rc;
   GatherArgs g;
   g.k_src = k_src;
   g.v_src = v_src;

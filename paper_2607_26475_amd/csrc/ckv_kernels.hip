@@ -768,10 +768,89 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_fused(SelectArgs a) {
   if (a.mpart) merge_partials(a, unit, lhist);
 }
 
-// Two selections of the same units (the corrected entries: the current token's
-// and the next step's) side by side: a unit's selection is one workgroup's
-// serial chain (18 us at 64 Ki positions), and two fit beside each other.
-__global__ __launch_bounds__(kFinishThreads) void k_select_pair(SelectArgs s1, SelectArgs s2) {
+// ---- miss detection -----------------------------------------------------------
+// First index i in [0, n) with a[i] >= v (a ascending).
+template <class P>
+__device__ __forceinline__ int lower_bound_i32(P a, int n, int v) {
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (a[mid] < v) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// One unit: which rows of the selected set (T, nt) the buffer already holds
+// (the predicted set P, np, in slot order), and where the others go.  Free
+// slots are those whose predicted row is not selected, then slots np..nt-1;
+// there are at least as many as misses.  Miss r (in set order) takes the r-th
+// free slot.  T/P/F are LDS arrays or the global sets, per IN_LDS.
+template <bool IN_LDS>
+__device__ __forceinline__ void miss_unit(const MissArgs& a, int unit, const int32_t* T,
+                                          const int32_t* P, int32_t* F, int nt, int np,
+                                          uint32_t* tmp) {
+  const int k = a.k, tid = threadIdx.x;
+  const int64_t base = (int64_t)unit * k;
+  const int ns = max(np, nt);
+  uint32_t nfree = 0;
+  for (int s0 = 0; s0 < ns; s0 += kMissThreads) {
+    const int sl = s0 + tid;
+    bool fr = false;
+    if (sl < ns) {
+      if (sl < np) {
+        const int pos = P[sl];
+        const int j = lower_bound_i32(T, nt, pos);
+        fr = !(j < nt && T[j] == pos);
+      } else {
+        fr = true;
+      }
+    }
+    uint32_t total;
+    const uint32_t incl = block_incl_scan<kMissThreads / 64>(fr ? 1u : 0u, tmp, &total);
+    if (fr) F[nfree + incl - 1] = sl;
+    nfree += total;
+  }
+  __syncthreads();  // the free list is complete
+  uint32_t nmiss = 0;
+  for (int i0 = 0; i0 < nt; i0 += kMissThreads) {
+    const int i = i0 + tid;
+    bool miss = false;
+    int slot = -1, pos = 0;
+    if (i < nt) {
+      pos = T[i];
+      const int j = lower_bound_i32(P, np, pos);
+      if (j < np && P[j] == pos) slot = j;
+      else miss = true;
+    }
+    uint32_t total;
+    const uint32_t incl = block_incl_scan<kMissThreads / 64>(miss ? 1u : 0u, tmp, &total);
+    if (miss) {
+      const uint32_t r = nmiss + incl - 1;  // < nfree
+      slot = F[r];
+      a.miss_pos[base + r] = pos;
+      a.miss_slot[base + r] = slot;
+    }
+    if (i < nt) a.slot_of[base + i] = slot;
+    nmiss += total;
+  }
+  if (tid == 0) {
+    a.n_miss[unit] = (int32_t)nmiss;
+    a.hits[unit] = nt - (int32_t)nmiss;
+  }
+}
+
+// The selections of a corrected layer in one launch: workgroups [0, U) select
+// the current token's sets (s1) and find their misses (m), workgroups [U, 2U),
+// when they are launched, the next step's sets (s2) beside them.  A unit's
+// selection is one workgroup's serial chain (18 us at 64 Ki positions), and two
+// fit beside each other; the misses need the set that the workgroup has in LDS
+// anyway (8.3 us as a launch of its own).  The set's positions and the miss
+// detection take the candidates' space.  Needs k <= kMissLds.
+__global__ __launch_bounds__(kFinishThreads) void k_select_miss(SelectArgs s1, SelectArgs s2,
+                                                               MissArgs m) {
+  static_assert(kMissThreads == kFinishThreads && 3 * kMissLds <= 2 * kCandLds,
+                "the miss detection's sets fit in the candidates' space");
   __shared__ uint2 cand[kCandLds];
   __shared__ uint32_t bm[kFusedSelectMaxCtx / 32];
   __shared__ __attribute__((aligned(16))) uint32_t lhist[2048];
@@ -780,7 +859,18 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_pair(SelectArgs s1, S
   const bool second = (int)blockIdx.x >= s1.units;
   const SelectArgs a = second ? s2 : s1;
   const int unit = blockIdx.x - (second ? s1.units : 0);
-  select_unit(a, unit, SelLds{cand, bm, lhist, tmp, misc}, true, nullptr, 0, 0, true);
+  int32_t* const T = reinterpret_cast<int32_t*>(cand);
+  int32_t* const P = T + kMissLds;
+  // one call site; the first selection's positions also go to T
+  const int nt = select_unit(a, unit, SelLds{cand, bm, lhist, tmp, misc}, true,
+                             second ? nullptr : T, 0u, (uint32_t)a.k, true);
+  if (second) return;  // uniform over the workgroup
+  copy_selection(a, unit, nt);
+  const int np = clamp_len(m.n_pred[unit], m.k);
+  const int32_t* gp = m.idx_pred + (int64_t)unit * m.k;
+  for (int i = threadIdx.x; i < np; i += kMissThreads) P[i] = gp[i];
+  __syncthreads();  // T and P are complete
+  miss_unit<true>(m, unit, T, P, P + kMissLds, nt, np, tmp);
 }
 
 // ---- selection and attention in one launch ------------------------------------
@@ -1574,78 +1664,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_reconstruct(ReconArgs a) {
   reconstruct_range(a, blockIdx.x, gridDim.x, lds);
 }
 
-// ---- miss detection -----------------------------------------------------------
-// First index i in [0, n) with a[i] >= v (a ascending).
-template <class P>
-__device__ __forceinline__ int lower_bound_i32(P a, int n, int v) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] < v) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
-}
-
-// One unit: which rows of the selected set (T, nt) the buffer already holds
-// (the predicted set P, np, in slot order), and where the others go.  Free
-// slots are those whose predicted row is not selected, then slots np..nt-1;
-// there are at least as many as misses.  Miss r (in set order) takes the r-th
-// free slot.  T/P/F are LDS arrays or the global sets, per IN_LDS.
-template <bool IN_LDS>
-__device__ __forceinline__ void miss_unit(const MissArgs& a, int unit, const int32_t* T,
-                                          const int32_t* P, int32_t* F, int nt, int np,
-                                          uint32_t* tmp) {
-  const int k = a.k, tid = threadIdx.x;
-  const int64_t base = (int64_t)unit * k;
-  const int ns = max(np, nt);
-  uint32_t nfree = 0;
-  for (int s0 = 0; s0 < ns; s0 += kMissThreads) {
-    const int sl = s0 + tid;
-    bool fr = false;
-    if (sl < ns) {
-      if (sl < np) {
-        const int pos = P[sl];
-        const int j = lower_bound_i32(T, nt, pos);
-        fr = !(j < nt && T[j] == pos);
-      } else {
-        fr = true;
-      }
-    }
-    uint32_t total;
-    const uint32_t incl = block_incl_scan<kMissThreads / 64>(fr ? 1u : 0u, tmp, &total);
-    if (fr) F[nfree + incl - 1] = sl;
-    nfree += total;
-  }
-  __syncthreads();  // the free list is complete
-  uint32_t nmiss = 0;
-  for (int i0 = 0; i0 < nt; i0 += kMissThreads) {
-    const int i = i0 + tid;
-    bool miss = false;
-    int slot = -1, pos = 0;
-    if (i < nt) {
-      pos = T[i];
-      const int j = lower_bound_i32(P, np, pos);
-      if (j < np && P[j] == pos) slot = j;
-      else miss = true;
-    }
-    uint32_t total;
-    const uint32_t incl = block_incl_scan<kMissThreads / 64>(miss ? 1u : 0u, tmp, &total);
-    if (miss) {
-      const uint32_t r = nmiss + incl - 1;  // < nfree
-      slot = F[r];
-      a.miss_pos[base + r] = pos;
-      a.miss_slot[base + r] = slot;
-    }
-    if (i < nt) a.slot_of[base + i] = slot;
-    nmiss += total;
-  }
-  if (tid == 0) {
-    a.n_miss[unit] = (int32_t)nmiss;
-    a.hits[unit] = nt - (int32_t)nmiss;
-  }
-}
-
+// ---- miss detection as a launch of its own -------------------------------------
 __global__ __launch_bounds__(kMissThreads) void k_miss(MissArgs a) {
   __shared__ int32_t l_true[kMissLds], l_pred[kMissLds], l_free[kMissLds];
   __shared__ uint32_t tmp[kMissThreads / 64 + 1];
@@ -1932,9 +1951,11 @@ hipError_t launch_select_fused(const SelectArgs& a, int units, hipStream_t s) {
   return launch_status();
 }
 
-hipError_t launch_select_pair(const SelectArgs& s1, const SelectArgs& s2, hipStream_t s) {
-  if (s1.units != s2.units) return hipErrorInvalidValue;
-  launch_kernel(CKV_K_FINISH, k_select_pair, dim3(2 * s1.units), dim3(kFinishThreads), s, s1, s2);
+hipError_t launch_select_miss(const SelectArgs& s1, const SelectArgs* s2, const MissArgs& m,
+                              hipStream_t s) {
+  if ((s2 && s1.units != s2->units) || m.k > kMissLds || m.k != s1.k) return hipErrorInvalidValue;
+  launch_kernel(CKV_K_FINISH, k_select_miss, dim3(s2 ? 2 * s1.units : s1.units),
+                dim3(kFinishThreads), s, s1, s2 ? *s2 : s1, m);
   return launch_status();
 }
 

@@ -64,8 +64,11 @@ hipError_t launch_hist(const SelectArgs& a, int units, hipStream_t s);
 hipError_t launch_filter(const SelectArgs& a, int units, hipStream_t s);
 hipError_t launch_finish(const SelectArgs& a, int units, hipStream_t s);
 hipError_t launch_select_fused(const SelectArgs& a, int units, hipStream_t s);
-// two selections of the same units in one launch, as launch_select_fused
-hipError_t launch_select_pair(const SelectArgs& s1, const SelectArgs& s2, hipStream_t s);
+// a corrected layer's selection s1 with its miss detection, and (s2 not null)
+// the next step's selection of the same units, in one launch; n_b <=
+// kFusedSelectMaxCtx, k <= kMissLds
+hipError_t launch_select_miss(const SelectArgs& s1, const SelectArgs* s2, const MissArgs& m,
+                              hipStream_t s);
 hipError_t launch_attn(const AttnArgs& a, int G, bool indexed, int units, hipStream_t s);
 // same-step selection and attention in one launch: heads == 1, nsplit shares
 // of rows per unit (partials [U][nsplit][G] for k_combine when nsplit > 1);
