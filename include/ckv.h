@@ -412,11 +412,12 @@ int ckv_pipeline_destroy(ckv_pipeline* pipe);
  * gather that reads pinned host memory slows kernels on other streams while
  * it runs; a narrower one (80 workgroups carry most of the link's rate)
  * leaves the compute stream most of its speed, for loops where that stream,
- * not the link, sets the step time.  0 (the default) chooses by shape: 80
- * workgroups for pinned sources when max_ctx >= 64 k (the scoring pass then
- * reads at least 32 times the bytes the link carries per layer), else what
- * ckv_gather_kv uses (256 for pinned sources).  0 <= workgroups <= 4096,
- * else CKV_EINVAL. */
+ * not the link, sets the step time.  0 (the default) chooses by shape for
+ * pinned sources: 80 workgroups when max_ctx >= 64 k (the scoring pass then
+ * reads at least 32 times the bytes the link carries per layer), 64 or 128
+ * when max_ctx >= 16 k and a refill has at most 16384 or 32768 rows, else 192;
+ * device sources as ckv_gather_kv.  0 <= workgroups <= 4096, else
+ * CKV_EINVAL. */
 int ckv_pipeline_set_gather_width(ckv_pipeline* pipe, int workgroups);
 
 /* For tests of the event protocol only, never for serving: breaks the

@@ -66,17 +66,30 @@ unsigned long long capture_id(hipStream_t s) {
 }
 
 // Refill grid when the caller set none.  A gather reading pinned host memory
-// with one workgroup per CU slows the compute stream's kernels several-fold
-// while it runs; a narrow one (80 workgroups carry most of the link's rate)
-// leaves them most of their speed.  The compute stream reads about
-// max_ctx/(2k) times the bytes the link carries per layer (the scoring
-// pass's keys against the selected K|V rows); from a ratio of 32 on, its
-// slowed kernels, not the link, would set the step time.
+// slows the compute stream's kernels while it runs, the more workgroups the
+// more; the fewer, the less of the link's rate it carries.  The compute stream
+// reads about max_ctx/(2k) times the bytes the link carries per layer (the
+// scoring pass's keys against the selected K|V rows).
+//   - From a ratio of 32 on, its slowed kernels, not the link, would set the
+//     step time: 80 workgroups.
+//   - From 8 on, refills of few rows leave it too little time of its own: 64
+//     workgroups for up to 16384 rows (4 layers, 8 units of 48 Ki positions, k
+//     2048: 667 us per step against 747 with 256; 16 units of 12 Ki, k 512: 360
+//     against 414), 128 up to 32768 rows (16 units of 48 Ki
+//     positions: 1266 against 1317, 192: 1263; of 64 Ki: 1274, 1358, 1296).
+//   - Else the link sets the step time: 192, level with or just above 256 at
+//     every larger refill (64 units, k 4096, n 131072: 4855 against 4883 us for
+//     2 layers; 32 units, k 2048: 1228 against 1237).
 constexpr int kNarrowRefillWgs = 80;
+constexpr int kWideRefillWgs = 192;
 
 int refill_width(const ckv_pipeline* p, const ckv_shape* shape, int32_t k, int src_kind) {
   if (p->gather_wgs || src_kind != CKV_SRC_HOST_PINNED || !shape || k < 1) return p->gather_wgs;
-  return (int64_t)shape->max_ctx >= 64 * (int64_t)k ? kNarrowRefillWgs : 0;
+  const int64_t n = shape->max_ctx, rows = (int64_t)shape->batch * shape->num_kv_heads * k;
+  if (n >= 64 * (int64_t)k) return kNarrowRefillWgs;
+  if (n >= 16 * (int64_t)k && rows <= 16384) return 64;
+  if (n >= 16 * (int64_t)k && rows <= 32768) return 128;
+  return kWideRefillWgs;
 }
 
 int gather_layer(const ckv_pipeline* p, const ckv_shape* shape, int32_t k, const ckv_layer& L,
