@@ -443,14 +443,11 @@ AttnArgs attn_args(const Dims& d, const Layout& L, void* ws, const uint16_t* q,
   return a;
 }
 
-// Selection given scores and a filled first-digit histogram: one workgroup
-// per unit for contexts that fit its LDS, else the many-workgroup filter
-// followed by the per-unit finish.
 // The scoring pass leaves per-workgroup histograms (stored, so no clearing
-// and no atomics) when the fused selection reads them and no unit needs more
-// than kMaxPartials of them; then the call has nothing to clear.  Otherwise
-// the histograms are added into cleared per-unit counts.
-// slots: how many a unit may have.
+// and no atomics) when the one-workgroup selection reads them and no unit needs
+// more than `slots` of them; then the call has nothing to clear.  Otherwise the
+// selection counts itself (self_counts) or the histograms are added into
+// cleared per-unit counts.
 bool use_partials(const Dims& d, const Layout& L, int nwg, int slots = kMaxPartials) {
   if (!L.hist_part_bytes || d.max_ctx > kFusedSelectMaxCtx || nwg < 1) return false;
   // a unit's gu groups meet at most ceil(gu / shortest range) + 1 ranges
@@ -489,6 +486,9 @@ void set_self_count(ScoreArgs* sc, SelectArgs* sa) {
   sa->hist = nullptr;
 }
 
+// Selection given scores: one workgroup per unit for contexts that fit its
+// LDS, else the many-workgroup filter (given the first-digit histogram) followed
+// by the per-unit finish.
 int run_select_tail(const SelectArgs& a, int units, hipStream_t s) {
   if (a.max_ctx <= kFusedSelectMaxCtx) {
     CKV_TRY_HIP(launch_select_fused(a, units, s), "select launch");
@@ -1384,7 +1384,9 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   }
   const int nwg = score_blocks(sc, d.G, one ? ScoreKind::kHist : ScoreKind::kTwo);
   const size_t slots_bytes = (size_t)(d.U + nwg) * kHistBins * 4;
-  if (use_partials(d, L, nwg) && (one || 2 * slots_bytes <= L.hist_part_bytes)) {
+  // room for both queries' slots, asked of one query too: layers of a loop that
+  // share cleared histograms must agree on whether they use them
+  if (use_partials(d, L, nwg) && 2 * slots_bytes <= L.hist_part_bytes) {
     set_partials(ws, L, nwg, &sc, &s1);
     if (!one) {  // the second query's slots after the first's
       sc.hist_part2 = at<uint32_t>(ws, L.hist_part + slots_bytes);

@@ -2,7 +2,8 @@
 // keys (Sec. 2.2: only the critical entries within the sparse budget are
 // retrieved; one index set per KV head).
 //
-// Three passes, all exact:
+// Three passes, all exact (one workgroup does 2 and 3, and 1 where nothing else
+// has, for contexts whose scores it can hold):
 //   1. histogram of the first digit (top 11 bits of the order key), fused
 //      into the scoring pass or run over given scores;
 //   2. filter (many workgroups per unit): positions whose first digit is

@@ -91,3 +91,47 @@ def test_two_queries(name, B, Hkv, G, n, k, queries, in_place):
             assert int(hits[b, h]) == len(both), (b, h)
     ref = oracle_attn_over(so, q, K, V, g_true, g_nt, k)
     assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
+
+
+def test_loop_mixes_one_and_two_queries():
+    """Corrected layers of one step share cleared histograms: a layer with one
+    query before one with two, at a unit count whose slots hold one query's
+    histograms but not two."""
+    print("loop of one and two queries", flush=True)
+    dev = device()
+    B, Hkv, G, n, k, d = 65, 8, 1, 300, 32, 128
+    w = dataclasses.replace(synth.WORKLOADS["dual64_s"], name="twoq_loop", batch=B, q_heads=Hkv,
+                            kv_heads=Hkv, max_ctx=n, ctx_min=100, k=k, layers=2)
+    i32 = dict(dtype=torch.int32, device=dev)
+    full = lambda *s: torch.full(s, -9, **i32)  # noqa: E731
+    o = orc()
+    so = o.shape(B, Hkv, Hkv, d, n)
+    layers, want, kept = [], [], []
+    for i in range(2):
+        t = synth.make_layer(w, seed=71, layer=i, device=dev)
+        lens = t["ctx_lens"].cpu().numpy()
+        q, qs = u16(t["q"]), u16(t["q_sel"]) if i else u16(t["q"])
+        S = [o.score_keys(so, x, u16(t["k"]), lens, SCALE, nthreads=8) for x in (q, qs)]
+        want.append([(o.select_topk(so, s, lens, k, nthreads=8), s) for s in S])
+        pred, npred = make_prediction("half", S[0], S[1], lens, k, n, np.random.default_rng(i))
+        layers.append({"q_att": t["q"], "q_sel": t["q_sel"] if i else None, "k_score": t["k"],
+                       "k_src": t["k"], "v_src": t["v"], "idx_prev": torch.from_numpy(pred).to(dev),
+                       "n_sel_prev": torch.from_numpy(npred).to(dev), "idx_next": full(B, Hkv, k),
+                       "n_sel_next": full(B, Hkv), "idx_true": full(B, Hkv, k),
+                       "n_true": full(B, Hkv), "hits": full(B, Hkv),
+                       "out": torch.zeros((B, Hkv, d), device=dev)})
+        kept.append(t)
+    s = ckv.shape_for(B, Hkv, Hkv, n)
+    ws = ckv.workspace(s, k, ckv.ENTRY_CORRECTED_ATTN)
+    ws.fill_(0xA5)
+    bufs = [torch.zeros((B, Hkv, k, d), dtype=torch.bfloat16, device=dev) for _ in range(4)]
+    pipe, copy = ckv.Pipeline(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    pipe.prime(s, k, layers, ckv.SRC_DEVICE, bufs[:2], bufs[2:], copy)
+    pipe.step(s, layers, kept[0]["ctx_lens"], k, SCALE, ckv.SRC_DEVICE, bufs[:2], bufs[2:], ws,
+              None, copy)
+    torch.cuda.synchronize()
+    pipe.close()
+    for l, ((true, s1), (nxt, s2)) in zip(layers, want):
+        check_index_sets(l["idx_true"].cpu().numpy(), l["n_true"].cpu().numpy(), *true, s1, lens)
+        check_index_sets(l["idx_next"].cpu().numpy(), l["n_sel_next"].cpu().numpy(), *nxt, s2, lens)
