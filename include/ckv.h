@@ -415,8 +415,8 @@ int ckv_pipeline_destroy(ckv_pipeline* pipe);
  * not the link, sets the step time.  0 (the default) chooses by shape for
  * pinned sources: 80 workgroups when max_ctx >= 64 k (the scoring pass then
  * reads at least 32 times the bytes the link carries per layer), 64 or 128
- * when max_ctx >= 16 k and a refill has at most 16384 or 32768 rows, else 192;
- * device sources as ckv_gather_kv.  0 <= workgroups <= 4096, else
+ * when max_ctx >= 16 k and a refill has at most 16384 or 32768 rows, else 192
+ * up to 262144 rows and 256 beyond; device sources as ckv_gather_kv.  0 <= workgroups <= 4096, else
  * CKV_EINVAL. */
 int ckv_pipeline_set_gather_width(ckv_pipeline* pipe, int workgroups);
 

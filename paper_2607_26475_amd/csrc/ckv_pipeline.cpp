@@ -77,11 +77,12 @@ unsigned long long capture_id(hipStream_t s) {
 //     2048: 667 us per step against 747 with 256; 16 units of 12 Ki, k 512: 360
 //     against 414), 128 up to 32768 rows (16 units of 48 Ki
 //     positions: 1266 against 1317, 192: 1263; of 64 Ki: 1274, 1358, 1296).
-//   - Else the link sets the step time: 192, level with or just above 256 at
-//     every larger refill (64 units, k 4096, n 131072: 4855 against 4883 us for
-//     2 layers; 32 units, k 2048: 1228 against 1237).
+//   - Else the link sets the step time: 192 up to 262144 rows (64 units, k 4096,
+//     n 131072: 4855 against 4883 us for 2 layers with 256; 32 units, k 2048:
+//     1228 against 1237), 256 beyond (512 units, k 1024: 9690 against 9755).
 constexpr int kNarrowRefillWgs = 80;
 constexpr int kWideRefillWgs = 192;
+constexpr int64_t kWideRefillRows = 262144;
 
 int refill_width(const ckv_pipeline* p, const ckv_shape* shape, int32_t k, int src_kind) {
   if (p->gather_wgs || src_kind != CKV_SRC_HOST_PINNED || !shape || k < 1) return p->gather_wgs;
@@ -89,7 +90,7 @@ int refill_width(const ckv_pipeline* p, const ckv_shape* shape, int32_t k, int s
   if (n >= 64 * (int64_t)k) return kNarrowRefillWgs;
   if (n >= 16 * (int64_t)k && rows <= 16384) return 64;
   if (n >= 16 * (int64_t)k && rows <= 32768) return 128;
-  return kWideRefillWgs;
+  return rows <= kWideRefillRows ? kWideRefillWgs : 0;  // 0: the gather's own width
 }
 
 int gather_layer(const ckv_pipeline* p, const ckv_shape* shape, int32_t k, const ckv_layer& L,
