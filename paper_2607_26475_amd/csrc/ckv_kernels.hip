@@ -338,8 +338,9 @@ struct RegCands {
   __device__ __forceinline__ void load(const ListCands& l) {
     nc = l.nc;
 #pragma unroll
-    for (int u = 0; u < kRegCands; ++u)  // unconditional (clamped) loads, all in flight
-      c[u] = l.listed(min((uint32_t)(u * kFinishThreads) + threadIdx.x, nc - 1u));
+    for (int u = 0; u < kRegCands; ++u)  // clamped loads, as many rounds as there are
+      if ((uint32_t)(u * kFinishThreads) < nc)  // uniform
+        c[u] = l.listed(min((uint32_t)(u * kFinishThreads) + threadIdx.x, nc - 1u));
   }
   template <class F>
   __device__ __forceinline__ void each(F f) const {
