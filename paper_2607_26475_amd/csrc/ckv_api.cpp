@@ -382,6 +382,13 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
   return a;
 }
 
+// Least range of a pass that adds its histograms: every range adds one per unit
+// it meets, and the atomics on a unit's few dozen crowded bins queue.  One unit
+// of 124 Ki positions (3886 groups), attend-and-score launch: 8 groups per
+// range 51 us, 16: 32, 24: 26.6, 32: 25; 3 units of 34 to 124 Ki, two tokens:
+// 18 groups 38, 19: 32, 24: 29, 32: 27.3.  Large batches have longer ranges.
+constexpr int kAddedMinRange = 32;
+
 // Scoring arguments; with sel set, the pass counts the first digit into that
 // selection's histograms, and a pipelined launch with enough work may take
 // it as claims from the selection's claim counter (unit 0's control word
@@ -409,7 +416,7 @@ ScoreArgs score_args(const Dims& d, const Layout& L, const uint16_t* q,
   a.units = d.U;
   a.chunk = 1;
   a.hist_part = nullptr;
-  a.min_range = 1;
+  a.min_range = sel ? kAddedMinRange : 1;  // slots set their own
   a.tails = 0;
   a.q2 = nullptr;
   a.scores2 = nullptr;
@@ -483,6 +490,7 @@ bool self_counts(const Dims& d) {
 
 void set_self_count(ScoreArgs* sc, SelectArgs* sa) {
   sc->hist = sc->coarse = sc->claim = nullptr;
+  sc->min_range = 1;  // nothing is added
   sa->hist = nullptr;
 }
 
