@@ -575,7 +575,8 @@ __device__ __forceinline__ void merge_partials(const SelectArgs& a, int unit, ui
 
 // LDS of a one-workgroup selection (see select_unit).
 struct SelLds {
-  uint2* cand;      // [CAP of select_unit]
+  uint4* cand;      // two candidates each, [CAP of select_unit / 2]: a count's four
+                    // copies lie here and are read 16 bytes at a time
   uint32_t* bm;     // [kFusedSelectMaxCtx / 32]
   uint32_t* lhist;  // [2048]
   uint32_t* tmp;    // [threads / 64 + 1]
@@ -608,6 +609,7 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   constexpr int kChunk = kSelRounds * NT, kBatch = kSelChunks * kChunk;
   constexpr int kCopies = 4;
   static_assert(2 * CAP >= kCopies * kHistBins, "the histogram's copies fit in the candidates");
+  static_assert(alignof(decltype(*L.cand)) >= 16, "the copies are read 16 bytes at a time");
   const int tid = threadIdx.x;
   uint32_t* const bm = L.bm;
   uint32_t* const lhist = L.lhist;
@@ -662,7 +664,7 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   }
   const int words = (n + 31) >> 5;
   if (counts) {
-    uint4* const copies = reinterpret_cast<uint4*>(L.cand);  // [bin][copy]
+    uint4* const copies = L.cand;  // [bin][copy]
     for (int i = tid; i < kHistBins; i += NT) copies[i] = make_uint4(0u, 0u, 0u, 0u);
     lds_barrier();
     uint32_t* const mine = reinterpret_cast<uint32_t*>(L.cand) + (tid & (kCopies - 1));
@@ -699,7 +701,8 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   if (tid < 64) find_first_bin_lds(lhist, (uint32_t)m, misc + 4);
   lds_barrier();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  LdsCands<NT, CAP> cs{L.cand + wave * LdsCands<NT, CAP>::kSeg, 0u};
+  LdsCands<NT, CAP> cs{
+      reinterpret_cast<uint2*>(L.cand) + wave * LdsCands<NT, CAP>::kSeg, 0u};
   const uint32_t b1 = misc[4], above = misc[5];
   const float g_lo = __uint_as_float(key_floor_bits((uint64_t)b1 << (32 - kHistBits)));
   const float g_hi = __uint_as_float(key_floor_bits((uint64_t)(b1 + 1u) << (32 - kHistBits)));
@@ -755,7 +758,7 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
 }
 
 __global__ __launch_bounds__(kFinishThreads) void k_select_fused(SelectArgs a) {
-  __shared__ uint2 cand[kCandLds];
+  __shared__ uint4 cand[kCandLds / 2];
   __shared__ uint32_t bm[kFusedSelectMaxCtx / 32];
   __shared__ __attribute__((aligned(16))) uint32_t lhist[2048];
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
@@ -852,7 +855,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_miss(SelectArgs s1, S
                                                                MissArgs m) {
   static_assert(kMissThreads == kFinishThreads && 3 * kMissLds <= 2 * kCandLds,
                 "the miss detection's sets fit in the candidates' space");
-  __shared__ uint2 cand[kCandLds];
+  __shared__ uint4 cand[kCandLds / 2];
   __shared__ uint32_t bm[kFusedSelectMaxCtx / 32];
   __shared__ __attribute__((aligned(16))) uint32_t lhist[2048];
   __shared__ uint32_t tmp[kFinishThreads / 64 + 1];
@@ -928,7 +931,7 @@ __device__ __forceinline__ void select_attn_part(const SelectArgs& sa, const Att
   static_assert(G % HEADS == 0, "whole heads per workgroup");
   constexpr int GA = G / HEADS;  // heads each workgroup attends with
   using Lds = SelAttnLds<GA>;
-  const SelLds L{reinterpret_cast<uint2*>(lds), lds + 2 * kCandLds,
+  const SelLds L{reinterpret_cast<uint4*>(lds), lds + 2 * kCandLds,
                  lds + 2 * kCandLds + kFusedSelectMaxCtx / 32, tmp, misc};
   int32_t* share = reinterpret_cast<int32_t*>(lds + Lds::kPosOff);
   // the share of a set of m positions is known before the set is: m =
@@ -1035,7 +1038,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_attn_chunks(SelectArg
   int unit, split;
   split_block(blockIdx.x, 2, &unit, &split);
   if (unit >= sa.units) return;  // uniform over the workgroup
-  const SelLds L{reinterpret_cast<uint2*>(lds), lds + 2 * kCandLds,
+  const SelLds L{reinterpret_cast<uint4*>(lds), lds + 2 * kCandLds,
                  lds + 2 * kCandLds + kFusedSelectMaxCtx / 32, tmp, misc};
   int32_t* list = reinterpret_cast<int32_t*>(lds + Lds::kPosOff);
   const int nc = unit_len(sa.ctx_lens[unit / sa.Hkv], sa.max_ctx, sa.chunk);
@@ -1276,7 +1279,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_dual_sel(AttnArgs at, ScoreArg
   uint32_t* l32 = reinterpret_cast<uint32_t*>(lds);
   int blk = blockIdx.x;
   if (blk < sel_blocks) {
-    const SelLds L{reinterpret_cast<uint2*>(l32), l32 + 2 * kDualSelCands,
+    const SelLds L{reinterpret_cast<uint4*>(l32), l32 + 2 * kDualSelCands,
                    l32 + 2 * kDualSelCands + kFusedSelectMaxCtx / 32, tmp, misc};
     select_unit<kAttnThreads, kDualSelCands>(sel, blk, L, true, nullptr, 0, 0, false);
     return;
