@@ -242,7 +242,9 @@ int ckv_critical_kv_attn_noalloc(const ckv_shape* shape, const uint16_t* q_att,
  *      for the next step.
  * idx_pred must be ascending in [0, max_ctx) and -1 padded, as
  * ckv_select_topk writes it; n_pred is clamped to [0, k].  k_buf/v_buf are
- * modified: slots of mispredicted rows are overwritten.  All streams run at
+ * modified: slots of mispredicted rows are overwritten.  idx_next/n_next may
+ * share memory with idx_pred/n_pred, idx_true/n_true and hits: the next step's
+ * sets are then written last and replace what was there.  All streams run at
  * the default priority; the misses are fetched on `stream` ahead of the
  * attention that needs them.  Workspace: CKV_ENTRY_CORRECTED_ATTN. */
 int ckv_corrected_attn(const ckv_shape* shape, const uint16_t* q_att,

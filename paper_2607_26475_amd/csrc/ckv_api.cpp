@@ -1368,12 +1368,20 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   float* scores = at<float>(ws, L.scores);
   // 1. the current token's own selection and the next step's, both from one
   //    pass over the keys (one selection, written twice, when there is one query)
-  // A caller may let the next step's sets take the place of the prediction:
-  // then they are written after 2. has read it.
-  const int64_t entries = (int64_t)d.U * k;
-  const bool in_place = (idx_next < idx_pred + entries && idx_pred < idx_next + entries) ||
-                        (n_next < n_pred + d.U && n_pred < n_next + d.U);
-  const bool one = q_sel == q_att && !in_place;
+  // A caller may let the next step's sets take the place of the prediction or of
+  // the call's own sets and counts: then they are selected after all else.
+  const int64_t entries = (int64_t)d.U * k, counts = d.U;
+  auto over_next = [&](const int32_t* p, int64_t n) {
+    auto meets = [&](const int32_t* q, int64_t m) {
+      const uintptr_t a = (uintptr_t)p, b = (uintptr_t)q;
+      return a < b + 4 * (uintptr_t)m && b < a + 4 * (uintptr_t)n;
+    };
+    return meets(idx_next, entries) || meets(n_next, counts);
+  };
+  const bool last = over_next(idx_pred, entries) || over_next(n_pred, counts) ||
+                    over_next(idx_true, entries) || over_next(n_true, counts) ||
+                    over_next(hits, counts);
+  const bool one = q_sel == q_att && !last;
   SelectArgs s1 = select_args(d, L, ws, scores, ctx_lens, k, idx_true, n_true);
   SelectArgs s2 = select_args(d, L, ws, at<float>(ws, L.scores2), ctx_lens, k, idx_next, n_next);
   s2.hist = at<uint32_t>(ws, L.hist2);
@@ -1424,14 +1432,14 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   m.k = k;
   // the selections, with the misses where one workgroup holds both sets
   const bool with_miss = d.max_ctx <= kFusedSelectMaxCtx && k <= kMissLds;
-  const bool beside = with_miss && !one && !in_place;  // both selections in that launch
+  const bool beside = with_miss && !one && !last;  // both selections in that launch
   if (with_miss) {
     CKV_TRY_HIP(launch_select_miss(s1, beside ? &s2 : nullptr, m, s), "select launch");
   } else {
     if ((rc = run_select_tail(s1, d.U, s))) return rc;
     CKV_TRY_HIP(launch_miss(m, d.U, s), "miss launch");
   }
-  if (!one && !beside && (rc = run_select_tail(s2, d.U, s))) return rc;
+  if (!one && !beside && !last && (rc = run_select_tail(s2, d.U, s))) return rc;
   GatherArgs g;
   g.k_src = k_src;
   g.v_src = v_src;
@@ -1459,7 +1467,8 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   db.max_ctx = k;
   AttnArgs at_ = attn_args(db, L, ws, q_att, k_buf, v_buf, m.slot_of, n_true, kD, k, scale,
                            out);
-  return run_attention(at_, d, true, s);
+  if ((rc = run_attention(at_, d, true, s))) return rc;
+  return last ? run_select_tail(s2, d.U, s) : CKV_OK;
 }
 
 extern "C" {

@@ -5,8 +5,9 @@ one pass.  Every group size has its own placement of the two queries' head
 rows in the matrix products; histograms go to slots (many units) or are added
 (few units, long contexts); heavy ties exceed a selection's candidate list.
 The caller may pass one query for both (the set is then written twice) and
-may let the next step's sets take the place of the prediction.  Sets against
-the oracle, outputs against the oracle's attention over the sets.
+may let the next step's sets take the place of the prediction, or of the
+call's own sets and counts.  Sets against the oracle, outputs against the
+oracle's attention over the sets.
 """
 from __future__ import annotations
 
@@ -90,6 +91,65 @@ def test_two_queries(name, B, Hkv, G, n, k, queries, in_place):
             both = np.intersect1d(g_true[b, h, :g_nt[b, h]], pred[b, h, :npred[b, h]])
             assert int(hits[b, h]) == len(both), (b, h)
     ref = oracle_attn_over(so, q, K, V, g_true, g_nt, k)
+    assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
+
+
+@pytest.mark.parametrize("queries", [1, 2])
+@pytest.mark.parametrize("n,place", [(4500, "sets"), (70001, "sets"), (4500, "counts"),
+                                     (4500, "shifted")])
+def test_next_in_the_place_of_results(n, place, queries):
+    """The next step's sets written over the call's own sets (idx_next =
+    idx_true, n_next = n_true), its counts over the hits, or its sets one unit
+    further in the own sets' array: the next step's sets are whole and the
+    output is the attention over the own sets."""
+    print("next in the place of results", n, place, queries, flush=True)
+    dev = device()
+    B, Hkv, G, k, d = 2, 2, 4, 96, 128
+    w = dataclasses.replace(synth.WORKLOADS["dual64_s"], name=f"twoq_place{n}", batch=B,
+                            q_heads=G * Hkv, kv_heads=Hkv, max_ctx=n, ctx_min=n // 3, k=k,
+                            layers=1)
+    t = synth.make_layer(w, seed=53, device=dev)
+    t["ctx_lens"][0] = k - 7  # counts that differ between the units
+    lens = t["ctx_lens"].cpu().numpy()
+    q, K, V = u16(t["q"]), u16(t["k"]), u16(t["v"])
+    o = orc()
+    so = o.shape(B, G * Hkv, Hkv, d, n)
+    S = [o.score_keys(so, x, K, lens, SCALE, nthreads=8)
+         for x in (q, u16(t["q_sel"]) if queries == 2 else q)]
+    want = [o.select_topk(so, s, lens, k, nthreads=8) for s in S]
+    pred, npred = make_prediction("half", S[0], S[1], lens, k, n, np.random.default_rng(3))
+
+    s = ckv.shape_for(B, G * Hkv, Hkv, n)
+    i32 = dict(dtype=torch.int32, device=dev)
+    sets = torch.full((B * Hkv + 1, k), -9, **i32)  # one unit more: for the shift
+    U = B * Hkv
+    idx_true = sets[:U].view(B, Hkv, k)
+    n_true, hits, n_next = (torch.full((B, Hkv), -9, **i32) for _ in range(3))
+    idx_next = torch.full((B, Hkv, k), -9, **i32)
+    if place == "sets":
+        idx_next, n_next = idx_true, n_true
+    elif place == "counts":
+        n_next = hits
+    else:
+        idx_next = sets[1:].view(B, Hkv, k)
+    idx_pred, n_pred = torch.from_numpy(pred).to(dev), torch.from_numpy(npred).to(dev)
+    kb = torch.zeros((B, Hkv, k, d), dtype=torch.bfloat16, device=dev)
+    vb = torch.zeros_like(kb)
+    ckv.gather_kv(s, t["k"], t["v"], ckv.SRC_DEVICE, idx_pred, n_pred, k, kb, vb)
+    out = torch.full((B, G * Hkv, d), float("nan"), device=dev)
+    ws = ckv.workspace(s, k, ckv.ENTRY_CORRECTED_ATTN)
+    ws.fill_(0xA5)
+    ckv.corrected_attn(s, t["q"], t["q_sel"] if queries == 2 else None, t["k"], t["ctx_lens"], k,
+                       SCALE, t["k"], t["v"], ckv.SRC_DEVICE, idx_pred, n_pred, kb, vb, idx_true,
+                       n_true, hits, idx_next, n_next, out, ws)
+    torch.cuda.synchronize()
+    check_index_sets(idx_next.cpu().numpy(), n_next.cpu().numpy(), *want[1], S[1], lens)
+    if place != "counts":
+        for b in range(B):
+            for h in range(Hkv):
+                both = np.intersect1d(want[0][0][b, h, :want[0][1][b, h]], pred[b, h, :npred[b, h]])
+                assert int(hits[b, h]) == len(both), (b, h)
+    ref = oracle_attn_over(so, q, K, V, *want[0], k)
     assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
 
 
