@@ -1432,7 +1432,9 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
   m.k = k;
   // the selections, with the misses where one workgroup holds both sets
   const bool with_miss = d.max_ctx <= kFusedSelectMaxCtx && k <= kMissLds;
-  const bool beside = with_miss && !one && !last;  // both selections in that launch
+  // both selections in that launch, where its work-items stay below 2^32
+  const bool beside = with_miss && !one && !last &&
+                      2 * (int64_t)d.U * kFinishThreads < ((int64_t)1 << 32);
   if (with_miss) {
     CKV_TRY_HIP(launch_select_miss(s1, beside ? &s2 : nullptr, m, s), "select launch");
   } else {

@@ -153,6 +153,36 @@ def test_next_in_the_place_of_results(n, place, queries):
     assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
 
 
+def test_more_units_than_one_launch_selects():
+    """The two selections of 2^21 + 8 units of one position: side by side they
+    would take more work-items than a launch may have."""
+    print("two selections of 2^21 + 8 units", flush=True)
+    dev = device()
+    U, d = (1 << 21) + 8, 128
+    s = ckv.shape_for(1, U, U, 1)
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    q = torch.ones((1, U, d), **bf)
+    keys = torch.ones((1, U, 1, d), **bf)
+    vals = (torch.arange(U, device=dev) % 251).to(torch.bfloat16).view(1, U, 1, 1).expand(
+        -1, -1, -1, d).contiguous()
+    lens = torch.ones(1, dtype=torch.int32, device=dev)
+    i32 = lambda v: torch.full((1, U, 1), v, dtype=torch.int32, device=dev)  # noqa: E731
+    pred, n_pred = i32(-1), i32(0).view(1, U)
+    kb, vb = torch.zeros_like(keys), torch.zeros_like(vals)
+    true, nxt = i32(-9), i32(-9)
+    n_true, n_next, hits = (i32(-9).view(1, U) for _ in range(3))
+    out = torch.full((1, U, d), float("nan"), device=dev)
+    ws = ckv.workspace(s, 1, ckv.ENTRY_CORRECTED_ATTN)
+    ckv.corrected_attn(s, q, q.clone(), keys, lens, 1, SCALE, keys, vals, ckv.SRC_DEVICE, pred,
+                       n_pred, kb, vb, true, n_true, hits, nxt, n_next, out, ws)
+    torch.cuda.synchronize()
+    for got in (true, nxt, hits):
+        assert int(got.abs().max()) == 0
+    for got in (n_true, n_next):
+        assert int(got.min()) == int(got.max()) == 1
+    assert torch.equal(out, vals.view(1, U, d).float())
+
+
 def test_loop_mixes_one_and_two_queries():
     """Corrected layers of one step share cleared histograms: a layer with one
     query before one with two, at a unit count whose slots hold one query's
