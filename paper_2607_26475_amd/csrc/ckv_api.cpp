@@ -286,10 +286,16 @@ Layout make_layout(const Dims& d, int32_t k, int entry) {
   return L;
 }
 
+// The shapes an entry takes follow from tiles of this many positions, whatever
+// tile its kernels use (kFilterTile is a multiple of it).
+constexpr int kGridTile = 4096;
+
 int check_grid(const Dims& d, const Layout& L) {
   // work-items per dispatch must stay below 2^32
+  static_assert(kFilterTile % kGridTile == 0 && kFilterThreads <= 1024, "fewer work-items");
   const int64_t limit = ((int64_t)1 << 32) / 1024 - 1;
-  if ((int64_t)d.U * L.filter_tiles > limit || (int64_t)d.U * L.chunks > limit)
+  const int64_t tiles = (d.max_ctx + kGridTile - 1) / kGridTile;
+  if (d.U * tiles > limit || (int64_t)d.U * L.chunks > limit)
     return fail(CKV_EUNSUPPORTED, "grid too large for this shape");
   return CKV_OK;
 }

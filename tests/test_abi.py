@@ -98,6 +98,25 @@ def test_budget_and_workspace_validation():
         ckv.workspace_bytes(s, 16, 42)
 
 
+def test_grids_past_the_limit_are_refused():
+    """Units times tiles of 4096 positions, or times chunks of 256 selected rows,
+    of 2^22 and more; the workspace (NULL here) is looked at after that."""
+    lib = ckv._lib
+
+    def select(units, n, k=16):
+        s = good_shape(batch=1, num_q_heads=units, num_kv_heads=units, max_ctx=n)
+        return lib.ckv_select_topk(ctypes.byref(s), FAKE, FAKE, k, FAKE, FAKE, None, 0, 0)
+
+    assert select(1 << 21, 4096) == STATUS["EWORKSPACE"]
+    assert select(1 << 21, 4097) == STATUS["EUNSUPPORTED"]
+    assert select(1 << 10, 1 << 24) == STATUS["EUNSUPPORTED"]
+    assert select((1 << 10) - 1, 1 << 24) == STATUS["EWORKSPACE"]
+    assert select((1 << 22) - 1, 1) == STATUS["EWORKSPACE"]
+    assert select(1 << 22, 1) == STATUS["EUNSUPPORTED"]
+    assert select(1 << 21, 1, k=256) == STATUS["EWORKSPACE"]
+    assert select(1 << 21, 1, k=257) == STATUS["EUNSUPPORTED"]
+
+
 def test_workspace_sizes_grow_with_shape():
     small = good_shape(max_ctx=1000)
     big = good_shape(max_ctx=100000)
