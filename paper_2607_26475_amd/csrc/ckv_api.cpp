@@ -1404,21 +1404,14 @@ int ckv::corrected_impl(const ckv_shape* shape, const uint16_t* q_att, const uin
     sc.coarse2 = s2.coarse;
     s1.cand_keys = s2.cand_keys = 0;  // the second scores take that space
   }
-  const int nwg1 = score_blocks(sc, d.G, ScoreKind::kHist);
-  const int nwg2 = score_blocks(sc, d.G, ScoreKind::kTwo);
-  const int nwg = one ? nwg1 : nwg2;
-  // The second query's slots lie after the first's, or, when a batch is too large
-  // for both there (above 512 units with 256 workgroups), in the place of the
-  // added histograms, which nothing uses then.  One query asks for the same room:
-  // layers of a loop that share cleared histograms must agree on whether they use
-  // them.
-  const size_t slots_bytes = (size_t)(d.U + nwg2) * kHistBins * 4;
-  const bool after = 2 * slots_bytes <= L.hist_part_bytes;
-  if (use_partials(d, L, nwg1) && use_partials(d, L, nwg2) &&
-      (after || slots_bytes <= L.zero_end)) {
+  const int nwg = score_blocks(sc, d.G, one ? ScoreKind::kHist : ScoreKind::kTwo);
+  const size_t slots_bytes = (size_t)(d.U + nwg) * kHistBins * 4;
+  // room for both queries' slots, asked of one query too: layers of a loop that
+  // share cleared histograms must agree on whether they use them
+  if (use_partials(d, L, nwg) && 2 * slots_bytes <= L.hist_part_bytes) {
     set_partials(ws, L, nwg, &sc, &s1);
-    if (!one) {
-      sc.hist_part2 = at<uint32_t>(ws, after ? L.hist_part + slots_bytes : L.hist);
+    if (!one) {  // the second query's slots after the first's
+      sc.hist_part2 = at<uint32_t>(ws, L.hist_part + slots_bytes);
       s2.hist_part = sc.hist_part2;
       s2.score_nwg = nwg;
       s2.min_range = s1.min_range;

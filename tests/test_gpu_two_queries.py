@@ -153,52 +153,6 @@ def test_next_in_the_place_of_results(n, place, queries):
     assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
 
 
-@pytest.mark.parametrize("queries", [1, 2])
-@pytest.mark.parametrize("B,G", [(64, 1), (65, 1), (65, 16), (200, 4)])
-def test_large_batches_clear_nothing(B, G, queries):
-    """512 units, whose slots for two queries lie one after the other, and more,
-    whose second slots take the place of the added histograms: no clearing
-    launch, and the oracle's sets, twice on one workspace."""
-    print("large batches", B, G, queries, flush=True)
-    dev = device()
-    Hkv, n, k, d = 8, 300, 32, 128
-    w = dataclasses.replace(synth.WORKLOADS["dual64_s"], name=f"twoq_large{B}", batch=B,
-                            q_heads=Hkv * G, kv_heads=Hkv, max_ctx=n, ctx_min=1, k=k, layers=1)
-    t = synth.make_layer(w, seed=57, device=dev)
-    lens = t["ctx_lens"].cpu().numpy()
-    q = u16(t["q"])
-    o = orc()
-    so = o.shape(B, Hkv * G, Hkv, d, n)
-    S = [o.score_keys(so, x, u16(t["k"]), lens, SCALE, nthreads=8)
-         for x in (q, u16(t["q_sel"]) if queries == 2 else q)]
-    want = [o.select_topk(so, s, lens, k, nthreads=8) for s in S]
-    pred, npred = make_prediction("half", S[0], S[1], lens, k, n, np.random.default_rng(B))
-    s = ckv.shape_for(B, Hkv * G, Hkv, n)
-    full = lambda *x: torch.full(x, -9, dtype=torch.int32, device=dev)  # noqa: E731
-    idx_pred, n_pred = torch.from_numpy(pred).to(dev), torch.from_numpy(npred).to(dev)
-    kb = torch.zeros((B, Hkv, k, d), dtype=torch.bfloat16, device=dev)
-    vb = torch.zeros_like(kb)
-    out = torch.zeros((B, Hkv * G, d), device=dev)
-    ws = ckv.workspace(s, k, ckv.ENTRY_CORRECTED_ATTN)
-    ws.fill_(0xA5)
-    for call in range(2):
-        true, nxt = full(B, Hkv, k), full(B, Hkv, k)
-        n_true, n_next, hits = full(B, Hkv), full(B, Hkv), full(B, Hkv)
-        ckv.gather_kv(s, t["k"], t["v"], ckv.SRC_DEVICE, idx_pred, n_pred, k, kb, vb)
-        ckv.profile_begin()
-        ckv.corrected_attn(s, t["q"], t["q_sel"] if queries == 2 else None, t["k"], t["ctx_lens"],
-                           k, SCALE, t["k"], t["v"], ckv.SRC_DEVICE, idx_pred, n_pred, kb, vb,
-                           true, n_true, hits, nxt, n_next, out, ws)
-        stats = ckv.profile_end()
-        assert "zero" not in stats, stats
-        torch.cuda.synchronize()
-        check_index_sets(true.cpu().numpy(), n_true.cpu().numpy(), *want[0], S[0], lens)
-        check_index_sets(nxt.cpu().numpy(), n_next.cpu().numpy(), *want[1], S[1], lens)
-    ref = oracle_attn_over(so, q, u16(t["k"]), u16(t["v"]), true.cpu().numpy(),
-                           n_true.cpu().numpy(), k)
-    assert np.abs(out.cpu().numpy() - ref).max() <= ATOL_OUT
-
-
 def test_more_units_than_one_launch_selects():
     """The two selections of 2^21 + 8 units of one position: side by side they
     would take more work-items than a launch may have."""
