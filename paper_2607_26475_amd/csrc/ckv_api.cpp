@@ -380,6 +380,7 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
   a.hist_part = nullptr;
   a.score_nwg = 0;
   a.min_range = 1;
+  a.stored = d.B > kScanRequests;
   a.units = d.U;
   a.mpart = nullptr;
   a.mout = nullptr;
@@ -423,6 +424,7 @@ ScoreArgs score_args(const Dims& d, const Layout& L, const uint16_t* q,
   a.chunk = 1;
   a.hist_part = nullptr;
   a.min_range = sel ? kAddedMinRange : 1;  // slots set their own
+  a.stored = d.B > kScanRequests;
   a.tails = 0;
   a.q2 = nullptr;
   a.scores2 = nullptr;
@@ -1106,7 +1108,7 @@ int ckv::critical_impl(const ckv_shape* shape, const uint16_t* q_att, const uint
     const int one = g_one_launch.load();
     // row halves need a partial per half in the attention partials
     const bool rows = one == CKV_ONE_LAUNCH_ROW_HALVES && L.chunks >= 2;
-    if (S == 1 && heads == 2 && partials && L.flags && one &&
+    if (S == 1 && heads == 2 && partials && L.flags && one && !sa.stored &&
         critical_blocks(d.G, d.U, nwg, rows)) {
       // scoring, selection and attention in one launch, XCD-affine slots
       sa.affine = 1;

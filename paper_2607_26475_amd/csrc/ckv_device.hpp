@@ -97,6 +97,7 @@ struct ScoreArgs {
   int Hq, Hkv, max_ctx, units;
   int chunk;                // rows per scored entry: n_b rows give ceil(n_b/chunk) entries
   int min_range;            // fewest groups of a workgroup's range (range_groups)
+  int stored;               // ranges over stored positions (more than kScanRequests requests)
   int tails;                // write -inf to every score at or past n_b (score_keys)
   // A second query over the same keys in the same pass (the corrected
   // entries: the current and the speculative token), with its own scores and
@@ -116,7 +117,8 @@ struct SelectArgs {
   uint32_t* ctrl;           // [U][kCtrlWords]
   const uint32_t* hist_part;  // non-null: the scoring pass wrote per-workgroup
   int score_nwg;            //   histograms with a grid of score_nwg workgroups
-  int min_range;            //   and ranges of at least min_range groups
+  int min_range;            //   and ranges of at least min_range groups,
+  int stored;               //   over stored positions (ScoreArgs::stored)
   int units;
   int32_t* sel;             // [U][k]   positions above the digit-1 bin, then
                             //          the chosen candidates
@@ -409,66 +411,110 @@ __device__ __forceinline__ uint32_t groups_of(int n) {
   return ((uint32_t)n + ROWS - 1) / ROWS;
 }
 
+//
+// Lengths are read by every workgroup, so reading them must stay cheap for any
+// batch: lane l takes the `per` consecutive items from l * per on, so that its
+// loads do not wait for each other, and one scan over the lanes follows.  One
+// item needs no scan, and batches of more than kScanRequests requests count the
+// stored positions instead, alike for all (RangeLens::same): one workgroup per
+// unit reading thousands of lengths costs more than the ranges gain.  Same-step
+// calls of requests of a quarter to all of max_ctx, lengths against stored
+// positions: 512 requests of 1024 x 8 heads 395 / 386 us (score_keys 130 / 137,
+// corrected 639 / 651), 1024 of 512 x 8 701 / 601, 2048 of 512 x 4 789 / 597; a scan
+// per 64 requests took 8192 requests of 256 x 2 to 3562, stored positions take 991.
+constexpr int kScanRequests = 512;
+
+// What a range counts of each of ni items (mult units each): len(i) entries per
+// unit, or, with same >= 0, that many of every item.
+template <class LEN>
+struct RangeLens {
+  int ni;
+  int same;
+  LEN len;
+  __device__ __forceinline__ int operator()(int i) const {  // i: uniform
+    return same >= 0 ? same : __builtin_amdgcn_readfirstlane(len(i));
+  }
+};
+template <class LEN>
+__device__ __forceinline__ RangeLens<LEN> range_lens(int ni, int stored, LEN len) {
+  int same = stored;
+  if (ni == 1 && stored < 0) same = __builtin_amdgcn_readfirstlane(len(0));
+  return RangeLens<LEN>{ni, same, len};
+}
+
 struct GroupScan {
-  int n;       // entries per unit of this lane's item of the current 64
-  uint32_t s;  // inclusive sum of its groups
+  int per;     // items per lane
+  int n;       // with per 1: entries per unit of this lane's item
+  uint32_t g;  // groups of this lane's items, one unit each
+  uint32_t s;  // inclusive sum over the lanes
 };
 
-// Sum of the groups of ROWS positions of the ni items (one unit each); *first:
-// the scan of items 0..63.  len(i): item i's entries per unit.
+// Sum of the groups of ROWS positions of the items (one unit each), and its scan.
 template <int ROWS = kStageRows, class LEN>
-__device__ __forceinline__ uint32_t sum_groups(int ni, LEN len, GroupScan* first) {
+__device__ __forceinline__ uint32_t sum_groups(const RangeLens<LEN>& L, GroupScan* f) {
+  f->per = 0;
+  if (L.same >= 0) return (uint32_t)L.ni * groups_of<ROWS>(L.same);
   const int lane = threadIdx.x & 63;
-  first->n = lane < ni ? len(lane) : 0;
-  first->s = wave_incl_scan(groups_of<ROWS>(first->n));
-  uint32_t t = __builtin_amdgcn_readlane(first->s, 63);
-  for (int i0 = 64; i0 < ni; i0 += 64)
-    t += wave_sum_u32(i0 + lane < ni ? groups_of<ROWS>(len(i0 + lane)) : 0u);
-  return t;
-}
-
-// Groups before item `item` (of one unit per item), and its entries in *n.
-template <class LEN>
-__device__ __forceinline__ uint32_t groups_before(int item, LEN len, GroupScan first, int* n) {
-  const int lane = threadIdx.x & 63;
-  uint32_t base = 0u;
-  int i0 = 0;
-  for (; item >= i0 + 64;) {
-    base += __builtin_amdgcn_readlane(first.s, 63);
-    i0 += 64;
-    first.n = i0 + lane <= item ? len(i0 + lane) : 0;  // items past `item` are not needed
-    first.s = wave_incl_scan(groups_of(first.n));
+  f->per = 1;
+  if (L.ni <= 64) {
+    f->n = lane < L.ni ? L.len(lane) : 0;
+    f->g = groups_of<ROWS>(f->n);
+  } else {
+    f->per = (L.ni + 63) >> 6;
+    f->n = 0;
+    f->g = 0u;
+#pragma unroll 4
+    for (int j = 0; j < f->per; ++j) {
+      const int i = lane * f->per + j;
+      const int n = L.len(min(i, L.ni - 1));  // unconditional loads
+      f->g += i < L.ni ? groups_of<ROWS>(n) : 0u;
+    }
   }
-  const int l = __builtin_amdgcn_readfirstlane(item - i0);
-  *n = __builtin_amdgcn_readlane(first.n, l);
-  return base + __builtin_amdgcn_readlane(first.s, l) - groups_of(*n);
+  f->s = wave_incl_scan(f->g);
+  return __builtin_amdgcn_readlane(f->s, 63);
 }
 
-// The item that holds group g (g below mult * the sum): its number, the
-// entries and groups of one of its units, and its first group.
+// The item that holds group g (g below mult * the sum): its number, the entries
+// and groups that count of one of its units, and its first group.
 struct GroupItem {
   int item, n;
   uint32_t vg, base;
 };
 template <int ROWS = kStageRows, class LEN>
-__device__ __forceinline__ GroupItem find_item(int ni, LEN len, GroupScan first, uint32_t mult,
-                                               uint32_t g) {
-  const int lane = threadIdx.x & 63;
-  uint32_t base = 0u;
-  int i0 = 0;
-  while (i0 + 64 < ni && g >= base + mult * __builtin_amdgcn_readlane(first.s, 63)) {
-    base += mult * __builtin_amdgcn_readlane(first.s, 63);
-    i0 += 64;
-    first.n = i0 + lane < ni ? len(i0 + lane) : 0;
-    first.s = wave_incl_scan(groups_of<ROWS>(first.n));
-  }
-  const uint64_t past = __ballot(base + mult * first.s > g);
-  const int l = past ? __ffsll((unsigned long long)past) - 1 : 63;
+__device__ __forceinline__ GroupItem find_item(const RangeLens<LEN>& L, const GroupScan& f,
+                                               uint32_t mult, uint32_t g) {
   GroupItem r;
+  if (L.same >= 0) {
+    r.n = L.same;
+    r.vg = groups_of<ROWS>(r.n);
+    r.item = (int)(g / (mult * r.vg));
+    r.base = (uint32_t)r.item * mult * r.vg;
+    return r;
+  }
+  const int lane = threadIdx.x & 63;
+  auto first_past = [&](uint32_t base, uint32_t s) {
+    const uint64_t past = __ballot(base + mult * s > g);
+    return past ? __ffsll((unsigned long long)past) - 1 : 64;
+  };
+  int l = min(first_past(0u, f.s), 63), i0 = 0, n = f.n;
+  uint32_t base = 0u, s = f.s;
+  if (f.per > 1) {  // then among that lane's items
+    i0 = l * f.per;
+    base = mult * (__builtin_amdgcn_readlane(f.s, l) - __builtin_amdgcn_readlane(f.g, l));
+    const int end = min(i0 + f.per, L.ni);
+    for (;; i0 += 64) {
+      n = i0 + lane < end ? L.len(i0 + lane) : 0;
+      s = wave_incl_scan(groups_of<ROWS>(n));
+      l = first_past(base, s);
+      if (l < 64 || i0 + 64 >= end) break;
+      base += mult * __builtin_amdgcn_readlane(s, 63);
+    }
+    l = min(l, 63);
+  }
   r.item = i0 + l;
-  r.n = __builtin_amdgcn_readlane(first.n, l);
+  r.n = __builtin_amdgcn_readlane(n, l);
   r.vg = groups_of<ROWS>(r.n);
-  r.base = base + mult * (__builtin_amdgcn_readlane(first.s, l) - r.vg);
+  r.base = base + mult * (__builtin_amdgcn_readlane(s, l) - r.vg);
   return r;
 }
 
@@ -512,15 +558,39 @@ __device__ __forceinline__ SlotRange hist_slots(const SelectArgs& a, int unit) {
   const uint32_t mult = a.affine ? 1u : (uint32_t)a.Hkv;
   const int item = a.affine ? (unit >> 3) : unit / a.Hkv;
   const uint32_t h = a.affine ? 0u : (uint32_t)(unit - item * a.Hkv);
-  auto len = [&](int i) {
+  auto valid = [&](int i) {
     return unit_len(a.ctx_lens[a.affine ? (8 * i + x) / a.Hkv : i], a.max_ctx, a.chunk);
   };
-  GroupScan first;
-  const uint32_t R = range_groups(mult * sum_groups(ni, len, &first), nwg, a.min_range);
-  int n;
-  const uint32_t before = groups_before(item, len, first, &n);
-  const uint32_t mine = groups_of(n), g0 = mult * before + h * mine;
-  const uint32_t lo = g0 / R, hi = (g0 + mine - 1u) / R;
+  const auto len = range_lens(ni, a.stored ? a.max_ctx : -1, valid);
+  const int lane = threadIdx.x & 63;
+  // groups per unit of all items and of this one, and those before the unit
+  uint32_t total, mine, before;
+  if (len.same >= 0) {
+    const uint32_t each = groups_of(len.same);
+    total = (uint32_t)ni * each;
+    mine = a.stored ? groups_of(__builtin_amdgcn_readfirstlane(valid(item))) : each;
+    before = (mult * (uint32_t)item + h) * each;
+  } else if (ni <= 64) {
+    const uint32_t g = lane < ni ? groups_of(valid(lane)) : 0u, s = wave_incl_scan(g);
+    const int l = __builtin_amdgcn_readfirstlane(item);
+    total = __builtin_amdgcn_readlane(s, 63);
+    mine = __builtin_amdgcn_readlane(g, l);
+    before = mult * (__builtin_amdgcn_readlane(s, l) - mine) + h * mine;
+  } else {
+    uint32_t all = 0u, low = 0u;
+#pragma unroll 4
+    for (int i0 = 0; i0 < ni; i0 += 64) {
+      const int i = i0 + lane;
+      const uint32_t g = groups_of(valid(min(i, ni - 1)));  // unconditional loads
+      all += i < ni ? g : 0u;
+      low += i < item ? g : 0u;
+    }
+    total = wave_sum_u32(all);
+    mine = groups_of(__builtin_amdgcn_readfirstlane(valid(item)));
+    before = mult * wave_sum_u32(low) + h * mine;
+  }
+  const uint32_t R = range_groups(mult * total, nwg, a.min_range);
+  const uint32_t lo = before / R, hi = (before + mine - 1u) / R;
   return SlotRange{a.affine ? (int64_t)x * (ni + nwg) + item + lo : (int64_t)unit + lo,
                    mine ? (int)(hi - lo + 1u) : 0};
 }

@@ -155,22 +155,42 @@ __device__ __forceinline__ void load_query(const ScoreArgs& a, int unit, bf16x8*
   }
 }
 
-// Scores of positions [32 * first, max_ctx) rows past the units' last valid
-// groups: -inf, in equal shares of the stored groups (all threads of the
-// workgroup; only score_keys, whose output has those rows, needs them).
+// Scores of the groups past the units' last valid ones: -inf, in equal shares
+// of the stored groups (all threads of the workgroup; only score_keys, whose
+// output has those rows, needs them).  Each lane looks at one group, so that a
+// batch without such groups pays for little more than one look at the lengths;
+// then eight lanes write each group found, one 128-byte line.
 __device__ __forceinline__ void fill_tails(const ScoreArgs& a, int wg, int nwg) {
-  const int64_t gu = (a.max_ctx + kStageRows - 1) / kStageRows;
-  const int64_t total = (int64_t)a.units * gu;
-  const int64_t t0 = total * wg / nwg, t1 = total * (wg + 1) / nwg;
-  for (int64_t t = t0; t < t1;) {
-    const int unit = (int)(t / gu);
-    const int64_t ubase = (int64_t)unit * gu, end = min(t1, ubase + gu);
-    const int64_t vg = groups_of(unit_len(a.ctx_lens[unit / a.Hkv], a.max_ctx, a.chunk));
-    float* srow = a.scores + (int64_t)unit * a.max_ctx;
-    const int64_t j1 = min((end - ubase) * kStageRows, (int64_t)a.max_ctx);
-    for (int64_t j = max(t - ubase, vg) * kStageRows + threadIdx.x; j < j1; j += blockDim.x)
-      srow[j] = -INFINITY;
-    t = end;
+  static_assert(kStageRows == 32, "eight lanes of four rows per group");
+  const int lane = threadIdx.x & 63;
+  const uint32_t gu = groups_of(a.max_ctx);
+  const uint32_t total = (uint32_t)a.units * gu;
+  const uint32_t share = (total + (uint32_t)nwg - 1u) / (uint32_t)nwg;
+  const uint32_t t0 = (uint32_t)wg * share, t1 = min(t0 + share, total);
+  for (uint32_t tw = t0 + threadIdx.x - lane; tw < t1; tw += blockDim.x) {  // wave-uniform
+    const uint32_t t = min(tw + lane, t1 - 1u), unit = t / gu;
+    const int g = (int)(t - unit * gu);
+    const int n = unit_len(a.ctx_lens[unit / (uint32_t)a.Hkv], a.max_ctx, a.chunk);
+    const uint64_t tails = __ballot(tw + lane < t1 && g >= (int)groups_of(n));
+    if (!tails) continue;
+#pragma unroll
+    for (int r = 0; r < 64; r += 8) {
+      const int src = r + (lane >> 3);
+      if (!((tails >> r) & 0xffu)) continue;  // uniform
+      const int64_t row = (int64_t)__shfl((int)unit, src) * a.max_ctx;
+      const int j = __shfl(g, src) * kStageRows + 4 * (lane & 7);
+      if (!((tails >> src) & 1u)) continue;
+      float* const at = a.scores + row + j;
+      if ((a.max_ctx & 3) == 0) {
+        if (j < a.max_ctx)
+          *reinterpret_cast<float4*>(at) =
+              make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (j + i < a.max_ctx) at[i] = -INFINITY;
+      }
+    }
   }
 }
 
@@ -243,17 +263,20 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
   const int wr = FUSED ? (wg >> 3) : wg, nwr = FUSED ? (nwg >> 3) : nwg;
   const int items = FUSED ? (a.units >> 3) : a.units / a.Hkv;
   const uint32_t mult = FUSED ? 1u : (uint32_t)a.Hkv;
-  auto len = [&](int i) {
-    const int n = unit_len(a.ctx_lens[FUSED ? (8 * i + xcd) / a.Hkv : i], a.max_ctx, a.chunk);
-    return PART ? static_rows(n) : n;
+  auto valid = [&](int i) {
+    return unit_len(a.ctx_lens[FUSED ? (8 * i + xcd) / a.Hkv : i], a.max_ctx, a.chunk);
   };
-  GroupScan first_items;
-  const uint32_t total = mult * sum_groups(items, len, &first_items);
+  auto part = [](int n) { return PART ? static_rows(n) : n; };
+  // the fused role has too few requests for stored ranges
+  const auto len = range_lens(items, !FUSED && a.stored ? part(a.max_ctx) : -1,
+                              [&](int i) { return part(valid(i)); });
+  GroupScan scan;
+  const uint32_t total = mult * sum_groups(len, &scan);
   const uint32_t R = range_groups(total, nwr, a.min_range);
   const uint32_t g0 = (uint32_t)min((uint64_t)wr * R, (uint64_t)total);
   const uint32_t g1 = (uint32_t)min((uint64_t)g0 + R, (uint64_t)total);
   if (g0 >= g1) return;  // uniform over the workgroup
-  GroupItem it = find_item(items, len, first_items, mult, g0);
+  GroupItem it = find_item(len, scan, mult, g0);
   uint32_t* stage = lds_stage + (active ? wave : 0) * kStageDwords;
   float* sbuf = reinterpret_cast<float*>(lds_stage + NW * kStageDwords) +
                 (active ? wave : 0) * kFlushGroups * kStageRows;
@@ -271,8 +294,17 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
     const int64_t slot =
         FUSED ? (int64_t)xcd * (items + nwr) + it.item + wr : (int64_t)unit + wg;
     const uint32_t ubase = it.base + h * it.vg;
-    const uint32_t seg_end = min(g1, ubase + it.vg);
-    const int n = it.n;
+    uint32_t seg_end = min(g1, ubase + it.vg);
+    int n = it.n;
+    if (!FUSED && a.stored) {  // the groups of the range below n_b, if any
+      n = min(n, (int)__builtin_amdgcn_readfirstlane(valid(it.item)));
+      const uint32_t next = seg_end;
+      seg_end = min(seg_end, ubase + groups_of(n));
+      if (seg >= seg_end) {  // uniform over the workgroup
+        seg = next;
+        continue;
+      }
+    }
     if (HIST) {
       if (!FUSED || tid < NT)
         for (int i = tid; i < kSets * kHistBins; i += NT) lds_hist[i] = 0u;
@@ -394,7 +426,7 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
       }
       __syncthreads();
     }
-    seg = seg_end;
+    seg = ubase + it.vg;
   }
   if constexpr (FUSED) {
     // every slot of the range handed over at its end, after one wait for all
@@ -407,7 +439,7 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
     const int64_t slot0 = (int64_t)xcd * (items + nwr) + wr;
     for (int t = tid; t < 2 * (it.item - item0 + 1); t += blockDim.x) {
       const int i = item0 + (t >> 1);
-      if (len(i))
+      if (valid(i))
         __hip_atomic_store(fs.flags + 2 * (slot0 + i) + (t & 1), fs.tag, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -461,12 +493,11 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
   const int items = a.units / a.Hkv;
   const uint32_t mult = (uint32_t)a.Hkv;
   auto full = [&](int i) { return unit_len(a.ctx_lens[i], a.max_ctx, a.chunk); };
-  auto len = [&](int i) {
-    const int n = full(i);
-    return n - static_rows(n);
-  };
-  GroupScan first_items;
-  const uint32_t total = mult * sum_groups<kClaimRows>(items, len, &first_items);
+  auto part = [](int n) { return n - static_rows(n); };
+  const auto len = range_lens(items, a.stored ? part(a.max_ctx) : -1,
+                              [&](int i) { return part(full(i)); });
+  GroupScan scan;
+  const uint32_t total = mult * sum_groups<kClaimRows>(len, &scan);
   uint32_t* stage = lds_stage + wave * kStageDwords;
   float* sbuf = reinterpret_cast<float*>(lds_stage + 4 * kStageDwords) +
                 wave * kFlushGroups * kStageRows;
@@ -476,17 +507,18 @@ __device__ __forceinline__ void score_claims(const ScoreArgs& a, int nwg, uint32
   auto last_resets = [&](uint32_t c) {
     if (c == total + (uint32_t)nwg - 1u) atomicExch(a.claim, 0u);
   };
-  // a claim's unit, valid length, and groups [g0, v1)
+  // a claim's unit, valid length, and groups [g0, v1), none if it lies past n_b
   struct Geo {
     int unit, n, g0, v1;
   };
   auto geo = [&](uint32_t c) {
-    const GroupItem it = find_item<kClaimRows>(items, len, first_items, mult, c);
+    const GroupItem it = find_item<kClaimRows>(len, scan, mult, c);
     const uint32_t h = (c - it.base) / it.vg;
     Geo r;
     r.unit = it.item * a.Hkv + (int)h;
-    r.n = full(it.item);
-    r.g0 = (r.n - it.n) / kStageRows + (int)(c - it.base - h * it.vg) * kClaimGroups;
+    r.n = __builtin_amdgcn_readfirstlane(full(it.item));
+    r.g0 = static_rows(a.stored ? a.max_ctx : r.n) / kStageRows +
+           (int)(c - it.base - h * it.vg) * kClaimGroups;
     r.v1 = min(r.g0 + kClaimGroups, (int)groups_of(r.n));
     return r;
   };
