@@ -254,35 +254,45 @@ __device__ __forceinline__ uint32_t emit_bitmap(const uint32_t* bm, int words, i
 }
 
 // Radix select among the candidates, which cs.each(f) presents as f(order key,
-// position), each by one of the NT threads; all share the first digit b1: the
-// need largest by (key descending, position ascending).
-// Returns the threshold key T; candidates with key > T are all chosen, and of
-// those equal to T the ones with position <= *pmax.  All NT threads call
-// this; hist needs 2048 words, misc 4.
+// position), each by one of the NT threads: the need largest by (key
+// descending, position ascending).  Both steps are called by all NT threads;
+// hist needs 2048 words, misc 4.
+//
+// First step: the second digit, bits 20..10 of the order key (11 bits), of
+// candidates that share the first.  Returns the digit of the threshold and takes
+// the candidates above it off *need.
 template <int NT, class Cands>
-__device__ __forceinline__ uint32_t refine_threshold(const Cands& cs, uint32_t need, uint32_t b1,
-                                                     uint32_t* hist, uint32_t* tmp,
-                                                     uint32_t* misc, uint32_t* pmax) {
+__device__ __forceinline__ uint32_t refine_digit2(const Cands& cs, uint32_t* need, uint32_t* hist,
+                                                  uint32_t* misc) {
   const int tid = threadIdx.x;
-  // Second digit: bits 20..10 of the order key (11 bits).
   static_assert(kHistBits == 11, "digits 11 + 11 + 10");
   for (int i = tid; i < 2048; i += NT) hist[i] = 0u;
   __syncthreads();
   cs.each([&](uint32_t key, uint32_t) { atomicAdd(&hist[(key >> 10) & 2047u], 1u); });
   __syncthreads();
-  if (tid < 64) find_first_bin_lds<2048>(hist, need, misc);
+  if (tid < 64) find_first_bin_lds<2048>(hist, *need, misc);
   __syncthreads();
-  const uint32_t b2 = misc[0], need2 = need - misc[1];
-  // Third digit: bits 9..0, among candidates whose second digit is b2.
+  *need -= misc[1];
+  return misc[0];
+}
+
+// Second step: the third digit, bits 9..0, of the candidates whose first two are
+// b12, and ties.  Returns the threshold key T; candidates with key > T are all
+// chosen, and of those equal to T the ones with position <= *pmax.
+template <int NT, class Cands>
+__device__ __forceinline__ uint32_t refine_rest(const Cands& cs, uint32_t need2, uint32_t b12,
+                                                uint32_t* hist, uint32_t* tmp, uint32_t* misc,
+                                                uint32_t* pmax) {
+  const int tid = threadIdx.x;
   for (int i = tid; i < 1024; i += NT) hist[i] = 0u;
   __syncthreads();
   cs.each([&](uint32_t key, uint32_t) {
-    if (((key >> 10) & 2047u) == b2) atomicAdd(&hist[key & 1023u], 1u);
+    if (key >> 10 == b12) atomicAdd(&hist[key & 1023u], 1u);
   });
   __syncthreads();
   if (tid < 64) find_first_bin_lds<1024>(hist, need2, misc);
   __syncthreads();
-  const uint32_t T = (b1 << 21) | (b2 << 10) | misc[0];
+  const uint32_t T = (b12 << 10) | misc[0];
   const uint32_t need3 = need2 - misc[1], eq = misc[2];  // eq candidates have key T
 
   // Ties at T: keep the need3 lowest positions (radix select on position,
@@ -392,9 +402,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(SelectArgs a) {
     // the positions that the filter selected outright
     const int32_t* sel = a.sel + (int64_t)unit * a.k;
     for (uint32_t i = tid; i < above; i += kFinishThreads) mark((uint32_t)sel[i]);
-    uint32_t pmax;
-    const uint32_t T =
-        refine_threshold<kFinishThreads>(cs, need, b1, hist, tmp, misc, &pmax);
+    uint32_t pmax, need2 = need;
+    const uint32_t b2 = refine_digit2<kFinishThreads>(cs, &need2, hist, misc);
+    const uint32_t T = refine_rest<kFinishThreads>(cs, need2, (b1 << 11) | b2, hist, tmp, misc,
+                                                   &pmax);
     cs.each([&](uint32_t key, uint32_t pos) {
       if (key > T || (key == T && pos <= pmax)) mark(pos);
     });
@@ -442,9 +453,13 @@ __device__ __forceinline__ void load_score_chunk(const float* srow, int j0, int 
 // Candidates of the one-workgroup selection: (fp32 bits, position) in LDS,
 // each wave's in its own segment (no reservation; the waves' positions are
 // interleaved, so the segments fill alike).  When a wave has more than its
-// segment holds (heavy ties) the lists are not used: every position is looked
-// at again (RescanCands), which needs no memory and costs a pass over the
-// unit's scores (256 KiB at most) per digit.
+// segment holds (crowded scores: a first-digit bin is a quarter of an octave)
+// the second digit is counted over all positions (BinScores) and the lists are
+// made again from the bin of both digits.  Only where they are too many again
+// (heavy ties) are they looked up among all positions for every digit
+// (RescanCands), which needs no memory.  Looking up at once, 8 units of 65536
+// scores of mean 10 and spread 1 took select_topk 62 us and the same-step call
+// 94; listed again they take 39 and 71 (equal scores: 334 either way).
 template <int NT, int CAP>
 struct LdsCands {
   static constexpr uint32_t kSeg = CAP / (NT / 64);
@@ -473,6 +488,32 @@ struct RescanCands {
         x = srow[i];
       const uint32_t key = order_key(x);
       if (key >> (32 - kHistBits) == b1 && x == x) f(key, i);
+    }
+  }
+};
+
+// The same positions in one streaming pass: those in [g_lo, g_hi), one chunk in
+// flight while the other is looked at.
+template <int NT, bool COH>
+struct BinScores {
+  const float* srow;
+  int n;
+  float g_lo, g_hi;
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+    constexpr int kChunk = kSelRounds * NT;
+    float x[2][kSelRounds];
+    load_score_chunk<NT, COH>(srow, 0, n, x[0]);
+#pragma unroll 1
+    for (int j0 = 0; j0 < n; j0 += kChunk) {
+      load_score_chunk<NT, COH>(srow, j0 + kChunk, n, x[1]);
+#pragma unroll
+      for (int u = 0; u < kSelRounds; ++u) {
+        const int i = j0 + u * NT + (int)threadIdx.x;
+        const float v = x[0][u];
+        if (i < n && v >= g_lo && !(v >= g_hi)) f(order_key(v), (uint32_t)i);
+        x[0][u] = x[1][u];
+      }
     }
   }
 };
@@ -704,8 +745,8 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
   LdsCands<NT, CAP> cs{
       reinterpret_cast<uint2*>(L.cand) + wave * LdsCands<NT, CAP>::kSeg, 0u};
   const uint32_t b1 = misc[4], above = misc[5];
-  const float g_lo = __uint_as_float(key_floor_bits((uint64_t)b1 << (32 - kHistBits)));
-  const float g_hi = __uint_as_float(key_floor_bits((uint64_t)(b1 + 1u) << (32 - kHistBits)));
+  float g_lo = __uint_as_float(key_floor_bits((uint64_t)b1 << (32 - kHistBits)));
+  float g_hi = __uint_as_float(key_floor_bits((uint64_t)(b1 + 1u) << (32 - kHistBits)));
   // classifies chunk c of the batch at j0 (positions at or past n_b as NaN)
   auto classify = [&](float (&x)[kSelRounds], int j0) {
     if (j0 >= n) return;
@@ -725,15 +766,38 @@ __device__ __forceinline__ int select_unit(const SelectArgs& a, int unit, const 
     }
 #pragma unroll
   for (int c = 0; c < kSelChunks; ++c) classify(sv[c], j0 + c * kChunk);
-  if ((tid & 63) == 0) tmp[wave] = cs.count;
-  __syncthreads();
-  bool listed = true;  // every wave's candidates are in its segment
+  auto all_listed = [&]() {  // every wave's candidates are in its segment
+    if ((tid & 63) == 0) tmp[wave] = cs.count;
+    __syncthreads();
+    bool listed = true;
 #pragma unroll
-  for (int w = 0; w < NT / 64; ++w) listed &= tmp[w] <= LdsCands<NT, CAP>::kSeg;
-  const uint32_t need = (uint32_t)m - above;
+    for (int w = 0; w < NT / 64; ++w) listed &= tmp[w] <= LdsCands<NT, CAP>::kSeg;
+    return listed;
+  };
+  bool listed = all_listed();
+  uint32_t need = (uint32_t)m - above, b12 = b1 << 11;
+  if (listed) {
+    b12 |= refine_digit2<NT>(cs, &need, lhist, misc);
+  } else {
+    b12 |= refine_digit2<NT>(BinScores<NT, COH>{srow, n, g_lo, g_hi}, &need, lhist, misc);
+    if (misc[2] <= (uint32_t)CAP) {  // the positions in the bin of both digits
+      g_lo = __uint_as_float(key_floor_bits((uint64_t)b12 << 10));
+      g_hi = __uint_as_float(key_floor_bits((uint64_t)(b12 + 1u) << 10));
+      cs.count = 0u;
+      load_score_chunk<NT, COH>(srow, 0, n, sv[0]);
+#pragma unroll 1
+      for (int j = 0; j < n; j += kChunk) {
+        load_score_chunk<NT, COH>(srow, j + kChunk, n, sv[1]);
+        classify(sv[0], j);
+#pragma unroll
+        for (int u = 0; u < kSelRounds; ++u) sv[0][u] = sv[1][u];
+      }
+      listed = all_listed();
+    }
+  }
   auto resolve = [&](const auto& cands) {
     uint32_t pmax;
-    const uint32_t T = refine_threshold<NT>(cands, need, b1, lhist, tmp, misc, &pmax);
+    const uint32_t T = refine_rest<NT>(cands, need, b12, lhist, tmp, misc, &pmax);
     cands.each([&](uint32_t key, uint32_t pos) {
       if (key > T || (key == T && pos <= pmax)) atomicOr(&bm[pos >> 5], 1u << (pos & 31));
     });
