@@ -1,7 +1,8 @@
 """select_topk past 65536 positions (MI355X only): the filter's tiles of 16384
 positions, the finish's candidates in registers and in its list, and the
 ordered output from LDS and memory bitmaps whose word counts are not multiples
-of 4, sparse and dense.  Exactly the oracle's sets on the same scores."""
+of 4 or 32, sparse and dense, and on both sides of the selection of a position in
+16 that tells them apart.  Exactly the oracle's sets on the same scores."""
 from __future__ import annotations
 
 import numpy as np
@@ -14,7 +15,8 @@ from helpers import device, orc
 pytestmark = pytest.mark.gpu
 
 CASES = [(65537, 1), (70003, 30000), (81920, 4096), (81921, 81000), (131072, 2048),
-         (1048575, 9000), (1048643, 40000)]
+         (1048575, 9000), (1048643, 40000), (65600, 4099), (65600, 4100), (65600, 4102),
+         (1048545, 400000), (1048643, 700000)]
 
 
 @pytest.mark.parametrize("n,k", CASES)
