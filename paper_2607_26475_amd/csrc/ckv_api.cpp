@@ -394,7 +394,18 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
 // of 124 Ki positions (3886 groups), attend-and-score launch: 8 groups per
 // range 51 us, 16: 32, 24: 26.6, 32: 25; 3 units of 34 to 124 Ki, two tokens:
 // 18 groups 38, 19: 32, 24: 29, 32: 27.3.  Large batches have longer ranges.
+// Units of few groups keep at least kAddedUnitRanges ranges, as ranges of 32
+// leave workgroups without work then.  32 units of 6000 positions, pipelined, at
+// least 2, 12, 16, 24 and 32 groups: 29.8, 30.3, 26.6, 29.2, 30.9 us; chunked in 8 (24
+// groups per unit), 2 and 32 groups: 25.2, 33.5; of 12000, pipelined, 24 and 32:
+// 39.1, 35.7.
 constexpr int kAddedMinRange = 32;
+constexpr int kAddedUnitRanges = 12;
+
+int added_min_range(int max_ctx) {
+  const int gu = (max_ctx + kStageRows - 1) / kStageRows;
+  return std::min(kAddedMinRange, (gu + kAddedUnitRanges - 1) / kAddedUnitRanges);
+}
 
 // Scoring arguments; with sel set, the pass counts the first digit into that
 // selection's histograms, and a pipelined launch with enough work may take
@@ -423,7 +434,7 @@ ScoreArgs score_args(const Dims& d, const Layout& L, const uint16_t* q,
   a.units = d.U;
   a.chunk = 1;
   a.hist_part = nullptr;
-  a.min_range = sel ? kAddedMinRange : 1;  // slots set their own
+  a.min_range = sel ? added_min_range(d.max_ctx) : 1;  // slots set their own
   a.stored = d.B > kScanRequests;
   a.tails = 0;
   a.q2 = nullptr;
