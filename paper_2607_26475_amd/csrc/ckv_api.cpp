@@ -348,6 +348,7 @@ ReconArgs recon_args(const Dims& d, int32_t rank, const uint16_t* u_fac, const u
   r.max_ctx = d.max_ctx;
   r.k = k;
   r.rank = rank;
+  r.units = d.U;
   return r;
 }
 

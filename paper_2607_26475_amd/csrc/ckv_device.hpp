@@ -75,6 +75,7 @@ constexpr int kGatherUnroll = 4;
 // the factors staged at a time.
 constexpr int kRecRows = 32;
 constexpr int kRecRanks = 64;
+constexpr int kRecFewRanks = 8;  // up to so many, one thread per 8 channels of a key
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -217,7 +218,7 @@ struct ReconArgs {
   const int32_t* slots;     // [U][k] destination slot of entry i; NULL: slot i
   uint16_t* k_dst;          // [U][k][d]
   int64_t tiles;            // U * ceil(k / kRecRows)
-  int max_ctx, k, rank;
+  int max_ctx, k, rank, units;
 };
 
 // Rows of the selected chunks.

@@ -1752,9 +1752,47 @@ __device__ __forceinline__ void reconstruct_range(const ReconArgs& a, int blk, i
   }
 }
 
+// Up to kRecFewRanks ranks: one thread sums 8 channels of a key in order.  A tile's
+// staging and its chain of waits cost more than so few products: 128 units of 500
+// keys, rank 1, 3, 8 and 16, per thread 15.1, 17.7, 23.4 and 33.1 us, in tiles
+// 30.7, 31.2, 30.0 and 29.9.
+__device__ __forceinline__ void reconstruct_few(const ReconArgs& a, int blk, int nblk) {
+  const int64_t stride = (int64_t)nblk * kGatherThreads, items = (int64_t)a.units * a.k * 16;
+  for (int64_t it = (int64_t)blk * kGatherThreads + threadIdx.x; it < items; it += stride) {
+    const int part = (int)(it & 15);
+    const int64_t entry = it >> 4, unit = entry / a.k;
+    const int i = (int)(entry - unit * a.k);
+    if (i >= clamp_len(a.n_sel[unit], a.k)) continue;
+    const int row = a.idx[entry];
+    const int di = a.slots ? a.slots[entry] : i;
+    if (row < 0 || row >= a.max_ctx || di < 0 || di >= a.k) continue;
+    const uint16_t* u = a.u_fac + (unit * a.max_ctx + row) * a.rank;
+    const uint16_t* w = a.w_fac + unit * a.rank * kD + 8 * part;
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int j = 0; j < a.rank; ++j) {
+      const double uj = (double)__uint_as_float((uint32_t)u[j] << 16);
+      float wf[8];
+      unpack8(ld16(w + (int64_t)j * kD), wf);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += uj * (double)wf[e];
+    }
+    uint32_t o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      o[e] = (uint32_t)f64_to_bf16_rne(acc[2 * e]) |
+             ((uint32_t)f64_to_bf16_rne(acc[2 * e + 1]) << 16);
+    *reinterpret_cast<uint4*>(a.k_dst + (unit * a.k + di) * kD + 8 * part) =
+        make_uint4(o[0], o[1], o[2], o[3]);
+  }
+}
+
 __global__ __launch_bounds__(kGatherThreads) void k_reconstruct(ReconArgs a) {
   __shared__ __attribute__((aligned(16))) RecLds lds;
   reconstruct_range(a, blockIdx.x, gridDim.x, lds);
+}
+
+__global__ __launch_bounds__(kGatherThreads) void k_reconstruct_few(ReconArgs a) {
+  reconstruct_few(a, blockIdx.x, gridDim.x);
 }
 
 // ---- miss detection as a launch of its own -------------------------------------
@@ -1838,6 +1876,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_miss_fill(GatherArgs g, Reco
   __shared__ __attribute__((aligned(16))) RecLds lds;
   if ((int)blockIdx.x < nfetch)
     gather_range(g, blockIdx.x, nfetch);
+  else if (r.rank <= kRecFewRanks)  // uniform
+    reconstruct_few(r, blockIdx.x - nfetch, gridDim.x - nfetch);
   else
     reconstruct_range(r, blockIdx.x - nfetch, gridDim.x - nfetch, lds);
 }
@@ -2330,16 +2370,24 @@ hipError_t launch_landmarks(const LandmarkArgs& a, hipStream_t s) {
   return launch_status();
 }
 
+static int reconstruct_blocks(const ReconArgs& a) {
+  return a.rank <= kRecFewRanks ? blocks_for((int64_t)a.units * a.k * 16, kGatherThreads, 8192)
+                                : blocks_for(a.tiles, 1, 8192);
+}
+
 hipError_t launch_reconstruct(const ReconArgs& a, hipStream_t s) {
-  const int blocks = blocks_for(a.tiles, 1, 8192);
-  launch_kernel(CKV_K_RECONSTRUCT, k_reconstruct, dim3(blocks), dim3(kGatherThreads), s, a);
+  const dim3 grid(reconstruct_blocks(a)), block(kGatherThreads);
+  if (a.rank <= kRecFewRanks)
+    launch_kernel(CKV_K_RECONSTRUCT, k_reconstruct_few, grid, block, s, a);
+  else
+    launch_kernel(CKV_K_RECONSTRUCT, k_reconstruct, grid, block, s, a);
   return launch_status();
 }
 
 hipError_t launch_miss_fill(const GatherArgs& g, int fetch_blocks, const ReconArgs& r,
                             hipStream_t s) {
   const int nf = blocks_for(g.items, kGatherThreads * kGatherUnroll, fetch_blocks);
-  const int nr = blocks_for(r.tiles, 1, 8192);
+  const int nr = reconstruct_blocks(r);
   launch_kernel(CKV_K_RECONSTRUCT, k_miss_fill, dim3(nf + nr), dim3(kGatherThreads), s, g, r,
                 nf);
   return launch_status();

@@ -1,4 +1,5 @@
-"""Rebuilt keys at the edges of the matrix tiles (MI355X only): row counts
+"""Rebuilt keys at the edges of the matrix tiles and of the ranks summed per
+thread instead (up to 8) (MI355X only): row counts
 around 32, ranks around the 4 of a product and the 64 staged at a time, odd
 ranks (rows that do not start on 16 bytes), bit for bit against the oracle's
 ordered fp64 sums, with factors whose magnitudes spread over 2^40 so that the
@@ -19,7 +20,8 @@ from helpers import device, orc, u16
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rank,counts", [(3, [1, 31]), (4, [32, 33]), (63, [64, 65]),
+@pytest.mark.parametrize("rank,counts", [(1, [70, 33]), (3, [1, 31]), (4, [32, 33]),
+                                         (8, [33, 70]), (9, [64, 33]), (63, [64, 65]),
                                          (64, [70, 0]), (65, [31, 32]), (72, [33, 70]),
                                          (130, [70, 15]), (200, [17, 64])])
 def test_reconstruct_tiles(rank, counts):
