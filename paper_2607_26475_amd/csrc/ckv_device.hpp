@@ -71,6 +71,9 @@ constexpr int kSelAttnMaxSplit = 8;
 constexpr int kGatherThreads = 256;
 constexpr int kGatherUnroll = 4;
 
+// Chunk landmarks: rows a thread requests before it adds the first, at most.
+constexpr int kLandmarkRows = 16;
+
 // Key reconstruction: a workgroup rebuilds kRecRows rows, kRecRanks ranks of
 // the factors staged at a time.
 constexpr int kRecRows = 32;

@@ -1561,10 +1561,13 @@ __device__ __forceinline__ uint16_t f64_to_bf16_rne(double x) {
 // One item = 8 channels of one landmark: the fp64 sum of the chunk's rows
 // below n_b in row order, divided by their count, rounded once to bf16.  A pass
 // over the keys, bound by how much of it is in flight: a thread requests BATCH
-// rows (the power of two from the chunk size up, at most 16) before it adds the
-// first, streaming past the caches.  32 units of 30 to 64 Ki positions, chunks
-// of 8 rows: 92 -> 78 us (5.6 TB/s), of 64 rows 105 -> 82, single rows 237 -> 187
-// (there the eight fp64 divisions per item, which a power of two does not need).
+// rows before it adds the first, streaming past the caches.  32 units of 30 to 64
+// Ki positions, chunks of 8 rows: 92 -> 78 us (5.6 TB/s), of 64 rows 105 -> 82,
+// single rows 237 -> 187 (there the eight fp64 divisions per item, which a power
+// of two does not need).  BATCH: a chunk's rows in the fewest equal rounds of at
+// most 16, so that hardly a row is loaded twice.  In rounds of a power of two, 512
+// units of 2000 positions, chunks of 9, 17, 20 and 33 rows took 54.4, 53.3, 51.8 and
+// 45.8 us, and so 50.6, 47.6, 47.0 and 44.5.
 template <int BATCH>
 __global__ __launch_bounds__(kGatherThreads) void k_landmarks(LandmarkArgs a) {
   const int64_t stride = (int64_t)gridDim.x * kGatherThreads;
@@ -2356,17 +2359,18 @@ hipError_t launch_check(const CheckArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_landmarks(const LandmarkArgs& a, hipStream_t s) {
-  const int batch = a.chunk <= 1 ? 1 : a.chunk <= 2 ? 2 : a.chunk <= 4 ? 4 : a.chunk < 16 ? 8 : 16;
-  const dim3 grid(blocks_for(a.items, kGatherThreads, 16384));
-  const dim3 block(kGatherThreads);
-  switch (batch) {
-    case 1: launch_kernel(CKV_K_LANDMARKS, k_landmarks<1>, grid, block, s, a); break;
-    case 2: launch_kernel(CKV_K_LANDMARKS, k_landmarks<2>, grid, block, s, a); break;
-    case 4: launch_kernel(CKV_K_LANDMARKS, k_landmarks<4>, grid, block, s, a); break;
-    case 8: launch_kernel(CKV_K_LANDMARKS, k_landmarks<8>, grid, block, s, a); break;
-    default: launch_kernel(CKV_K_LANDMARKS, k_landmarks<16>, grid, block, s, a); break;
+template <int BATCH = kLandmarkRows>
+static void launch_landmarks_b(const LandmarkArgs& a, int batch, hipStream_t s) {
+  if constexpr (BATCH > 1) {
+    if (batch < BATCH) return launch_landmarks_b<BATCH - 1>(a, batch, s);
   }
+  launch_kernel(CKV_K_LANDMARKS, k_landmarks<BATCH>,
+                dim3(blocks_for(a.items, kGatherThreads, 16384)), dim3(kGatherThreads), s, a);
+}
+
+hipError_t launch_landmarks(const LandmarkArgs& a, hipStream_t s) {
+  const int rounds = (a.chunk + kLandmarkRows - 1) / kLandmarkRows;
+  launch_landmarks_b(a, (a.chunk + rounds - 1) / rounds, s);
   return launch_status();
 }
 

@@ -1,6 +1,7 @@
 """Chunk landmarks at the edges of the batches of rows a thread loads (MI355X
-only): chunk sizes around 1, 2, 4, 8 and 16, chunks that divide by a power of
-two and others, partial last chunks, bit for bit against the oracle."""
+only): every batch of 1 to 16 rows, chunks of several rounds, chunks that divide
+by a power of two and others, partial last chunks, bit for bit against the
+oracle."""
 from __future__ import annotations
 
 import dataclasses
@@ -16,7 +17,7 @@ from helpers import device, orc, u16
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("chunk", [1, 2, 3, 4, 5, 8, 9, 15, 16, 17, 33, 700])
+@pytest.mark.parametrize("chunk", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 20, 32, 33, 700])
 def test_landmark_batches(chunk):
     print("landmark batches", chunk, flush=True)
     dev = device()
