@@ -390,24 +390,6 @@ SelectArgs select_args(const Dims& d, const Layout& L, void* ws, const float* sc
   return a;
 }
 
-// Least range of a pass that adds its histograms: every range adds one per unit
-// it meets, and the atomics on a unit's few dozen crowded bins queue.  One unit
-// of 124 Ki positions (3886 groups), attend-and-score launch: 8 groups per
-// range 51 us, 16: 32, 24: 26.6, 32: 25; 3 units of 34 to 124 Ki, two tokens:
-// 18 groups 38, 19: 32, 24: 29, 32: 27.3.  Large batches have longer ranges.
-// Units of few groups keep at least kAddedUnitRanges ranges, as ranges of 32
-// leave workgroups without work then.  32 units of 6000 positions, pipelined, at
-// least 2, 12, 16, 24 and 32 groups: 29.8, 30.3, 26.6, 29.2, 30.9 us; chunked in 8 (24
-// groups per unit), 2 and 32 groups: 25.2, 33.5; of 12000, pipelined, 24 and 32:
-// 39.1, 35.7.
-constexpr int kAddedMinRange = 32;
-constexpr int kAddedUnitRanges = 12;
-
-int added_min_range(int max_ctx) {
-  const int gu = (max_ctx + kStageRows - 1) / kStageRows;
-  return std::min(kAddedMinRange, (gu + kAddedUnitRanges - 1) / kAddedUnitRanges);
-}
-
 // Scoring arguments; with sel set, the pass counts the first digit into that
 // selection's histograms, and a pipelined launch with enough work may take
 // it as claims from the selection's claim counter (unit 0's control word
@@ -435,7 +417,7 @@ ScoreArgs score_args(const Dims& d, const Layout& L, const uint16_t* q,
   a.units = d.U;
   a.chunk = 1;
   a.hist_part = nullptr;
-  a.min_range = sel ? added_min_range(d.max_ctx) : 1;  // slots set their own
+  a.min_range = sel ? added_min_range(groups_of(d.max_ctx)) : 1;  // slots set their own
   a.stored = d.B > kScanRequests;
   a.tails = 0;
   a.q2 = nullptr;
@@ -476,16 +458,12 @@ AttnArgs attn_args(const Dims& d, const Layout& L, void* ws, const uint16_t* q,
 // selection counts itself (self_counts) or the histograms are added into
 // cleared per-unit counts.
 bool use_partials(const Dims& d, const Layout& L, int nwg, int slots = kMaxPartials) {
-  if (!L.hist_part_bytes || d.max_ctx > kFusedSelectMaxCtx || nwg < 1) return false;
-  // a unit's gu groups meet at most ceil(gu / shortest range) + 1 ranges
-  const int64_t gu = (d.max_ctx + kStageRows - 1) / kStageRows;
-  const int64_t shortest = gu * d.U / nwg;
-  return shortest >= 1 && (gu + shortest - 1) / shortest + 1 <= slots;
+  return L.hist_part_bytes && d.max_ctx <= kFusedSelectMaxCtx && nwg >= 1 &&
+         slots_fit(groups_of(d.max_ctx), d.U, nwg, slots);
 }
 
 void set_partials(void* ws, const Layout& L, int nwg, ScoreArgs* sc, SelectArgs* sa) {
-  const int64_t gu = (sc->max_ctx + kStageRows - 1) / kStageRows;
-  sc->min_range = sa->min_range = min_range_groups(gu, kMaxPartials);
+  sc->min_range = sa->min_range = min_range_groups(groups_of(sc->max_ctx), kMaxPartials);
   sc->hist_part = at<uint32_t>(ws, L.hist_part);
   sa->hist_part = sc->hist_part;
   sa->score_nwg = nwg;
@@ -498,9 +476,10 @@ void set_partials(void* ws, const Layout& L, int nwg, ScoreArgs* sc, SelectArgs*
 // 4096 positions 26.7 -> 18.4 us, 24 units of 16384 43.7 -> 40.9, 8 units of
 // 24001 36.1 -> 34.1; counting grows with the context (equal scores serialise
 // in LDS) and loses from 32 Ki (16 units: 55.5 -> 56.1, of 64 Ki pipelined
-// 69.7 -> 72.8).  Batches of 25 to about 36 units, too few for slots, keep the
-// cleared and added form (which the tests ask of 32 units of 6000 positions,
-// though those too would gain, 29.6 -> 25.1).
+// 69.7 -> 72.8).  Batches of 25 to 36 units, too few for slots, clear and add:
+// there the paths differ.  32 units of 6000 positions, added against
+// self-counted: same step 33.5 / 28.7 us, chunked in two 30.1 / 25.4, but four
+// layers of the loop 101.9 / 110.1 (of 12000: 142.9 / 149.5).
 constexpr int kSelfCountUnits = 24;
 constexpr int kSelfCountMaxCtx = 24576;
 
@@ -1070,7 +1049,9 @@ int ckv::critical_impl(const ckv_shape* shape, const uint16_t* q_att, const uint
   ScoreArgs sc = score_args(d, L, q_sel, k_score, ctx_lens, scale, scores, &sa);
   int nwg = score_blocks(
       sc, d.G, !pipelined ? ScoreKind::kHist : in_place ? ScoreKind::kDualIndexed : ScoreKind::kDual);
-  // same-step calls of shorter contexts read one round of slots at most
+  // same-step calls of shorter contexts: slots where a full batch needs one round
+  // of loads for them (ragged ones may need a second).  32 units of 6000 positions,
+  // added histograms against up to 16 slots: 33.5 / 31.5 us
   const int slots = pipelined || d.max_ctx > kSelfCountMaxCtx ? kMaxPartials : kFirstPartials;
   bool partials = use_partials(d, L, nwg, slots);
   // the previous layer's pending selection joins this launch when this

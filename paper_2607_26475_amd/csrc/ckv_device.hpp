@@ -20,7 +20,7 @@ constexpr int kStageDwords = kStageRows * kStageRowDwords;
 constexpr int kFlushGroups = 64;   // groups of scores held per wave in LDS
 constexpr int kClaimGroups = 64;   // groups per claim of the dynamic scoring pass
 constexpr int kStaticEighths = 4;  // of a unit's claims, those scored as static ranges
-constexpr int kMinClaimsPerWg = 4; // claims per workgroup from which a pass takes claims
+constexpr int kMinClaimsPerWg = 4; // claims, static ones included, from which a pass takes them
 constexpr int kScoreLdsDwords = 4 * kStageDwords + 4 * kFlushGroups * kStageRows;
 
 // Selection: the first radix digit is the top 11 bits of the order key; a
@@ -43,7 +43,8 @@ constexpr int kFusedSelectMaxCtx = 65536;
 // Scoring grids are capped at kMaxScoreWgs workgroups.  With per-workgroup
 // histograms (ScoreArgs::hist_part) the histogram of unit u is the sum of the
 // slots u + wg over the workgroups wg whose range meets the unit's groups
-// below n_b (both sides derive the ranges from ctx_lens); slot u + wg is
+// below n_b (both sides derive the ranges from ctx_lens, or, for many requests,
+// from the stored positions); slot u + wg is
 // unique because ranges and units are both in group order.  The selection
 // reads at most kMaxPartials slots per unit (min_range keeps it so), the first
 // kFirstPartials of them in one round trip; batches of so few units that a unit
@@ -411,7 +412,7 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
 // kernel, units x, x + 8, ... of XCD x.  Valid groups fit in 32 bits: a group is
 // 8 KiB of keys.  All functions are wave-uniform and need all 64 lanes.
 template <int ROWS = kStageRows>
-__device__ __forceinline__ uint32_t groups_of(int n) {
+__host__ __device__ __forceinline__ uint32_t groups_of(int n) {
   return ((uint32_t)n + ROWS - 1) / ROWS;
 }
 
@@ -524,20 +525,62 @@ __device__ __forceinline__ GroupItem find_item(const RangeLens<LEN>& L, const Gr
 
 // The rows of a unit of n positions that a pass with claims scores as static
 // ranges before it takes claims: whole claims, and never the last one.
-__device__ __forceinline__ int static_rows(int n) {
+__host__ __device__ __forceinline__ int static_rows(int n) {
   constexpr int kRows = kClaimGroups * kStageRows;
   return (int)((groups_of<kRows>(n) * kStaticEighths) >> 3) * kRows;
 }
 
 // Groups per range: an equal share of the total, at least min_range (the host
 // sets it so that no unit meets more than kMaxPartials ranges when the
-// histograms go to slots, else 1).
-__device__ __forceinline__ uint32_t range_groups(uint32_t total, int nwg, int min_range) {
-  return max((total + (uint32_t)nwg - 1u) / (uint32_t)nwg, (uint32_t)min_range);
+// histograms go to slots, else 1 or added_min_range).
+__host__ __device__ __forceinline__ uint32_t range_groups(uint32_t total, int nwg, int min_range) {
+  const uint32_t even = (total + (uint32_t)nwg - 1u) / (uint32_t)nwg;
+  return even > (uint32_t)min_range ? even : (uint32_t)min_range;
+}
+// Workgroup wg's groups [g0, g1) of ranges of R.
+struct GroupRange {
+  uint32_t g0, g1;
+};
+__host__ __device__ __forceinline__ GroupRange range_of(int wg, uint32_t R, uint32_t total) {
+  const uint64_t a = (uint64_t)wg * R, b = a + R;
+  return GroupRange{(uint32_t)(a < total ? a : total), (uint32_t)(b < total ? b : total)};
 }
 // A unit's vg <= gu groups meet at most floor((gu - 1) / R) + 2 ranges of R.
 __host__ __device__ __forceinline__ int min_range_groups(int64_t gu, int max_slots) {
   return (int)((gu - 1) / (max_slots - 1)) + 1;
+}
+// The ranges that hold a unit's groups [before, before + mine): the first, and
+// how many (0 for a unit without groups).
+struct UnitRanges {
+  uint32_t first, count;
+};
+__host__ __device__ __forceinline__ UnitRanges unit_ranges(uint32_t before, uint32_t mine,
+                                                           uint32_t R) {
+  const uint32_t lo = before / R;
+  return UnitRanges{lo, mine ? (before + mine - 1u) / R - lo + 1u : 0u};
+}
+// Whether units of gu stored groups, all of them valid, meet at most `slots` of
+// nwg ranges, as estimated from their even share: the rule that gives a pass
+// slots.  Ragged batches may meet more; min_range_groups then bounds them.
+inline bool slots_fit(int64_t gu, int64_t units, int nwg, int slots) {
+  const int64_t share = gu * units / nwg;
+  return share >= 1 && (gu + share - 1) / share + 1 <= slots;
+}
+// Least range of a pass that adds its histograms: every range adds one per unit
+// it meets, and the atomics on a unit's few dozen crowded bins queue.  One unit
+// of 124 Ki positions (3886 groups), attend-and-score launch: 8 groups per
+// range 51 us, 16: 32, 24: 26.6, 32: 25; 3 units of 34 to 124 Ki, two tokens:
+// 18 groups 38, 19: 32, 24: 29, 32: 27.3.  Large batches have longer ranges.
+// Units of few groups keep at least kAddedUnitRanges ranges, as ranges of 32
+// leave workgroups without work then.  32 units of 6000 positions, pipelined, at
+// least 2, 12, 16, 24 and 32 groups: 29.8, 30.3, 26.6, 29.2, 30.9 us; chunked in 8 (24
+// groups per unit), 2 and 32 groups: 25.2, 33.5; of 12000, pipelined, 24 and 32:
+// 39.1, 35.7.
+constexpr int kAddedMinRange = 32;
+constexpr int kAddedUnitRanges = 12;
+inline int added_min_range(int64_t gu) {
+  const int64_t part = (gu + kAddedUnitRanges - 1) / kAddedUnitRanges;
+  return (int)(part < kAddedMinRange ? part : kAddedMinRange);
 }
 
 // The one-launch same-step kernel's scoring ranges are XCD-affine: its
@@ -593,10 +636,9 @@ __device__ __forceinline__ SlotRange hist_slots(const SelectArgs& a, int unit) {
     mine = groups_of(__builtin_amdgcn_readfirstlane(valid(item)));
     before = mult * wave_sum_u32(low) + h * mine;
   }
-  const uint32_t R = range_groups(mult * total, nwg, a.min_range);
-  const uint32_t lo = before / R, hi = (before + mine - 1u) / R;
-  return SlotRange{a.affine ? (int64_t)x * (ni + nwg) + item + lo : (int64_t)unit + lo,
-                   mine ? (int)(hi - lo + 1u) : 0};
+  const UnitRanges r = unit_ranges(before, mine, range_groups(mult * total, nwg, a.min_range));
+  return SlotRange{a.affine ? (int64_t)x * (ni + nwg) + item + r.first : (int64_t)unit + r.first,
+                   (int)r.count};
 }
 
 // Inclusive prefix sum over a workgroup of NW waves.  `tmp` is LDS scratch of

@@ -52,8 +52,8 @@ __device__ __forceinline__ void store_hist(const uint32_t* lds_hist, uint32_t* s
         *reinterpret_cast<const uint4*>(lds_hist + kPer * t + i);
 }
 
-// The workgroup's LDS histogram as its slot, device-coherent, 8 bytes per lane with consecutive lanes on consecutive
-// words (NT threads).
+// The workgroup's LDS histogram as its slot, device-coherent, 8 bytes per lane
+// with consecutive lanes on consecutive words (NT threads).
 template <int NT>
 __device__ __forceinline__ void store_hist_coherent(const uint32_t* lds_hist, uint32_t* slot) {
   constexpr int kPairs = kHistBins / NT / 2;
@@ -273,8 +273,8 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
   GroupScan scan;
   const uint32_t total = mult * sum_groups(len, &scan);
   const uint32_t R = range_groups(total, nwr, a.min_range);
-  const uint32_t g0 = (uint32_t)min((uint64_t)wr * R, (uint64_t)total);
-  const uint32_t g1 = (uint32_t)min((uint64_t)g0 + R, (uint64_t)total);
+  const GroupRange range = range_of(wr, R, total);
+  const uint32_t g0 = range.g0, g1 = range.g1;
   if (g0 >= g1) return;  // uniform over the workgroup
   GroupItem it = find_item(len, scan, mult, g0);
   uint32_t* stage = lds_stage + (active ? wave : 0) * kStageDwords;
@@ -467,7 +467,8 @@ __device__ __forceinline__ void score_range(const ScoreArgs& a, int wg, int nwg,
 // and prefetches that claim's first group across the boundary.  A
 // workgroup thus holds up to two claims it has not started, which leaves
 // workgroups idle at the end unless there are several claims per workgroup:
-// the host uses claims from four per workgroup.  (Taking the next claim
+// the host uses claims from four of stored positions per workgroup, static ones
+// included.  (Taking the next claim
 // later, two rounds before the current claim's end, made the
 // million-token loop's gather beside the pass slower.)  Each workgroup takes
 // exactly one claim at or past the total; those take values total ..

@@ -1,8 +1,9 @@
 """Claims in the pipelined scoring pass (MI355X only).
 
 A pipelined attend-and-score launch whose scoring adds its first-digit
-histograms (contexts above 65536 positions) takes its work as claims of 64
-groups of 32 positions from a counter when the pass has at least four claims
+histograms (contexts above 65536 positions) scores half of each unit's claims,
+whole claims of 64 groups of 32 positions, as static ranges and takes the rest
+from a counter, when the pass has at least four claims, static ones included,
 per scoring workgroup; the workgroup that takes the last claim resets the
 counter.  These cases are the smallest shapes that take claims on the device
 (16 units of 2^18 positions: 2048 claims for 512 resident workgroups), with

@@ -1,67 +1,60 @@
-"""Bookkeeping of the per-workgroup histograms, by brute force (no GPU).
+"""Which batches get per-workgroup histogram slots, and how many a unit has, by
+brute force (no GPU).
 
-The scoring pass splits T = units x groups-per-unit groups of keys into nwg
-contiguous ranges, [wg*T/nwg, (wg+1)*T/nwg).  A workgroup stores the
-histogram of each unit it meets as slot unit + wg (zeros when its groups of
-the unit all lie past n_b), and the selection of a unit sums the slots of the
-workgroups that own its first and last group and every one between.  These
-checks enumerate the ranges directly; the selection's reading is the case
-where every group of the unit counts.
-Slots must be unique.  The owner of a group, computed as
-((g + 1) * nwg - 1) // T, must be the range that holds it.  The workgroups
-between the two owners must be exactly those whose range meets the unit's
-valid groups.  And the bound the library uses to pick this mode,
-ceil(gu / floor(T / nwg)) + 1, must cover the slot count of every unit.
+The library's own functions, compiled for the host.  slots_fit promises from
+the stored shape alone that the units of a full batch meet at most `slots` of
+the even ranges.  With slots the ranges are at least min_range_groups long, so
+that no unit of any batch meets more than the selection reads; slots must be
+unique and below units + nwg.
 """
 from __future__ import annotations
 
 import numpy as np
 import pytest
 
-
-def owner(g, T, nwg):
-    return ((g + 1) * nwg - 1) // T
-
-
-def ranges(T, nwg):
-    return [(T * wg // nwg, T * (wg + 1) // nwg) for wg in range(nwg)]
-
+from native_ranges import lib, pair
 
 CASES = [(1, 1, 1), (2, 5, 3), (128, 1024, 512), (128, 94, 512), (256, 47, 512), (16, 7, 100),
-         (3, 1000, 7), (64, 4096, 1024), (5, 3, 15)]
+         (3, 1000, 7), (64, 4096, 1024), (5, 3, 15), (16, 1024, 256), (24, 1024, 256),
+         (36, 188, 256), (40, 188, 256), (520, 10, 256)]
 
 
 @pytest.mark.parametrize("U,gu,nwg", CASES)
-def test_owner_and_slots(U, gu, nwg):
-    T = U * gu
-    nwg = min(nwg, T)  # the grid never has more workgroups than groups
-    rs = ranges(T, nwg)
-    assert rs[0][0] == 0 and rs[-1][1] == T
-    assert all(a < b for a, b in rs), "every range holds a group"
-    for wg, (a, b) in enumerate(rs):
-        for g in range(a, b):
-            assert owner(g, T, nwg) == wg
-    slots = set()
-    for wg, (a, b) in enumerate(rs):
-        for u in range(a // gu, (b - 1) // gu + 1):  # units this range meets
-            s = u + wg
-            assert s not in slots, (u, wg)
-            slots.add(s)
-    assert max(slots) < U + nwg
+def test_slots_fit_full_batches(U, gu, nwg):
+    so = lib()
+    nwg = min(nwg, U * gu)  # the grid never has more workgroups than groups
+    R = so.t_range_groups(U * gu, nwg, 1)
+    most = max(pair(so.t_unit_ranges, u * gu, gu, R)[1] for u in range(U))
+    for slots in range(2, 40):
+        if so.t_slots_fit(gu, U, nwg, slots):
+            assert most <= slots
+    # the promise is within two of what the units meet
+    assert so.t_slots_fit(gu, U, nwg, most + 2 + (gu * U) % nwg)
 
 
 @pytest.mark.parametrize("U,gu,nwg", CASES)
-def test_select_covers_the_writers(U, gu, nwg):
-    T = U * gu
-    nwg = min(nwg, T)
-    rs = ranges(T, nwg)
-    shortest = T // nwg
-    bound = -(-gu // shortest) + 1
+def test_slots_of_ragged_batches(U, gu, nwg):
+    so = lib()
+    nwg, most = min(nwg, U * gu), so.t_max_partials()
     rng = np.random.default_rng(U * 7 + gu)
-    for u in range(U):
-        g0 = u * gu
-        for vg in sorted({1, gu, int(rng.integers(1, gu + 1))}):  # valid groups of the unit
-            lo, hi = owner(g0, T, nwg), owner(g0 + vg - 1, T, nwg)
-            writers = [wg for wg, (a, b) in enumerate(rs) if a < g0 + vg and b > g0]
-            assert writers == list(range(lo, hi + 1)), (u, vg)
-            assert hi - lo + 1 <= bound, (u, vg, hi - lo + 1, bound)
+    for trial in range(8):
+        vg = rng.integers(0, gu + 1, size=U) if trial else np.eye(1, U, U // 2, dtype=int)[0] * gu
+        R = so.t_range_groups(int(vg.sum()), nwg, so.t_min_range_groups(gu, most))
+        seen, base = set(), 0
+        for u, g in enumerate(vg.tolist()):
+            first, count = pair(so.t_unit_ranges, base, g, R)
+            assert count <= most, (u, g)
+            for s in range(u + first, u + first + count):
+                assert s not in seen and s < U + nwg
+                seen.add(s)
+            base += g
+
+
+@pytest.mark.parametrize("units,fit8,fit16", [(16, 0, 0), (18, 0, 1), (24, 0, 1), (36, 0, 1),
+                                              (37, 1, 1), (40, 1, 1)])
+def test_slots_edge(units, fit8, fit16):
+    """256 workgroups and 32 Ki positions: 8 slots from 37 units, 16 from 18."""
+    so = lib()
+    gu = so.t_groups_of(32768)
+    assert so.t_slots_fit(gu, units, 256, 8) == fit8
+    assert so.t_slots_fit(gu, units, 256, 16) == fit16
