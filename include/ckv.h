@@ -418,8 +418,8 @@ int ckv_pipeline_destroy(ckv_pipeline* pipe);
  * pinned sources: 80 workgroups when max_ctx >= 64 k (the scoring pass then
  * reads at least 32 times the bytes the link carries per layer), 64 or 128
  * when max_ctx >= 16 k and a refill has at most 16384 or 32768 rows, else 192
- * up to 262144 rows and 256 beyond; device sources as ckv_gather_kv.  0 <= workgroups <= 4096, else
- * CKV_EINVAL. */
+ * up to 262144 rows and 256 beyond; device sources as ckv_gather_kv.
+ * 0 <= workgroups <= 4096, else CKV_EINVAL. */
 int ckv_pipeline_set_gather_width(ckv_pipeline* pipe, int workgroups);
 
 /* For tests of the event protocol only, never for serving: breaks the
@@ -572,10 +572,10 @@ int ckv_set_debug(int on);
  * the group size is 2, 4 or 8, the batch has a multiple of 8 units with two
  * workgroups per unit fitting on the device, 512 <= k <= 2048, max_ctx <=
  * 65536, and the per-workgroup histogram slots apply (at least about 40
- * units).  Each unit's selection
- * and attention then start as soon as that unit's scores are complete (Sec. 2.2
- * selection inside the step, with the attention of Sec. 5.3-5.4), not after
- * the whole scoring pass.  The launch hands each unit's scores over through
+ * units, 24 above 24576 positions).  Each unit's selection and attention then
+ * start as soon as that unit's scores are complete (Sec. 2.2 selection inside
+ * the step, with the attention of Sec. 5.3-5.4), not after the whole scoring
+ * pass.  The launch hands each unit's scores over through
  * flags in the workspace, which are zero again when it ends.  Each of a
  * unit's two workgroups selects the unit's set; by default each then attends
  * over half of the set's rows with all of the group's heads, and the second
