@@ -819,6 +819,15 @@ def measure_pipelined_hbm(torch, ckv, layers, kv_ptrs, shape, w, scale, steps, s
 _STREAMS = []
 
 
+def refill_workgroups(n, k, rows):
+    """Workgroups the loop chooses for a refill of `rows` rows from pinned memory."""
+    if n >= 64 * k:
+        return 80
+    if n >= 16 * k and rows <= 32768:
+        return 64 if rows <= 16384 else 128
+    return 192 if rows <= 262144 else 256
+
+
 def _pipeline_streams(torch):
     """The compute and copy streams of every decode loop.  The runtime gives
     a stream its hardware queue at the stream's first use, a fresh one while
@@ -998,7 +1007,7 @@ def measure_pipeline(torch, ckv, synth, dev, np, host_link, wl="long128k", n_hbm
                                        for kname, v in stats.items()},
                "overlap": (gather_ms + compute_ms) / ms,
                "refill_GBps": B * Hkv * k * 2 * d * 2 / (gather_ms / L * 1e-3) / 1e9,
-               "gather_workgroups": gather_width or ("auto: 80" if n >= 64 * k else "auto: 256")}
+               "gather_workgroups": gather_width or f"auto: {refill_workgroups(n, k, B * Hkv * k)}"}
         if corrected:  # the misses cross the link too, on the compute stream
             found = sum(int(hits[t][l].sum()) for t in range(first, first + steps)
                         for l in range(L))
