@@ -1879,10 +1879,17 @@ __global__ __launch_bounds__(kGatherThreads) void k_miss_fill(GatherArgs g, Reco
   __shared__ __attribute__((aligned(16))) RecLds lds;
   if ((int)blockIdx.x < nfetch)
     gather_range(g, blockIdx.x, nfetch);
-  else if (r.rank <= kRecFewRanks)  // uniform
-    reconstruct_few(r, blockIdx.x - nfetch, gridDim.x - nfetch);
   else
     reconstruct_range(r, blockIdx.x - nfetch, gridDim.x - nfetch, lds);
+}
+
+// The same with few ranks (kRecFewRanks).
+__global__ __launch_bounds__(kGatherThreads) void k_miss_fill_few(GatherArgs g, ReconArgs r,
+                                                                  int nfetch) {
+  if ((int)blockIdx.x < nfetch)
+    gather_range(g, blockIdx.x, nfetch);
+  else
+    reconstruct_few(r, blockIdx.x - nfetch, gridDim.x - nfetch);
 }
 
 // ---- fixed scratch for callers that cannot allocate -------------------------
@@ -2396,8 +2403,11 @@ hipError_t launch_miss_fill(const GatherArgs& g, int fetch_blocks, const ReconAr
                             hipStream_t s) {
   const int nf = blocks_for(g.items, kGatherThreads * kGatherUnroll, fetch_blocks);
   const int nr = reconstruct_blocks(r);
-  launch_kernel(CKV_K_RECONSTRUCT, k_miss_fill, dim3(nf + nr), dim3(kGatherThreads), s, g, r,
-                nf);
+  const dim3 grid(nf + nr), block(kGatherThreads);
+  if (r.rank <= kRecFewRanks)
+    launch_kernel(CKV_K_RECONSTRUCT, k_miss_fill_few, grid, block, s, g, r, nf);
+  else
+    launch_kernel(CKV_K_RECONSTRUCT, k_miss_fill, grid, block, s, g, r, nf);
   return launch_status();
 }
 

@@ -103,6 +103,10 @@ LOWRANK_CASES = [
     ("llama8b_s", "half", ckv.SRC_HOST_PINNED, 64),
     ("tiny", "exact", ckv.SRC_DEVICE, 8),
     ("tiny", "empty", ckv.SRC_HOST_PINNED, 8),
+    # on both sides of the ranks that one thread sums
+    ("dual64_s", "half", ckv.SRC_DEVICE, 3),
+    ("dual64_s", "disjoint", ckv.SRC_HOST_PINNED, 8),
+    ("dual64_s", "disjoint", ckv.SRC_DEVICE, 9),
 ]
 
 
